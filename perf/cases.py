@@ -191,6 +191,118 @@ def work(case):
     return {"bytes": 4 * tensor + extra, "flops": attention + scoring}
 
 
+def _philox(ctr, key):
+    """Philox4x32-10 of int64 tensors holding 32-bit words, ctr = 4 words, key = 2 ints -> 4 words"""
+    low = 0xFFFFFFFF
+    c, (k0, k1) = list(ctr), key
+    for _ in range(10):
+        # the 64-bit product of two 32-bit words from two 48-bit ones (int64 would overflow)
+        hi, lo = [], []
+        for m, x in ((0xD2511F53, c[0]), (0xCD9E8D57, c[2])):
+            a, b = m * (x & 0xFFFF), m * (x >> 16)
+            t = a + ((b & 0xFFFF) << 16)
+            lo.append(t & low)
+            hi.append((b >> 16) + (t >> 32))
+        c = [hi[1] ^ c[1] ^ k0, lo[1], hi[0] ^ c[3] ^ k1, lo[0]]
+        k0, k1 = (k0 + 0x9E3779B9) & low, (k1 + 0xBB67AE85) & low
+    return c
+
+
+def _select(scores, head, k_sel, seed, gumbel):
+    """the k_sel largest of one head's logits plus the seeded bias -> ascending block numbers per row"""
+    nb = scores.shape[0]
+    i = torch.arange(nb, device=scores.device)[:, None].expand(nb, -(-nb // 4))
+    j4 = torch.arange(-(-nb // 4), device=scores.device)[None, :].expand_as(i)
+    words = _philox((j4, i, torch.full_like(i, head), torch.zeros_like(i)), (seed, 0))
+    u = torch.stack(words, dim=-1).reshape(nb, -1)[:, :nb]
+    if gumbel:
+        bias = -torch.log(-torch.log(((u >> 9).double() + 0.5) * 2.0 ** -23))
+    else:
+        bias = ((torch.where(u >= 2 ** 31, u - 2 ** 32, u)) >> 8).double() * 2.0 ** -23
+    top = torch.sort(scores + AMP * bias, dim=1, descending=True, stable=True).indices[:, :k_sel]
+    return torch.sort(top, dim=1).values
+
+
+def exact(case, seed):
+    """What run() returns, in 64 bits, straight from the definition of the path (None where that takes too long)."""
+    c, path = case, case["path"]
+    if work(c)["flops"] > 8e12:
+        return None
+    s = prepare(c, seed)
+    if path == "l1":
+        return (s["a"].double() - s["b"].double()).abs().mean().reshape(1)
+    q4, k4, v4 = s["q"], s["k"], s["v"]
+    n, d, b, B, H = _n(c), c["d"], c["block"], c["batch"], c["heads"]
+    nb, scale, dev = -(-n // b), c["d"] ** -0.5, q4.device
+    pad = nb * b - n
+    size = torch.full((nb,), b, dtype=torch.float64, device=dev)
+    size[-1] = b - pad
+    group = min(c["group"], nb)
+    k_sel = max(1, min(nb, int(c["keep"] * nb + 0.5)))
+    bits = 2 ** torch.arange(32, device=dev)
+    outs, lses, all_scores, lists, masks = [], [], [], [], []
+    for head in range(B * H):
+        # [blocks, tokens of a block, d], zero beyond the last token
+        q, k, v = (torch.nn.functional.pad(t[head // H, head % H].double(), (0, 0, 0, pad)).view(nb, b, d) for t in (q4, k4, v4))
+        if path == "dense":
+            o, l = [], []
+            for r in range(0, n, 1024):
+                z = q.view(-1, d)[r:min(r + 1024, n)] @ k.view(-1, d)[:n].T * scale
+                l.append(torch.logsumexp(z, dim=1))
+                o.append(torch.exp(z - l[-1][:, None]) @ v.view(-1, d)[:n])
+            outs.append(torch.cat(o))
+            lses.append(torch.cat(l))
+            continue
+        kbar, vsum = k.sum(1) / size[:, None], v.sum(1)
+        scores = (q.sum(1) / size[:, None]) @ kbar.T * scale
+        if path != "select":
+            cov = k.transpose(1, 2) @ v - kbar[:, :, None] * vsum[:, None, :]
+            of_group = torch.arange(nb, device=dev) // group
+            n_groups = int(of_group[-1]) + 1
+            member = torch.nn.functional.one_hot(of_group, n_groups).double()
+            mean_cov = (member.T @ cov.reshape(nb, -1) / member.sum(0)[:, None]).view(n_groups, d, d)
+            if path == "stages":
+                scores = scores + torch.log((cov - mean_cov[of_group]).flatten(1).norm(dim=1) + 1e-6)
+            del cov
+        idx = s["idx"].view(B * H, nb, k_sel)[head].long() if path == "static" else _select(scores, head, k_sel, s["seed"], c["gumbel"])
+        lists.append(idx)
+        chosen = torch.zeros((nb, -(-nb // 32) * 32), dtype=torch.bool, device=dev)
+        chosen.scatter_(1, idx, True)
+        if path == "select":
+            word = (chosen.view(nb, -1, 32) * bits).sum(-1)
+            masks.append(torch.where(word >= 2 ** 31, word - 2 ** 32, word).to(torch.int32))
+            all_scores.append(scores)
+            continue
+        ragged = torch.arange(nb * b, device=dev).view(nb, b) >= n
+        o, l = [], []
+        step = max(1, int(2 ** 26 / (k_sel * b * d)))
+        for r in range(0, nb, step):
+            rows, qr = idx[r:r + step], q[r:r + step] * scale
+            m = rows.shape[0]
+            z = qr @ k[rows].view(m, -1, d).transpose(1, 2)
+            z = z.masked_fill(ragged[rows].view(m, 1, -1), -math.inf)
+            za = (qr @ kbar.T).masked_fill(chosen[r:r + step, None, :nb], -math.inf)
+            top = torch.maximum(z.amax(-1), za.amax(-1))[..., None]
+            p, a = torch.exp(z - top), torch.exp(za - top)
+            den = p.sum(-1) + a @ size
+            num = p @ v[rows].view(m, -1, d) + a @ vsum
+            weight = a @ member
+            for g in range(n_groups):
+                num += weight[..., g:g + 1] * (qr @ mean_cov[g])
+            o.append(num / den[..., None])
+            l.append(top[..., 0] + torch.log(den))
+        outs.append(torch.cat(o).view(-1, d)[:n])
+        lses.append(torch.cat(l).view(-1)[:n])
+    if path == "select":
+        return torch.stack(all_scores), torch.stack(lists).int(), torch.stack(masks)
+    out = torch.stack(outs).view(B, H, n, d)
+    if path == "forward":
+        return out, torch.stack(lists).int()
+    if path == "stages":
+        return out, torch.stack(lses), torch.stack(lists).int()
+    return out, torch.stack(lses)
+
+
 def tolerance(case):
     """About four times what was measured: outputs against the fp64 oracle (2-norm 1.7e-3, largest 6e-3) and against the
     same path summed in another order (key-range slices: 6e-4, largest 8e-3); bf16 rounding of P and O sets both."""
