@@ -166,15 +166,13 @@ def vr(base, n=1):
 
 
 def max_stream(S):
-    """T0 = c * max over the lane's 16 logits v[S:S+15] and those of lane ^ 32"""
+    """T0 = c * max over the lane's 16 logits v[S:S+15]"""
     s = lambda i: vr(S + i)
     t0, t1 = vr(FS_T), vr(FS_T + 1)
     return [f"v_max3_f32 {t0}, {s(0)}, {s(1)}, {s(2)}", f"v_max3_f32 {t1}, {s(8)}, {s(9)}, {s(10)}",
             f"v_max3_f32 {t0}, {t0}, {s(3)}, {s(4)}", f"v_max3_f32 {t1}, {t1}, {s(11)}, {s(12)}",
             f"v_max3_f32 {t0}, {t0}, {s(5)}, {s(6)}", f"v_max3_f32 {t1}, {t1}, {s(13)}, {s(14)}",
-            f"v_max3_f32 {t0}, {t0}, {s(7)}, {s(15)}", f"v_max_f32 {t0}, {t0}, {t1}",
-            f"v_mov_b32 {t1}, {t0}", "s_nop 1", f"v_permlane32_swap_b32 {t0}, {t1}", "s_nop 0",
-            f"v_max_f32 {t0}, {t0}, {t1}", f"v_mul_f32 {t0}, %[c], {t0}"]
+            f"v_max3_f32 {t0}, {t0}, {s(7)}, {s(15)}", f"v_max_f32 {t0}, {t0}, {t1}", f"v_mul_f32 {t0}, %[c], {t0}"]
 
 
 def exp_stream(S, P, convert=True):
@@ -207,8 +205,11 @@ def convert_stream(S, P):
 
 
 def raise_max(n_o, now, also=()):
-    """after max_stream: if the maximum grew for some lane, m <- max(m, T0), T3 = exp2(m_old - m), l *= T3, and
-    either the accumulators too (now) or the wave-uniform decision is left in %[flag] for later.
+    """after max_stream: if the maximum grew for some lane, m <- max(m, T0 of both lanes of the query), T3 = exp2(m_old - m),
+    l *= T3, and either the accumulators too (now) or the wave-uniform decision is left in %[flag] for later.
+    The lane's own maximum decides: both lanes of a query hold the same m, so one of them sees the growth, and the exchange
+    with lane ^ 32 (four instructions and their wait states in the middle of a dependence chain) is only made then, in about
+    every fourth half.
     The conditional part is one item: it must not be split up (nothing else may sit between branch and label)."""
     t0, t1, t2, t3 = (vr(FS_T + i) for i in range(4))
     tag = "a" if now else "b"
@@ -216,7 +217,8 @@ def raise_max(n_o, now, also=()):
     if not now:
         out.append("s_mov_b64 %[flag], vcc")
     cond = [f"s_cbranch_vccz .Lfs_keep{tag}_%=",
-            f"v_max_f32 {t1}, %[m], {t0}", f"v_sub_f32 {t2}, %[m], {t1}", f"v_exp_f32 {t3}, {t2}",
+            f"v_mov_b32 {t1}, {t0}", "s_nop 1", f"v_permlane32_swap_b32 {t0}, {t1}", "s_nop 0",
+            f"v_max3_f32 {t1}, %[m], {t0}, {t1}", f"v_sub_f32 {t2}, %[m], {t1}", f"v_exp_f32 {t3}, {t2}",
             f"v_mov_b32 %[m], {t1}", "s_nop 0", f"v_mul_f32 %[l], %[l], {t3}"]
     if now:
         cond += [f"v_mul_f32 {vr(FS_O + i)}, {vr(FS_O + i)}, {t3}" for i in range(n_o)]
