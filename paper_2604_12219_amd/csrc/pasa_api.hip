@@ -92,6 +92,10 @@ AttnWorkspace carve_attn(const pasa_shape_t* s) {
     // two that divides the group) while that leaves the device short of workgroups, at the price of more unit sums.
     w.unit = group < 32 ? group : 32;
     while (w.unit > 8 && (int64_t)bh * ((nb + w.unit - 1) / w.unit) < 1024) w.unit /= 2;
+    // Below 8 blocks the unit sums are more bytes than the keys and values they come from; that pays only where even
+    // units of 8 leave most compute units without one and the kernel's time is that of one workgroup's serial sweep:
+    // 65 blocks x 4 heads take kv_stats_kernel 20 us with units of 8 and 8.6 us with units of 2.
+    while (w.unit > 1 && (int64_t)bh * ((nb + w.unit - 1) / w.unit) < 128) w.unit /= 2;
     w.n_units = (nb + w.unit - 1) / w.unit;
     w.st = off; off = align_up(off + bh * w.n_chunks * 64 * s->d * 2);
     w.hg = off; off = align_up(off + bh * w.n_groups * s->d * s->d * 2);

@@ -46,7 +46,8 @@ struct StatsParams {
   float scale;
   int32_t n_chunks;  // ceil(nb / 32)
   uint16_t* st;      // out bf16 [BH][n_chunks][64][d] (see AttnParams::st)
-  float* partial;    // scratch fp32 [BH][n_units][d][d]: sum over the unit's blocks of H_j
+  float* partial;    // scratch fp32 [BH][n_units][d][d]: sum over the unit's blocks of H_j; once the statistics are done the
+                     // slot of a group's first unit holds the sum over the whole group
   uint16_t* hg;      // out bf16 [BH][n_groups][d][d] (see AttnParams::hg)
   uint16_t* kbar_split;  // out [BH][nb][d] x 4 bytes: block-mean keys as split bf16 pairs in the score kernel's layout
                          // (per 32 elements 32 x hi then 32 x lo), so that scoring need not read K again

@@ -176,33 +176,50 @@ __global__ void __launch_bounds__(256, 2) kv_stats_kernel(StatsParams p) {
   }
 }
 
-// partial [BH][n_units][d_in][d_out] fp32 -> hg [BH][n_groups][d_out][d_in] bf16 = (scale * Hg)^T
+// partial [BH][n_units][d_in][d_out] fp32 -> hg [BH][n_groups][d_out][d_in] bf16 = (scale * Hg)^T, and the group's fp32 sum
+// into the slot of its first unit (for key_prior_kernel).  Bound by the latency of its loads (a group is 64 KB per unit):
+// a workgroup takes a 16 x 64 piece of the matrix, four consecutive value columns per thread in 16-byte loads of which
+// eight units' are in flight at once, and turns the piece through LDS, so that the stores are whole 32-byte runs.
+// (One thread per eight key columns of a value column, 4-byte loads one unit after the other, took 21 us for two groups of
+// 64 blocks and four heads and 30 us for 30 groups and three heads, against 4.5 and 10.7 us now.)
+constexpr int kFinishIn = 16, kFinishOut = 64;  // key columns, value columns of a workgroup's piece
 template <int D>
 __global__ void __launch_bounds__(256) hg_finish_kernel(StatsParams p) {
-  const int g = blockIdx.x, bh = blockIdx.y;
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) uint16_t piece[kFinishOut][kFinishIn + 8];
+  const int g = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
   const int upg = (p.group >= p.nb) ? p.n_units : p.group / p.unit;  // units per group
-  const int u_lo = g * upg, u_hi = min(u_lo + upg, p.n_units);
+  const int u_lo = g * upg, n_u = min(upg, p.n_units - u_lo);
   const int blocks_in_group = min((g + 1) * p.group, p.nb) - g * p.group;
   const float f = p.scale / (float)blocks_in_group;
-  const float* part = p.partial + (int64_t)bh * p.n_units * D * D;
-  uint16_t* out = p.hg + ((int64_t)bh * p.n_groups + g) * D * D;
-  // 8 consecutive key columns of one value column per thread; the grid's z dimension covers the matrix
-  for (int x = threadIdx.x + 256 * blockIdx.z; x < D * D / 8; x += 256 * gridDim.z) {
-    const int d_out = x % D, d_in0 = (x / D) * 8;
-    bf16x8 v;
+  const int in0 = kFinishIn * (blockIdx.z % (D / kFinishIn)), out0 = kFinishOut * (blockIdx.z / (D / kFinishIn));
+  const int in = tid >> 4, out = (tid & 15) * 4;
+  float* const src = p.partial + ((int64_t)bh * p.n_units + u_lo) * D * D + (in0 + in) * D + out0 + out;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  int u = 0;
+  for (; u + 8 <= n_u; u += 8) {
+    f32x4 x[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float sum = 0.f;
-      for (int u = u_lo; u < u_hi; ++u) sum += part[((int64_t)u * D + d_in0 + i) * D + d_out];
-      v[i] = (__bf16)(sum * f);
-    }
-    *reinterpret_cast<bf16x8*>(out + (int64_t)d_out * D + d_in0) = v;
+    for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + (int64_t)(u + i) * D * D);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += x[i];
+  }
+#pragma unroll 4
+  for (; u < n_u; ++u) sum += *reinterpret_cast<const f32x4*>(src + (int64_t)u * D * D);
+  *reinterpret_cast<f32x4*>(src) = sum;  // read above by this thread alone
+#pragma unroll
+  for (int e = 0; e < 4; ++e) piece[out + e][in] = __builtin_bit_cast(uint16_t, (__bf16)(sum[e] * f));
+  __syncthreads();
+  if (tid < 2 * kFinishOut) {
+    const int row = tid >> 1, c = (tid & 1) * 8;
+    uint16_t* const dst = p.hg + (((int64_t)bh * p.n_groups + g) * D + out0 + row) * D + in0 + c;
+    *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(&piece[row][c]);
   }
 }
 
 // Covariance-aware routing prior (Eq.8): beta_j = log(|| H_j - Hg_{g(j)} ||_F + eps) for every key block.
 // The same sweep as kv_stats_kernel, but H_j is formed per block and compared, element by element in fp32, with the
-// group mean, which the workgroup first sums up from the unit sums that kv_stats_kernel left (`partial`).
+// group mean, from the group's sum that the statistics left in the slot of its first unit (`partial`).
 // Nothing but beta is written.
 template <int D>
 __global__ void __launch_bounds__(256) key_prior_kernel(StatsParams p, float eps, float* beta) {
@@ -215,26 +232,19 @@ __global__ void __launch_bounds__(256) key_prior_kernel(StatsParams p, float eps
   const int j_lo = u * p.unit, j_hi = min(j_lo + p.unit, p.nb);
   const int tin0 = (wave >> 1) * TI, tout0 = (wave & 1) * TI;
 
-  // the group this unit belongs to, and its mean: sum of the group's unit sums / blocks in the group
+  // the group this unit belongs to, and its mean
   const int g = j_lo / p.group;
   const int upg = (p.group >= p.nb) ? p.n_units : p.group / p.unit;  // units per group
-  const int u_lo = g * upg, u_hi = min(u_lo + upg, p.n_units);
   const float inv_blocks = 1.0f / (float)(min((g + 1) * p.group, p.nb) - g * p.group);
+  const float* const group_sum = p.partial + ((int64_t)bh * p.n_units + g * upg) * D * D;
   f32x16 mean[TI][TI];
 #pragma unroll
   for (int a = 0; a < TI; ++a)
 #pragma unroll
-    for (int b = 0; b < TI; ++b) {
-      mean[a][b] = f32x16{0};
-      for (int uu = u_lo; uu < u_hi; ++uu) {
-        const float* part = p.partial + ((int64_t)bh * p.n_units + uu) * D * D;
+    for (int b = 0; b < TI; ++b)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          mean[a][b][r] += part[(32 * (tin0 + a) + mfma_row(r, h)) * D + 32 * (tout0 + b) + (lane & 31)];
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mean[a][b][r] *= inv_blocks;
-    }
+      for (int r = 0; r < 16; ++r)
+        mean[a][b][r] = group_sum[(32 * (tin0 + a) + mfma_row(r, h)) * D + 32 * (tout0 + b) + (lane & 31)] * inv_blocks;
 
   f32x16 acc[TI][TI];
 #pragma unroll
@@ -272,9 +282,7 @@ __global__ void __launch_bounds__(256) key_prior_kernel(StatsParams p, float eps
 }  // namespace
 
 hipError_t pasa_launch_kv_stats(const StatsParams& p, hipStream_t stream) {
-  // few groups (long groups, or one global matrix): spread each matrix over several workgroups
-  const int split = (int64_t)p.n_groups * p.bh < 2048 ? p.d * p.d / 8 / 256 : 1;
-  dim3 g1(p.n_units, p.bh), g2(p.n_groups, p.bh, split);
+  dim3 g1(p.n_units, p.bh), g2(p.n_groups, p.bh, (p.d / kFinishIn) * (p.d / kFinishOut));
   const bool finish = p.unit != p.group;  // otherwise a unit is a whole group and kv_stats_kernel writes the matrices itself
   if (p.d == 128) {
     hipLaunchKernelGGL(kv_stats_kernel<128>, g1, dim3(256), 0, stream, p);

@@ -123,6 +123,30 @@ def test_key_prior_matches_oracle_and_feeds_the_scores(P, grid, d, block, group)
     np.testing.assert_allclose(s.cpu().numpy(), want, atol=1e-3 * np.abs(want).max(), rtol=0)
 
 
+@pytest.mark.parametrize("n,heads,d,block,group", [
+    (64 * 129 - 3, 1, 128, 64, 64),   # units of 1 block: 64 + 64 + 1 units in the three groups
+    (64 * 90, 3, 64, 64, 32),         # units of 2 blocks: 16 + 16 + 13 units
+    (64 * 21 + 1, 1, 128, 64, 1000),  # one group of 22 blocks, units of 1: remainder of 6 after 2 rounds of 8
+    (128 * 5, 2, 64, 128, 4),         # a group of one block behind a whole one
+])
+def test_statistics_of_small_problems(P, n, heads, d, block, group):
+    """few blocks: the units of the statistics shrink and the groups are put together from many of them.  Tolerances as in
+    the tests of the prior and of the attention above and below (fp32 sums in another order move neither)"""
+    q, k, v = _inputs((1, 1, n), heads, d, seed=n)
+    shape = P.Shape.of(q, block=block, group=group)
+    ws = P.kv_stats(k, v, shape, ws=torch.full((P.attn_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda"))
+    beta = P.key_prior(k, v, shape, ws)
+    idx, mask = P.route(P.block_score(q, k, shape), 1, 3, 0.2)
+    out = P.sparse_attn_fwd(q, k, v, shape, idx, mask, ws=ws, prepared=True)
+    torch.cuda.synchronize()
+    want, got = oracle.key_prior(to_f64(k), to_f64(v), block, group, eps=1e-6), beta.cpu().numpy()
+    alone = want < np.log(1e-5)  # a block that is its own group: the norm is rounding noise
+    np.testing.assert_allclose(got[~alone], want[~alone], atol=2e-3, rtol=0)
+    assert np.all(got[alone] < np.log(1e-2))
+    res = oracle.pasa_attention(to_f64(q), to_f64(k), to_f64(v), idx.cpu().numpy(), block, group=group)
+    assert_close(to_f64(out), res, what="attention with the statistics of a small problem")
+
+
 # ------------------------------------------------------------------------------------------------
 # stage 2: routing is bit-exact against the oracle fed the GPU's scores
 # ------------------------------------------------------------------------------------------------
