@@ -104,7 +104,10 @@ PASA_API size_t pasa_score_workspace_bytes(const pasa_shape_t* shape);
 /* host-only.  Bytes of scratch pasa_kv_stats, pasa_sparse_attn_fwd and pasa_attn_dense_ref need (key/value block
  * statistics, group matrices and unit sums, block-mean keys for pasa_block_score_with_stats, room for a selection
  * bitmap: 0.20 GB at 40 heads of 75,600 tokens; with kv_slices > 1 also the per-slice partial results:
- * B*H*kv_slices*n*(d+2)*4 bytes, 12.6 GB at 40 heads of 75,600 tokens with 8 slices); 0 on a bad shape. */
+ * B*H*kv_slices*n*(d+2)*4 bytes, 12.6 GB at 40 heads of 75,600 tokens with 8 slices); 0 on a bad shape.
+ * Shapes of at most 256 query tiles (B*H*ceil(n/128)) get room for partial results as well, at most 35 MB: with it the
+ * attention kernels may share a query tile out among several workgroups.  A workspace without that room is accepted
+ * and then every query tile is one workgroup's (the results differ by floating-point summation order only). */
 PASA_API size_t pasa_attn_workspace_bytes(const pasa_shape_t* shape);
 
 /*

@@ -19,6 +19,8 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr int kMaxChunks = 8192;   // chunks of 32 key blocks per head (262,144 key blocks)
 constexpr int kMaxGroups = 65535;  // first-order groups per head
+// Key split (attn_parts): workgroups wanted, the most parts of a query tile, and the tile steps a part has to have
+constexpr int kSplitWorkgroupsDense = 512, kSplitWorkgroupsSparse = 256, kMaxParts = 8, kMinSteps = 6;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -50,8 +52,9 @@ int check_group(int group, int nb) {
 float effective_scale(const pasa_shape_t* s) { return s->scale > 0.f ? s->scale : 1.0f / sqrtf((float)s->d); }
 
 struct AttnWorkspace {
-  size_t st, hg, partial, kbar, part_o, part_ml, queue, bitmap, total;
+  size_t st, hg, partial, kbar, part_o, part_ml, queue, bitmap, required, total;
   int n_groups, unit, n_units, n_chunks, n_slices;
+  int max_parts;  // key split: there is room for this many parts between `required` and `total`
 };
 
 // Number of key-range slices of the sparse kernel.  K and V of one head should fit the 4 MB L2 of an
@@ -69,6 +72,23 @@ int check_slices(const pasa_shape_t* s) {
   if (s->kv_slices <= 1) return PASA_OK;
   if (s->kv_slices % 8 != 0 || s->kv_slices > (num_blocks(s) + 31) / 32) return PASA_EUNSUPPORTED;
   return PASA_OK;
+}
+
+// Key split of small grids: every query tile is shared out among several workgroups, whose partial results (fp32 numerators,
+// then maxima and normalisers) take this many bytes.
+size_t numerator_bytes(const pasa_shape_t* s, int parts) { return align_up((size_t)s->B * s->H * parts * s->n * s->d * 4); }
+size_t split_bytes(const pasa_shape_t* s, int parts) {
+  return parts > 1 ? numerator_bytes(s, parts) + align_up((size_t)s->B * s->H * parts * s->n * 2 * 4) : 0;
+}
+
+// The largest number of parts a workspace has room for.  A workspace that fits the static scratch array without this room
+// also fits it with it, so that pasa_sparse_attn_fwd_static takes the same shapes.
+int max_parts(const pasa_shape_t* s, size_t required) {
+  const int64_t wgs = (int64_t)s->B * s->H * ((s->n + 127) / 128);
+  int parts = (int)(kSplitWorkgroupsDense / wgs < kMaxParts ? kSplitWorkgroupsDense / wgs : kMaxParts);
+  while (parts > 1 && required <= (size_t)PASA_STATIC_SCRATCH_BYTES && required + split_bytes(s, parts) > (size_t)PASA_STATIC_SCRATCH_BYTES)
+    --parts;
+  return parts > 1 ? parts : 1;
 }
 
 AttnWorkspace carve_attn(const pasa_shape_t* s) {
@@ -102,8 +122,30 @@ AttnWorkspace carve_attn(const pasa_shape_t* s) {
     w.partial = off; off = align_up(off + bh * w.n_units * s->d * s->d * 4);
     w.kbar = off; off = align_up(off + bh * nb * s->d * 4);  // block-mean keys as split bf16 pairs, for pasa_block_score_with_stats
   }
-  w.total = off;
+  w.required = w.total = off;
+  w.max_parts = w.n_slices > 1 ? 1 : max_parts(s, w.required);
+  w.total += split_bytes(s, w.max_parts);
   return w;
+}
+
+// Into how many parts the key list of every query tile is cut (1: not at all).  k_sel = 0: the dense path.  Where query
+// tiles are fewer than compute units the kernel takes as long as one workgroup's serial walk, about a microsecond per tile
+// step; the partial results and their merge cost 2 to 5 us, so a part has to have a few steps of its own.  The dense path
+// gains up to two workgroups per compute unit, the sparse one, whose parts each go through a group's whole matrix, up to one.
+// Attention alone, us, one part / the rule's: dense 1365 tokens, 6 heads, d = 64: 22.4 / 16.7; dense 4140 tokens, 4 heads,
+// d = 128: 81 / 61; dense 9900 tokens, 3 heads: 187 / 177; sparse 4140 tokens, 15 % of the blocks, 1 head: 26 / 21, 4 heads
+// (132 query tiles): 30, cut in three 33.
+int attn_parts(const pasa_shape_t* s, const AttnWorkspace& w, int k_sel, size_t ws_bytes) {
+  const int64_t wgs = (int64_t)s->B * s->H * ((s->n + 127) / 128);
+  int64_t steps = (s->n + 63) / 64, wanted = kSplitWorkgroupsDense / wgs;
+  if (k_sel > 0) {
+    steps = (int64_t)k_sel * (s->block / 64) + (s->group > 0 ? w.n_chunks + (int64_t)w.n_groups * (s->d / 64) : 0);
+    wanted = kSplitWorkgroupsSparse / wgs;
+  }
+  if (wanted > steps / kMinSteps) wanted = steps / kMinSteps;
+  int parts = wanted < w.max_parts ? (int)wanted : w.max_parts;
+  while (parts > 1 && ws_bytes < w.required + split_bytes(s, parts)) --parts;
+  return parts > 1 ? parts : 1;
 }
 
 constexpr int kMaxDevices = 64;
@@ -172,8 +214,7 @@ size_t pasa_attn_workspace_bytes(const pasa_shape_t* shape) {
   if (check_shape(shape) != PASA_OK) return 0;
   if (check_group(shape->group, num_blocks(shape)) != PASA_OK) return 0;
   if (check_slices(shape) != PASA_OK) return 0;
-  const size_t t = carve_attn(shape).total;
-  return t ? t : kAlign;  // never zero for a valid shape, so that 0 always means "bad shape"
+  return carve_attn(shape).total;  // never zero for a valid shape (it holds a bitmap), so that 0 always means "bad shape"
 }
 
 static int block_score_impl(const void* q, const void* k, const pasa_shape_t* shape, const float* key_bias, float* scores,
@@ -253,7 +294,7 @@ static int check_attn_args(const pasa_shape_t* shape, bool sparse, const void* w
   }
   if (!ws) return PASA_EINVAL;
   if (!aligned16(ws)) return PASA_EALIGN;
-  if (ws_bytes < pasa_attn_workspace_bytes(s)) return PASA_EWORKSPACE;
+  if (ws_bytes < carve_attn(s).required) return PASA_EWORKSPACE;
   return PASA_OK;
 }
 
@@ -339,7 +380,11 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     const int rs = pasa_kv_stats(k, v, &s, ws, ws_bytes, stream);
     if (rs != PASA_OK) return rs;
   }
-  const AttnWorkspace w = carve_attn(&s);
+  AttnWorkspace w = carve_attn(&s);
+  if (!sparse) {  // the room for partial results lies behind the statistics that the caller's shape may have left in ws
+    pasa_shape_t full = *shape;
+    if (check_group(full.group, nb) == PASA_OK && check_slices(&full) == PASA_OK) w = carve_attn(&full);
+  }
   char* base = static_cast<char*>(ws);
   AttnParams a{};
   a.q = static_cast<const uint16_t*>(q); a.k = static_cast<const uint16_t*>(k); a.v = static_cast<const uint16_t*>(v);
@@ -365,6 +410,13 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     a.part_o = reinterpret_cast<float*>(base + w.part_o);
     a.part_ml = reinterpret_cast<float*>(base + w.part_ml);
     a.queue = reinterpret_cast<uint32_t*>(base + w.queue);
+  }
+  const int parts = attn_parts(&s, w, sparse ? k_sel : 0, ws_bytes);
+  if (parts > 1) {
+    a.split = 1;
+    a.n_slices = parts;
+    a.part_o = reinterpret_cast<float*>(base + w.required);
+    a.part_ml = reinterpret_cast<float*>(base + w.required + numerator_bytes(&s, parts));
   }
   return pasa_launch_attn(a, sparse, s.d, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
