@@ -370,6 +370,35 @@ def test_key_split_of_small_grids_matches_oracle_and_the_uncut_kernel(P, n, head
             np.testing.assert_allclose(cut_lse.cpu().numpy(), res["lse"], atol=2e-2)
 
 
+def _lists(rng, nb, k_sel, keep_own):
+    """index lists [1, nb, k_sel]: every row selects (keep_own: both, first, none) of the blocks 2 (i // 2), 2 (i // 2) + 1, the
+    ones its workgroup visits first if they are in both rows of the pair, and random others"""
+    idx = np.empty((1, nb, k_sel), np.int32)
+    for i in range(nb):
+        pair = [j for j in (i - i % 2, i - i % 2 + 1) if j < nb]
+        own = {"both": pair, "first": pair[:1], "none": []}[keep_own]
+        rest = rng.permutation([j for j in range(nb) if j not in pair])[:k_sel - len(own)]
+        idx[0, i] = np.sort(np.concatenate([own, rest]).astype(np.int32))
+    return idx
+
+
+@pytest.mark.parametrize("n,d,block,kv_slices", [(1283, 128, 64, 0), (1345, 64, 64, 0), (1408, 128, 128, 0), (1409, 64, 128, 0),
+                                                 (16460, 64, 64, 8)])
+@pytest.mark.parametrize("keep_own", ["both", "first", "none"])
+def test_blocks_visited_first_are_visited_once(P, n, d, block, kv_slices, keep_own):
+    """whole, ragged and missing partners of the last pair, 128-token blocks, walks that start in the middle of the bitmap"""
+    rng = np.random.default_rng(n)
+    q, k, v = _inputs((1, 1, n), 1, d, seed=n)
+    shape = P.Shape.of(q, block=block, group=32, kv_slices=kv_slices)
+    nb = P.num_blocks(shape)
+    idx = _lists(rng, nb, 7, keep_own)
+    out, lse = P.sparse_attn_fwd(q, k, v, shape, torch.from_numpy(idx).cuda(), None, want_lse=True)
+    torch.cuda.synchronize()
+    res = oracle.pasa_attention(to_f64(q), to_f64(k), to_f64(v), idx, block, group=32, return_all=True)
+    assert_close(to_f64(out), res["o"], what=f"{n} d={d} b={block} own={keep_own}")
+    np.testing.assert_allclose(lse.cpu().numpy(), res["lse"], atol=2e-2)
+
+
 def test_keep_everything_equals_dense_kernel_and_oracle(P):
     q, k, v = _inputs((5, 21, 13), 2, 128, seed=2)
     out, _, idx = _run_sparse(P, q, k, v, 64, 32, 1.0)
