@@ -316,7 +316,9 @@ int pasa_check_selection(const int32_t* idx, const uint32_t* mask, int32_t BH, i
                  hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
-int pasa_kv_stats(const void* k, const void* v, const pasa_shape_t* shape, void* ws, size_t ws_bytes, void* stream) {
+// idx not null: the same launch builds the selection bitmap in the workspace from these index lists of k_sel blocks
+static int kv_stats_impl(const void* k, const void* v, const pasa_shape_t* shape, const int32_t* idx, int32_t k_sel, void* ws,
+                         size_t ws_bytes, void* stream) {
   pasa_shape_t s;
   const int rc = check_attn_args(shape, true, ws, ws_bytes, &s);
   if (rc != PASA_OK) return rc;
@@ -337,7 +339,13 @@ int pasa_kv_stats(const void* k, const void* v, const pasa_shape_t* shape, void*
   t.hg = reinterpret_cast<uint16_t*>(base + w.hg);
   t.partial = reinterpret_cast<float*>(base + w.partial);
   t.kbar_split = reinterpret_cast<uint16_t*>(base + w.kbar);
+  t.idx = idx; t.k_sel = k_sel; t.mask_words = (nb + 31) / 32;
+  t.mask = reinterpret_cast<uint32_t*>(base + w.bitmap);
   return pasa_launch_kv_stats(t, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
+}
+
+int pasa_kv_stats(const void* k, const void* v, const pasa_shape_t* shape, void* ws, size_t ws_bytes, void* stream) {
+  return kv_stats_impl(k, v, shape, nullptr, 0, ws, ws_bytes, stream);
 }
 
 int pasa_key_prior(const void* k, const void* v, const pasa_shape_t* shape, float eps, float* beta, void* ws,
@@ -376,8 +384,9 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     if ((!idx && !mask) || k_sel < 1 || k_sel > nb) return PASA_EINVAL;
     if ((idx && !aligned4(idx)) || (mask && !aligned4(mask))) return PASA_EALIGN;
   }
+  const bool mask_with_stats = sparse && with_stats && !mask && s.group > 0;  // (without the approximation there is no statistics launch)
   if (sparse && with_stats) {
-    const int rs = pasa_kv_stats(k, v, &s, ws, ws_bytes, stream);
+    const int rs = kv_stats_impl(k, v, &s, mask_with_stats ? idx : nullptr, k_sel, ws, ws_bytes, stream);
     if (rs != PASA_OK) return rs;
   }
   AttnWorkspace w = carve_attn(&s);
@@ -396,7 +405,8 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
   if (sparse) {
     if (!mask) {  // the caller has index lists only: the bitmap the kernel walks is built from them
       uint32_t* built = reinterpret_cast<uint32_t*>(base + w.bitmap);
-      if (pasa_launch_mask_from_idx(idx, (int64_t)s.B * s.H * nb, nb, k_sel, built, static_cast<hipStream_t>(stream)) != hipSuccess)
+      if (!mask_with_stats &&
+          pasa_launch_mask_from_idx(idx, (int64_t)s.B * s.H * nb, nb, k_sel, built, static_cast<hipStream_t>(stream)) != hipSuccess)
         return PASA_EHIP;
       mask = built;
     }

@@ -110,3 +110,16 @@ PASA_DEVICE f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 
 // M index (row of the 32x32 result) held in register `reg` (0..15) of a lane in half-wave h
 PASA_DEVICE int mfma_row(int reg, int h) { return 8 * (reg >> 2) + 4 * h + (reg & 3); }
+
+// One row of the selection bitmap from its ascending index list, by one wavefront: clears the row's words, then sets its
+// bits (integer atomic OR inside the row: the result does not depend on the order)
+PASA_DEVICE void mask_row_from_idx(const int32_t* irow, int nb, int k_sel, int mask_words, uint32_t* mrow, int lane) {
+  for (int wd = lane; wd < mask_words; wd += 64) mrow[wd] = 0u;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  for (int e = lane; e < k_sel; e += 64) {
+    const int32_t j = irow[e];
+    if (j >= 0 && j < nb) atomicOr(mrow + (j >> 5), 1u << (j & 31));  // out-of-range entries are a caller error; never written
+  }
+}

@@ -52,6 +52,10 @@ struct StatsParams {
   uint16_t* hg;      // out bf16 [BH][n_groups][d][d] (see AttnParams::hg)
   uint16_t* kbar_split;  // out [BH][nb][d] x 4 bytes: block-mean keys as split bf16 pairs in the score kernel's layout
                          // (per 32 elements 32 x hi then 32 x lo), so that scoring need not read K again
+  // selection bitmap of the attention kernel, built in the same launch from a caller's index lists (idx null: not wanted)
+  const int32_t* idx;    // [BH][nb][k_sel]
+  int32_t k_sel, mask_words;
+  uint32_t* mask;        // out [BH][nb][mask_words]
 };
 hipError_t pasa_launch_kv_stats(const StatsParams& p, hipStream_t stream);
 // beta [BH][nb] fp32 = log(||H_j - Hg_{g(j)}||_F + eps); needs p.partial as pasa_launch_kv_stats left it

@@ -11,6 +11,7 @@
 //      ballot + prefix popcount, so the output order needs no sort.
 // Integer work throughout except the single fused multiply-add, hence bit-reproducible on a CPU.
 // (The Gumbel variant of the bias takes two logarithms and is reproducible only up to their rounding.)
+#include "pasa_device.hpp"
 #include "pasa_kernels.hpp"
 
 namespace {
@@ -169,23 +170,11 @@ __global__ void __launch_bounds__(256) check_selection_kernel(const int32_t* idx
 
 __global__ void zero_i32_kernel(int32_t* x) { *x = 0; }
 
-// bitmap rows from ascending index lists: one wavefront per row clears the row's words, then sets its bits
-// (integer atomic OR inside the row: the result does not depend on the order)
+// bitmap rows from ascending index lists, one wavefront per row
 __global__ void __launch_bounds__(256) mask_from_idx_kernel(const int32_t* idx, int64_t rows, int nb, int k_sel, int mask_words,
                                                             uint32_t* mask) {
-  const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  uint32_t* mrow = mask + row * mask_words;
-  for (int wd = lane; wd < mask_words; wd += 64) mrow[wd] = 0u;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const int32_t* irow = idx + row * k_sel;
-  for (int e = lane; e < k_sel; e += 64) {
-    const int32_t j = irow[e];
-    if (j >= 0 && j < nb) atomicOr(mrow + (j >> 5), 1u << (j & 31));  // out-of-range entries are a caller error; never written
-  }
+  if (row < rows) mask_row_from_idx(idx + row * k_sel, nb, k_sel, mask_words, mask + row * mask_words, threadIdx.x & 63);
 }
 
 template <int KPL>

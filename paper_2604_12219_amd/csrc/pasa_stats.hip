@@ -94,6 +94,14 @@ __global__ void __launch_bounds__(256, 2) kv_stats_kernel(StatsParams p) {
   __shared__ __attribute__((aligned(16))) char smem[2 * TILE_BYTES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
   const int u = blockIdx.x, bh = blockIdx.y;
+  // Workgroups beyond the units: four rows each of the selection bitmap, which only the attention kernel reads (a launch of
+  // its own between two that wait for each other costs 3 us: 43.6 / 41.0 us a call at 4140 tokens, four heads).
+  if (u >= p.n_units) {
+    const int row = 4 * (u - p.n_units) + wave;
+    const int64_t flat = (int64_t)bh * p.nb + row;
+    if (row < p.nb) mask_row_from_idx(p.idx + flat * p.k_sel, p.nb, p.k_sel, p.mask_words, p.mask + flat * p.mask_words, lane);
+    return;  // the whole workgroup, before any barrier
+  }
   const int j_lo = u * p.unit, j_hi = min(j_lo + p.unit, p.nb);
   const int tin0 = (wave >> 1) * TI, tout0 = (wave & 1) * TI;
 
@@ -282,7 +290,7 @@ __global__ void __launch_bounds__(256) key_prior_kernel(StatsParams p, float eps
 }  // namespace
 
 hipError_t pasa_launch_kv_stats(const StatsParams& p, hipStream_t stream) {
-  dim3 g1(p.n_units, p.bh), g2(p.n_groups, p.bh, (p.d / kFinishIn) * (p.d / kFinishOut));
+  dim3 g1(p.n_units + (p.idx ? (p.nb + 3) / 4 : 0), p.bh), g2(p.n_groups, p.bh, (p.d / kFinishIn) * (p.d / kFinishOut));
   const bool finish = p.unit != p.group;  // otherwise a unit is a whole group and kv_stats_kernel writes the matrices itself
   if (p.d == 128) {
     hipLaunchKernelGGL(kv_stats_kernel<128>, g1, dim3(256), 0, stream, p);

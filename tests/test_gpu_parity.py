@@ -399,6 +399,21 @@ def test_blocks_visited_first_are_visited_once(P, n, d, block, kv_slices, keep_o
     np.testing.assert_allclose(lse.cpu().numpy(), res["lse"], atol=2e-2)
 
 
+@pytest.mark.parametrize("n,heads,batch,d,block,group", [(63, 1, 1, 64, 64, 32), (1345, 3, 1, 128, 64, 32), (1345, 2, 2, 64, 64, 1),
+                                                         (2113, 2, 1, 64, 128, 64), (1345, 2, 1, 128, 64, 0)])
+def test_bitmap_built_with_the_statistics_equals_the_callers(P, n, heads, batch, d, block, group):
+    """index lists alone (the bitmap is built in the statistics launch, without the approximation in one of its own) against the
+    routing's own bitmap: the same bits, whatever the workspace held"""
+    q, k, v = _inputs((1, 1, n), heads, d, seed=n, batch=batch)
+    shape = P.Shape.of(q, block=block, group=group)
+    idx, mask = P.route(P.block_score(q, k, shape), P.topk_count(P.num_blocks(shape), 0.2), 3, 0.2)
+    ws = torch.full((P.attn_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    lists, lists_lse = P.sparse_attn_fwd(q, k, v, shape, idx, None, ws=ws, want_lse=True)
+    both, both_lse = P.sparse_attn_fwd(q, k, v, shape, idx, mask, want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(lists, both) and torch.equal(lists_lse, both_lse)
+
+
 def test_keep_everything_equals_dense_kernel_and_oracle(P):
     q, k, v = _inputs((5, 21, 13), 2, 128, seed=2)
     out, _, idx = _run_sparse(P, q, k, v, 64, 32, 1.0)
