@@ -91,6 +91,34 @@ int max_parts(const pasa_shape_t* s, size_t required) {
   return parts > 1 ? parts : 1;
 }
 
+// Blocks summed by one workgroup of the statistics kernel: a whole group, at most 32 blocks, or half of that, a quarter, ...
+// (a power of two that divides the group).  512 workgroups run at a time, so the sweep takes as many rounds as there are 512
+// units, each as long as a unit and the writing and averaging of its sum, which is worth about 6 blocks.
+// kv_stats_kernel + hg_finish_kernel, us, units of 32 / 16 / 8 / 4: 12 heads of 512 blocks - / 60 / 67 / 83; 5 of 1182 - / 56 / 63 / 79;
+// 3 of 1857 in groups of 64 - / 53 / 60 / 74.
+// Below 8 blocks the unit sums are more bytes than the keys and values they come from; that pays only where even units of 8
+// leave most compute units without one and the kernel's time is that of one workgroup's serial sweep: 65 blocks x 4 heads
+// take kv_stats_kernel 20 us with units of 8 and 8.6 us with units of 2.
+int stats_unit(int64_t bh, int nb, int group) {
+  auto units = [&](int unit) { return bh * ((nb + unit - 1) / unit); };
+  auto cost = [&](int unit) { return (units(unit) + 511) / 512 * (unit + 6); };
+  int best = group < 32 ? group : 32;
+  for (int unit = best / 2; unit >= 8 && units(2 * unit) < 1024; unit /= 2)  // (with 1024 units the sums are many already)
+    if (cost(unit) < cost(best)) best = unit;
+  while (best > 1 && units(best) < 128) best /= 2;
+  return best;
+}
+
+// The same for the prior's kernel, which has no sums to write but fetches its group's matrix once per workgroup (as many bytes
+// as two blocks): half a unit pays while that leaves fewer than 1024 workgroups.  us, units of 16 / 8 / 4: 12 heads of 512 blocks
+// 100 / 82 / 91, 5 of 1182 100 / 81 / 89, 3 of 1857 100 / 80 / 84.
+int prior_unit(int64_t bh, int nb, int group) {
+  int unit = group < 32 ? group : 32;
+  while (unit > 8 && bh * ((nb + unit - 1) / unit) < 1024) unit /= 2;
+  while (unit > 1 && bh * ((nb + unit - 1) / unit) < 128) unit /= 2;
+  return unit;
+}
+
 AttnWorkspace carve_attn(const pasa_shape_t* s) {
   AttnWorkspace w{};
   const int nb = num_blocks(s);
@@ -108,14 +136,7 @@ AttnWorkspace carve_attn(const pasa_shape_t* s) {
   if (s->group > 0) {
     const int group = s->group >= nb ? nb : s->group;
     w.n_groups = (nb + group - 1) / group;
-    // Blocks summed by one workgroup of the statistics kernel: a whole group, at most 32 blocks -- fewer (a power of
-    // two that divides the group) while that leaves the device short of workgroups, at the price of more unit sums.
-    w.unit = group < 32 ? group : 32;
-    while (w.unit > 8 && (int64_t)bh * ((nb + w.unit - 1) / w.unit) < 1024) w.unit /= 2;
-    // Below 8 blocks the unit sums are more bytes than the keys and values they come from; that pays only where even
-    // units of 8 leave most compute units without one and the kernel's time is that of one workgroup's serial sweep:
-    // 65 blocks x 4 heads take kv_stats_kernel 20 us with units of 8 and 8.6 us with units of 2.
-    while (w.unit > 1 && (int64_t)bh * ((nb + w.unit - 1) / w.unit) < 128) w.unit /= 2;
+    w.unit = stats_unit((int64_t)bh, nb, group);
     w.n_units = (nb + w.unit - 1) / w.unit;
     w.st = off; off = align_up(off + bh * w.n_chunks * 64 * s->d * 2);
     w.hg = off; off = align_up(off + bh * w.n_groups * s->d * s->d * 2);
@@ -364,6 +385,7 @@ int pasa_key_prior(const void* k, const void* v, const pasa_shape_t* shape, floa
   t.stride_b = s.stride_b; t.stride_h = s.stride_h; t.stride_n = s.stride_n;
   t.bh = s.B * s.H; t.H = s.H; t.n = s.n; t.nb = nb; t.block = s.block; t.tail = s.n - (nb - 1) * s.block; t.d = s.d;
   t.group = s.group >= nb ? nb : s.group; t.n_groups = w.n_groups; t.unit = w.unit; t.n_units = w.n_units;
+  t.prior_unit = prior_unit(t.bh, nb, t.group);
   t.scale = effective_scale(&s);
   t.n_chunks = w.n_chunks;
   t.partial = reinterpret_cast<float*>(base + w.partial);

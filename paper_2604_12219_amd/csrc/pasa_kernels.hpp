@@ -44,6 +44,7 @@ struct StatsParams {
   int32_t n_groups;  // ceil(nb / group)
   int32_t unit;      // blocks summed by one workgroup: a power of two that divides the group, at most 32
   int32_t n_units;   // units per head
+  int32_t prior_unit;  // the prior's kernel: blocks that one of its workgroups looks at (as `unit`, of its own)
   float scale;
   int32_t n_chunks;  // ceil(nb / 32)
   uint16_t* st;      // out bf16 [BH][n_chunks][64][d] (see AttnParams::st)

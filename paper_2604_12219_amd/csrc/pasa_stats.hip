@@ -237,12 +237,12 @@ __global__ void __launch_bounds__(256) key_prior_kernel(StatsParams p, float eps
   __shared__ float red_s[2][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5;
   const int u = blockIdx.x, bh = blockIdx.y;
-  const int j_lo = u * p.unit, j_hi = min(j_lo + p.unit, p.nb);
+  const int j_lo = u * p.prior_unit, j_hi = min(j_lo + p.prior_unit, p.nb);
   const int tin0 = (wave >> 1) * TI, tout0 = (wave & 1) * TI;
 
-  // the group this unit belongs to, and its mean
+  // the group these blocks belong to, and its mean
   const int g = j_lo / p.group;
-  const int upg = (p.group >= p.nb) ? p.n_units : p.group / p.unit;  // units per group
+  const int upg = (p.group >= p.nb) ? p.n_units : p.group / p.unit;  // unit sums per group
   const float inv_blocks = 1.0f / (float)(min((g + 1) * p.group, p.nb) - g * p.group);
   const float* const group_sum = p.partial + ((int64_t)bh * p.n_units + g * upg) * D * D;
   f32x16 mean[TI][TI];
@@ -303,7 +303,7 @@ hipError_t pasa_launch_kv_stats(const StatsParams& p, hipStream_t stream) {
 }
 
 hipError_t pasa_launch_key_prior(const StatsParams& p, float eps, float* beta, hipStream_t stream) {
-  dim3 g1(p.n_units, p.bh);
+  dim3 g1((p.nb + p.prior_unit - 1) / p.prior_unit, p.bh);
   if (p.d == 128) hipLaunchKernelGGL(key_prior_kernel<128>, g1, dim3(256), 0, stream, p, eps, beta);
   else hipLaunchKernelGGL(key_prior_kernel<64>, g1, dim3(256), 0, stream, p, eps, beta);
   return hipGetLastError();
