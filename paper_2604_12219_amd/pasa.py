@@ -128,7 +128,7 @@ def load_library() -> ctypes.CDLL:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check_extent(shape: "Shape", **tensors):
@@ -141,13 +141,16 @@ def _check_extent(shape: "Shape", **tensors):
             continue
         if t.dtype != torch.bfloat16:
             raise ValueError(f"{name}: expected bf16, got {t.dtype}")
+        if t.is_contiguous() and last < t.numel():  # inside the tensor itself; otherwise the storage decides
+            continue
         room = t.untyped_storage().nbytes() // t.element_size() - t.storage_offset()
         if last >= room:
             raise ValueError(f"{name}: the shape's strides reach element {last} of a storage that holds {room} from the tensor's start")
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """the current stream of the current device as an integer (the handle alone, without a torch.cuda.Stream around it)"""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check(rc: int, where: str):
@@ -163,7 +166,11 @@ def topk_count(n_blocks: int, keep_ratio: float) -> int:
 
 
 def num_blocks(shape: Shape) -> int:
-    nb = load_library().pasa_num_blocks(ctypes.byref(shape.c()))
+    return _num_blocks(ctypes.byref(shape.c()))
+
+
+def _num_blocks(c) -> int:
+    nb = load_library().pasa_num_blocks(c)
     if nb < 0:
         raise PasaError(nb, "pasa_num_blocks")
     return nb
@@ -181,9 +188,10 @@ def attn_workspace_bytes(shape: Shape) -> int:
     return load_library().pasa_attn_workspace_bytes(ctypes.byref(shape.c()))
 
 
-def _workspace(nbytes: int, device, ws):
+def _workspace(nbytes, device, ws):
+    """ws, or a new workspace of nbytes() bytes"""
     if ws is None:
-        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        ws = torch.empty(max(nbytes(), 256), dtype=torch.uint8, device=device)
     return ws
 
 
@@ -191,16 +199,17 @@ def block_score(q, k, shape: Shape, key_bias=None, scores=None, ws=None, stats_w
     """-> scores fp32 [B*H, N_B, N_B].  With stats_ws (the workspace kv_stats() filled for the same k and shape) the
     block-mean keys are taken from there and K is not read (k may be None)."""
     L = load_library()
-    nb = num_blocks(shape)
+    c = ctypes.byref(shape.c())
+    nb = _num_blocks(c)
     if scores is None:
         scores = torch.empty((shape.B * shape.H, nb, nb), dtype=torch.float32, device=q.device)
-    ws = _workspace(score_workspace_bytes(shape), q.device, ws)
+    ws = _workspace(lambda: score_workspace_bytes(shape), q.device, ws)
     _check_extent(shape, q=q, k=k)
     if stats_ws is not None:
-        _check(L.pasa_block_score_with_stats(_ptr(q), ctypes.byref(shape.c()), _ptr(key_bias), _ptr(scores), _ptr(ws), ws.numel(),
+        _check(L.pasa_block_score_with_stats(_ptr(q), c, _ptr(key_bias), _ptr(scores), _ptr(ws), ws.numel(),
                                              _ptr(stats_ws), stats_ws.numel(), _stream()), "pasa_block_score_with_stats")
         return scores
-    _check(L.pasa_block_score(_ptr(q), _ptr(k), ctypes.byref(shape.c()), _ptr(key_bias), _ptr(scores), _ptr(ws),
+    _check(L.pasa_block_score(_ptr(q), _ptr(k), c, _ptr(key_bias), _ptr(scores), _ptr(ws),
                               ws.numel(), _stream()), "pasa_block_score")
     return scores
 
@@ -235,7 +244,7 @@ def check_selection(idx, mask, n_blocks: int, k_sel: int, n_bad=None):
 def kv_stats(k, v, shape: Shape, ws=None):
     """fills (and returns) the attention workspace with the key/value block statistics"""
     L = load_library()
-    ws = _workspace(attn_workspace_bytes(shape), k.device, ws)
+    ws = _workspace(lambda: attn_workspace_bytes(shape), k.device, ws)
     _check_extent(shape, k=k, v=v)
     _check(L.pasa_kv_stats(_ptr(k), _ptr(v), ctypes.byref(shape.c()), _ptr(ws), ws.numel(), _stream()), "pasa_kv_stats")
     return ws
@@ -261,7 +270,7 @@ def l1_distance(a, b, out=None, ws=None):
         raise ValueError("l1_distance supports bf16 and fp32")
     if out is None:
         out = torch.empty(1, dtype=torch.float32, device=a.device)
-    ws = _workspace(int(L.pasa_l1_workspace_bytes()), a.device, ws)
+    ws = _workspace(lambda: int(L.pasa_l1_workspace_bytes()), a.device, ws)
     _check(L.pasa_l1_distance(_ptr(a), _ptr(b), a.numel(), dtype, _ptr(out), _ptr(ws), ws.numel(), _stream()),
            "pasa_l1_distance")
     return out
@@ -291,7 +300,7 @@ def sparse_attn_fwd(q, k, v, shape: Shape, idx, mask, out=None, lse=None, ws=Non
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty((shape.B * shape.H, shape.n), dtype=torch.float32, device=q.device)
-    ws = _workspace(attn_workspace_bytes(shape), q.device, ws)
+    ws = _workspace(lambda: attn_workspace_bytes(shape), q.device, ws)
     _check_extent(shape, q=q, k=k, v=v, out=out)
     fn = L.pasa_sparse_attn_fwd_prepared if prepared else L.pasa_sparse_attn_fwd
     k_sel = idx.shape[-1] if idx is not None else int(k_sel)
@@ -318,7 +327,7 @@ def attn_dense_ref(q, k, v, shape: Shape, out=None, lse=None, ws=None, want_lse:
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty((shape.B * shape.H, shape.n), dtype=torch.float32, device=q.device)
-    ws = _workspace(attn_workspace_bytes(shape), q.device, ws)
+    ws = _workspace(lambda: attn_workspace_bytes(shape), q.device, ws)
     _check_extent(shape, q=q, k=k, v=v, out=out)
     _check(L.pasa_attn_dense_ref(_ptr(q), _ptr(k), _ptr(v), ctypes.byref(shape.c()), _ptr(out), _ptr(lse), _ptr(ws),
                                  ws.numel(), _stream()), "pasa_attn_dense_ref")
@@ -332,7 +341,9 @@ def forward(q, k, v, keep_ratio: float, seed: int, noise_amp: float, block: int 
     ``buffers`` (optional dict) caches every intermediate and workspace between calls.
     """
     shape = Shape.of(q, block=block, group=group, scale=scale)
-    nb = num_blocks(shape)
+    L = load_library()
+    c = ctypes.byref(shape.c())
+    nb = _num_blocks(c)
     k_sel = topk_count(nb, keep_ratio)
     b = buffers if buffers is not None else {}
     key = (tuple(q.shape), block, group, k_sel)
@@ -345,9 +356,14 @@ def forward(q, k, v, keep_ratio: float, seed: int, noise_amp: float, block: int 
         b["ws_score"] = torch.empty(score_workspace_bytes(shape), dtype=torch.uint8, device=q.device)
         b["ws_attn"] = torch.empty(attn_workspace_bytes(shape), dtype=torch.uint8, device=q.device)
         b["out"] = torch.empty_like(q)
-    block_score(q, k, shape, scores=b["scores"], ws=b["ws_score"])
-    route(b["scores"], k_sel, seed, noise_amp, idx=b["idx"], mask=b["mask"])
-    sparse_attn_fwd(q, k, v, shape, b["idx"], b["mask"], out=b["out"], ws=b["ws_attn"])
+    # block_score, route and sparse_attn_fwd with the marshalling of the three done once: at 1024 tokens the six launches take
+    # the device 27 us, and a call was bound by 40 us of host work (23 now)
+    _check_extent(shape, q=q, k=k, v=v, out=b["out"])
+    stream, qp, kp, scores, idx, mask = _stream(), _ptr(q), _ptr(k), _ptr(b["scores"]), _ptr(b["idx"]), _ptr(b["mask"])
+    _check(L.pasa_block_score(qp, kp, c, None, scores, _ptr(b["ws_score"]), b["ws_score"].numel(), stream), "pasa_block_score")
+    _check(L.pasa_route(scores, shape.B * shape.H, nb, k_sel, seed & (2**64 - 1), noise_amp, idx, mask, stream), "pasa_route")
+    _check(L.pasa_sparse_attn_fwd(qp, kp, _ptr(v), c, idx, mask, k_sel, _ptr(b["out"]), None, _ptr(b["ws_attn"]),
+                                  b["ws_attn"].numel(), stream), "pasa_sparse_attn_fwd")
     return b["out"], b["idx"]
 
 
@@ -355,16 +371,17 @@ def forward_single_call(q, k, v, shape: Shape, keep_ratio: float, seed: int, noi
                         want_lse: bool = False):
     """pasa_forward: the whole path in one library call, every intermediate inside one workspace"""
     L = load_library()
-    nbytes = int(L.pasa_forward_workspace_bytes(ctypes.byref(shape.c()), float(keep_ratio)))
+    c = ctypes.byref(shape.c())
+    nbytes = int(L.pasa_forward_workspace_bytes(c, float(keep_ratio)))
     if nbytes == 0:
         raise PasaError(-1, "pasa_forward_workspace_bytes")
-    ws = _workspace(nbytes, q.device, ws)
+    ws = _workspace(lambda: nbytes, q.device, ws)
     if out is None:
         out = torch.empty_like(q)
     if lse is None and want_lse:
         lse = torch.empty((shape.B * shape.H, shape.n), dtype=torch.float32, device=q.device)
     _check_extent(shape, q=q, k=k, v=v, out=out)
-    _check(L.pasa_forward(_ptr(q), _ptr(k), _ptr(v), ctypes.byref(shape.c()), float(keep_ratio), seed & (2**64 - 1), noise_amp,
+    _check(L.pasa_forward(_ptr(q), _ptr(k), _ptr(v), c, float(keep_ratio), seed & (2**64 - 1), noise_amp,
                           _ptr(out), _ptr(lse), _ptr(ws), ws.numel(), _stream()), "pasa_forward")
     return (out, lse) if want_lse else out
 
