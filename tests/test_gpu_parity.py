@@ -147,6 +147,28 @@ def test_statistics_of_small_problems(P, n, heads, d, block, group):
     assert_close(to_f64(out), res, what="attention with the statistics of a small problem")
 
 
+@pytest.mark.parametrize("n,heads,d,block,group", [(64 * 110 - 39, 40, 64, 64, 32),     # units of 16, the prior's of 8
+                                                   (64 * 110, 40, 128, 64, 64),         # the same, four units to a group
+                                                   (128 * 52 + 5, 20, 64, 128, 1000),   # one group of 53 blocks
+                                                   (64 * 110, 40, 64, 64, 16)])         # a unit is a group, the prior's half of one
+def test_statistics_in_larger_units_than_the_prior_takes(P, n, heads, d, block, group):
+    """more units of 8 than run at a time: the statistics take larger ones, the prior's kernel its own.  First and last head against
+    the oracle, tolerances as above"""
+    gen = torch.Generator(device="cuda").manual_seed(n)  # (a smooth field along one axis of this length is slow to make)
+    q, k, v = (torch.randn((1, heads, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    shape = P.Shape.of(q, block=block, group=group)
+    ws = P.kv_stats(k, v, shape, ws=torch.full((P.attn_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda"))
+    beta = P.key_prior(k, v, shape, ws)
+    idx, mask = P.route(P.block_score(q, k, shape), 1, 3, 0.2)
+    out = P.sparse_attn_fwd(q, k, v, shape, idx, mask, ws=ws, prepared=True)
+    torch.cuda.synchronize()
+    for h in (0, heads - 1):
+        qh, kh, vh = (to_f64(t[:, h:h + 1]) for t in (q, k, v))
+        np.testing.assert_allclose(beta[h:h + 1].cpu().numpy(), oracle.key_prior(kh, vh, block, group, eps=1e-6), atol=2e-3, rtol=0)
+        res = oracle.pasa_attention(qh, kh, vh, idx[h:h + 1].cpu().numpy(), block, group=group)
+        assert_close(to_f64(out[:, h:h + 1]), res, what=f"head {h}")
+
+
 # ------------------------------------------------------------------------------------------------
 # stage 2: routing is bit-exact against the oracle fed the GPU's scores
 # ------------------------------------------------------------------------------------------------
