@@ -105,8 +105,8 @@ PASA_API size_t pasa_score_workspace_bytes(const pasa_shape_t* shape);
  * statistics, group matrices and unit sums, block-mean keys for pasa_block_score_with_stats, room for a selection
  * bitmap: 0.20 GB at 40 heads of 75,600 tokens; with kv_slices > 1 also the per-slice partial results:
  * B*H*kv_slices*n*(d+2)*4 bytes, 12.6 GB at 40 heads of 75,600 tokens with 8 slices); 0 on a bad shape.
- * Shapes of at most 256 query tiles (B*H*ceil(n/128)) get room for partial results as well, at most 35 MB: with it the
- * attention kernels may share a query tile out among several workgroups.  A workspace without that room is accepted
+ * Shapes of at most 128 query tiles (B*H*ceil(n/128)) get room for partial results as well, at most 18 MB: with it
+ * the sparse kernel may share a query tile out among several workgroups.  A workspace without that room is accepted
  * and then every query tile is one workgroup's (the results differ by floating-point summation order only). */
 PASA_API size_t pasa_attn_workspace_bytes(const pasa_shape_t* shape);
 
@@ -263,7 +263,8 @@ PASA_API int pasa_sparse_attn_fwd_static(const void* q, const void* k, const voi
 
 /*
  * Dense attention, Eq.1: O = softmax(Q K^T * scale) V, same kernels with every block selected.
- *   out bf16 [B,H,n,d]; lse fp32 [BH, n] or NULL; ws as for pasa_sparse_attn_fwd.
+ *   out bf16 [B,H,n,d]; lse fp32 [BH, n] or NULL; ws as for pasa_sparse_attn_fwd (group ignored).  The workspace is
+ *   neither read nor written: calls that overlap, and statistics left in it, may share it.
  */
 PASA_API int pasa_attn_dense_ref(const void* q, const void* k, const void* v, const pasa_shape_t* shape,
                         void* out, float* lse, void* ws, size_t ws_bytes, void* stream);

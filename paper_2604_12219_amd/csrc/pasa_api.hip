@@ -20,7 +20,7 @@ constexpr size_t kAlign = 256;
 constexpr int kMaxChunks = 8192;   // chunks of 32 key blocks per head (262,144 key blocks)
 constexpr int kMaxGroups = 65535;  // first-order groups per head
 // Key split (attn_parts): workgroups wanted, the most parts of a query tile, and the tile steps a part has to have
-constexpr int kSplitWorkgroupsDense = 512, kSplitWorkgroupsSparse = 256, kMaxParts = 8, kMinSteps = 6;
+constexpr int kSplitWorkgroups = 256, kMaxParts = 8, kMinSteps = 6;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -74,7 +74,7 @@ int check_slices(const pasa_shape_t* s) {
   return PASA_OK;
 }
 
-// Key split of small grids: every query tile is shared out among several workgroups, whose partial results (fp32 numerators,
+// Key split of small grids, sparse path: every query tile is shared out among several workgroups, whose partial results (fp32 numerators,
 // then maxima and normalisers) take this many bytes.
 size_t numerator_bytes(const pasa_shape_t* s, int parts) { return align_up((size_t)s->B * s->H * parts * s->n * s->d * 4); }
 size_t split_bytes(const pasa_shape_t* s, int parts) {
@@ -85,7 +85,7 @@ size_t split_bytes(const pasa_shape_t* s, int parts) {
 // also fits it with it, so that pasa_sparse_attn_fwd_static takes the same shapes.
 int max_parts(const pasa_shape_t* s, size_t required) {
   const int64_t wgs = (int64_t)s->B * s->H * ((s->n + 127) / 128);
-  int parts = (int)(kSplitWorkgroupsDense / wgs < kMaxParts ? kSplitWorkgroupsDense / wgs : kMaxParts);
+  int parts = (int)(kSplitWorkgroups / wgs < kMaxParts ? kSplitWorkgroups / wgs : kMaxParts);
   while (parts > 1 && required <= (size_t)PASA_STATIC_SCRATCH_BYTES && required + split_bytes(s, parts) > (size_t)PASA_STATIC_SCRATCH_BYTES)
     --parts;
   return parts > 1 ? parts : 1;
@@ -149,24 +149,32 @@ AttnWorkspace carve_attn(const pasa_shape_t* s) {
   return w;
 }
 
-// Into how many parts the key list of every query tile is cut (1: not at all).  k_sel = 0: the dense path.  Where query
-// tiles are fewer than compute units the kernel takes as long as one workgroup's serial walk, about a microsecond per tile
-// step; the partial results and their merge cost 2 to 5 us, so a part has to have a few steps of its own.  The dense path
-// gains up to two workgroups per compute unit, the sparse one, whose parts each go through a group's whole matrix, up to one.
-// Attention alone, us, one part / the rule's: dense 1365 tokens, 6 heads, d = 64: 22.4 / 16.7; dense 4140 tokens, 4 heads,
-// d = 128: 81 / 61; dense 9900 tokens, 3 heads: 187 / 177; sparse 4140 tokens, 15 % of the blocks, 1 head: 26 / 21, 4 heads
-// (132 query tiles): 30, cut in three 33.
+// Into how many parts the sparse path cuts the key list of every query tile (1: not at all).  Where query tiles are fewer
+// than compute units the kernel takes as long as one workgroup's serial walk, about a microsecond per tile step; the
+// partial results and their merge cost 2 to 5 us, so a part has to have a few steps of its own, and as the parts each go through
+// a group's whole matrix, more than one workgroup per compute unit does not pay.
+// Attention alone, us, one part / the rule's: 4140 tokens, 15 % of the blocks, 1 head: 26 / 21, 4 heads (132 query tiles):
+// 30, cut in three 33.
 int attn_parts(const pasa_shape_t* s, const AttnWorkspace& w, int k_sel, size_t ws_bytes) {
   const int64_t wgs = (int64_t)s->B * s->H * ((s->n + 127) / 128);
-  int64_t steps = (s->n + 63) / 64, wanted = kSplitWorkgroupsDense / wgs;
-  if (k_sel > 0) {
-    steps = (int64_t)k_sel * (s->block / 64) + (s->group > 0 ? w.n_chunks + (int64_t)w.n_groups * (s->d / 64) : 0);
-    wanted = kSplitWorkgroupsSparse / wgs;
-  }
+  const int64_t steps = (int64_t)k_sel * (s->block / 64) + (s->group > 0 ? w.n_chunks + (int64_t)w.n_groups * (s->d / 64) : 0);
+  int64_t wanted = kSplitWorkgroups / wgs;
   if (wanted > steps / kMinSteps) wanted = steps / kMinSteps;
   int parts = wanted < w.max_parts ? (int)wanted : w.max_parts;
   while (parts > 1 && ws_bytes < w.required + split_bytes(s, parts)) --parts;
   return parts > 1 ? parts : 1;
+}
+
+// Whether the dense path halves the keys between two teams of waves of a workgroup.  Such a workgroup fills a compute unit (eight
+// waves of 256 registers): it pays where no compute unit would get two workgroups -- query tiles of a head are dealt to the
+// eight XCDs in runs, so it is the 32 compute units of the XCD with the most tiles that count -- and where the walk is long
+// enough to make up for the handing over.  us, one team / two:
+//   d = 128: 512 tokens, 1 head 14.1 / 14.3; 768, 4: 19.0 / 18.1; 1024, 31: 29.8 / 28.3; 4140, 4: 79.9 / 68.9; 9900, 3: 198 / 168;
+//     32,760, 1: 559 / 516; two workgroups on some compute units: 4140, 7: 123 / 141; 9900, 4: 273 / 301
+//   d = 64: 320 tokens, 8 heads 7.8 / 8.1; 512, 16: 10.7 / 10.3; 1365, 6: 22.3 / 19.0; 9900, 3: 128 / 103; 1365, 22: 34.2 / 38.1
+bool dense_teams(const pasa_shape_t* s) {
+  const int64_t q_tiles_per_xcd = ((int64_t)s->n + 1023) / 1024, key_tiles = ((int64_t)s->n + 63) / 64;
+  return (int64_t)s->B * s->H * q_tiles_per_xcd <= 32 && key_tiles >= (s->d == 128 ? 12 : 8);
 }
 
 constexpr int kMaxDevices = 64;
@@ -411,11 +419,7 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     const int rs = kv_stats_impl(k, v, &s, mask_with_stats ? idx : nullptr, k_sel, ws, ws_bytes, stream);
     if (rs != PASA_OK) return rs;
   }
-  AttnWorkspace w = carve_attn(&s);
-  if (!sparse) {  // the room for partial results lies behind the statistics that the caller's shape may have left in ws
-    pasa_shape_t full = *shape;
-    if (check_group(full.group, nb) == PASA_OK && check_slices(&full) == PASA_OK) w = carve_attn(&full);
-  }
+  const AttnWorkspace w = carve_attn(&s);
   char* base = static_cast<char*>(ws);
   AttnParams a{};
   a.q = static_cast<const uint16_t*>(q); a.k = static_cast<const uint16_t*>(k); a.v = static_cast<const uint16_t*>(v);
@@ -443,7 +447,8 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     a.part_ml = reinterpret_cast<float*>(base + w.part_ml);
     a.queue = reinterpret_cast<uint32_t*>(base + w.queue);
   }
-  const int parts = attn_parts(&s, w, sparse ? k_sel : 0, ws_bytes);
+  a.teams = !sparse && dense_teams(&s);
+  const int parts = sparse ? attn_parts(&s, w, k_sel, ws_bytes) : 1;
   if (parts > 1) {
     a.split = 1;
     a.n_slices = parts;

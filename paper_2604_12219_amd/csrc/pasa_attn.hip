@@ -29,9 +29,12 @@
 //
 // Key split (grids that leave compute units without a workgroup).  A short sequence with few heads has fewer
 // query tiles than the device has compute units, and the kernel's time is one workgroup's serial walk: a step per
-// tile pair, each as long as the latency of a tile.  There every query tile is given to several workgroups, each
-// taking every n_parts-th selected block and a run of the chunks of the approximation, and the same second
-// kernel merges their partial results.  The rule is in pasa_api.hip (attn_parts).
+// tile pair, each as long as the latency of a tile.
+// Sparse path: every query tile is given to several workgroups, each taking every n_parts-th selected block and a run of
+// the chunks of the approximation, and the same second kernel merges their partial results.
+// Dense path: a workgroup has two teams of four waves, one for either half of the keys, each with a ring of its own; the
+// second team hands its result to the first one through LDS.  (Nothing goes through the workspace: callers may share one
+// among dense calls that overlap.)  The rules are in pasa_api.hip (attn_parts, dense_teams).
 //
 // Data movement.  All tiles (K, V, block statistics, group matrices) are 64-row tiles that stream
 // through a ring of four 16 KB LDS buffers by direct global->LDS loads: the exact passes consume a
@@ -315,21 +318,26 @@ struct BitWalk {
 // 2: sparse, two adjacent 64-token query blocks per workgroup.  MULTI: the group has fewer than 32
 // blocks, so a chunk of 32 blocks intersects several groups and the per-block weights of a chunk have
 // to be kept until all of its group matrices have passed.  PART: kWhole: a workgroup walks all keys of its
-// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kSplit: key split (partial results).
-enum : int { kWhole = 0, kSliced = 1, kSplit = 2 };
+// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kSplit: key split of the sparse
+// path (partial results); kTeams (dense): two teams of waves.
+enum : int { kWhole = 0, kSliced = 1, kSplit = 2, kTeams = 3 };
+constexpr int teams_of(int part) { return part == kTeams ? 2 : 1; }
 template <int D, int MODE, bool MULTI, int PART>
-__global__ void __launch_bounds__(kWaves * 64, 2) attn_kernel(AttnParams p) {
+__global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(AttnParams p) {
   constexpr bool SPARSE = MODE != 0, SLICED = PART == kSliced, SPLIT = PART == kSplit;
+  constexpr int TEAMS = teams_of(PART);
+  static_assert(TEAMS == 1 || MODE == 0, "the sparse passes count on every wave of the workgroup making the same steps");
   constexpr int TILE_BYTES = 64 * 2 * D;
   constexpr int NI = TileDma<D>::NI;
   constexpr int HPARTS = D / 64;  // 64-row tiles per group matrix
-  __shared__ __attribute__((aligned(1024))) char ring[kRing * TILE_BYTES];
+  __shared__ __attribute__((aligned(1024))) char ring[TEAMS * kRing * TILE_BYTES];
 
   __shared__ int s_item, s_queue;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (kWaves * 64));
+  const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) - team * kWaves);  // within the team
   const int ql = lane & 31, h = lane >> 5;
-  const uint32_t ring_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring;
+  const uint32_t ring_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + (uint32_t)(team * kRing * TILE_BYTES);
   LaneOffsets<D> lo;
   lo.init(lane);
   TileDma<D> dma;
@@ -502,9 +510,9 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_kernel(AttnParams p) {
     if constexpr (SPARSE) {
       walk.init(mask_a, mask_b, w_lo, w_hi, first_a, first_b, lane, own_w, own_sel);
       blk = first_of(walk, slice);
-    } else if constexpr (SPLIT) {
-      dense_next = __builtin_amdgcn_readfirstlane((int)((int64_t)slice * n_dense_tiles / p.n_slices));
-      dense_end = __builtin_amdgcn_readfirstlane((int)((int64_t)(slice + 1) * n_dense_tiles / p.n_slices));
+    } else if constexpr (TEAMS == 2) {  // the first half of the tiles (rounded down) and the rest
+      if (team == 0) dense_end = n_dense_tiles / 2;
+      else dense_next = n_dense_tiles / 2;
     }
     auto plan = [&]() -> int {  // first row of the next tile, or -1
       if constexpr (MODE == 0) {
@@ -557,6 +565,8 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_kernel(AttnParams p) {
       r_cur = r_nxt;
       ++pair;
     }
+    if constexpr (TEAMS == 2)  // one barrier per tile, the same number in both teams
+      if (team == 0 && (n_dense_tiles & 1)) ring_barrier<NI>(0);
   }
 
   // ---------------- exact attention, part 2: key blocks that only one of the two query blocks selected ----------------
@@ -803,9 +813,39 @@ __global__ void __launch_bounds__(kWaves * 64, 2) attn_kernel(AttnParams p) {
   // The last steps of the tile loops repeat a request that nobody consumes: let those loads land
   // before this workgroup's LDS can be handed to another one.
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  const float l_tot = half_swap_sum(w.l);
+  float l_tot = half_swap_sum(w.l);
+  if constexpr (TEAMS == 2) {  // the second team leaves its result in its own ring (as large as that), m and l in the other's
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    static_assert(kWaves * 64 * D / 2 * sizeof(float) == kRing * TILE_BYTES, "half of D value columns per lane");
+    f32x4* const xo = reinterpret_cast<f32x4*>(ring + kRing * TILE_BYTES) + wave * (D / 8) * 64 + lane;
+    float2* const xml = reinterpret_cast<float2*>(ring) + wave * 64 + lane;
+    ring_barrier<NI>(0);  // no load into a ring is in flight and nobody reads one any more
+    if (team == 1) {
+#pragma unroll
+      for (int t = 0; t < D / 32; ++t)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          xo[(4 * t + g) * 64] = f32x4{w.o[t][4 * g], w.o[t][4 * g + 1], w.o[t][4 * g + 2], w.o[t][4 * g + 3]};
+      *xml = make_float2(w.m, l_tot);
+    }
+    __syncthreads();
+    if (team == 1) return;
+    // as merge_kernel; a team that had no tile has m = -inf, l = 0
+    const float2 ml = *xml;
+    const float M = fmaxf(w.m, ml.x), f0 = __builtin_amdgcn_exp2f(w.m - M), f1 = __builtin_amdgcn_exp2f(ml.x - M);
+    w.m = M;
+    l_tot = f0 * l_tot + f1 * ml.y;
+#pragma unroll
+    for (int t = 0; t < D / 32; ++t)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 x = xo[(4 * t + g) * 64];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w.o[t][4 * g + r] = f0 * w.o[t][4 * g + r] + f1 * x[r];
+      }
+  }
   if (q_row < n) {
-    if constexpr (PART != kWhole) {  // leave the partial result of this slice or part to the merge kernel
+    if constexpr (SLICED || SPLIT) {  // leave the partial result of this slice or part to the merge kernel
       const int64_t prow = ((int64_t)bh * p.n_slices + slice) * n + q_row;
       float* orow = p.part_o + prow * D;
 #pragma unroll
@@ -884,15 +924,18 @@ __global__ void __launch_bounds__(256) merge_kernel(AttnParams p) {
 
 template <int D, int MODE, bool MULTI, int PART>
 hipError_t launch(const AttnParams& p, int grid, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_kernel<D, MODE, MULTI, PART>), dim3(grid), dim3(kWaves * 64), 0, stream, p);
+  hipLaunchKernelGGL((attn_kernel<D, MODE, MULTI, PART>), dim3(grid), dim3(teams_of(PART) * kWaves * 64), 0, stream, p);
   return hipGetLastError();
 }
 
 template <int D, int MODE, bool MULTI>
 hipError_t launch_part(const AttnParams& p, int grid, hipStream_t stream) {
-  if (p.split) return launch<D, MODE, MULTI, kSplit>(p, grid, stream);
-  if constexpr (MODE != 0)
+  if constexpr (MODE == 0) {
+    if (p.teams) return launch<D, MODE, MULTI, kTeams>(p, grid, stream);
+  } else {
+    if (p.split) return launch<D, MODE, MULTI, kSplit>(p, grid, stream);
     if (p.n_slices > 1) return launch<D, MODE, MULTI, kSliced>(p, grid, stream);
+  }
   return launch<D, MODE, MULTI, kWhole>(p, grid, stream);
 }
 

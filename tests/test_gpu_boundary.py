@@ -159,3 +159,17 @@ def test_nothing_is_written_outside_the_buffers_and_nothing_outside_the_inputs_i
     ref = oracle.pasa_attention(to_f64(q0), to_f64(k0), to_f64(v0), b["idx"].cpu().numpy(), block, group=group)
     assert_close(to_f64(b["out"]), ref, what="guarded sparse")
     assert_close(to_f64(b["dense"]), oracle.dense_attention(to_f64(q0), to_f64(k0), to_f64(v0)), what="guarded dense")
+
+
+@pytest.mark.parametrize("n,heads,d,group", [(1365, 2, 64, 32), (4140, 1, 128, 32), (300, 1, 128, 64)])
+def test_dense_calls_leave_the_workspace_alone(P, n, heads, d, group):
+    """dense calls may share a workspace with calls that overlap them, and with statistics of whatever shape: not a byte of it
+    changes"""
+    q, k, v = workloads.make_qkv((1, 1, n), heads, d, seed=n, device="cuda")
+    shape, other = P.Shape.of(q, group=group), P.Shape.of(q, group=0)  # (the group is ignored by the dense path)
+    ws = P.kv_stats(k, v, shape, ws=torch.full((P.attn_workspace_bytes(shape) + (32 << 20),), 0xA5, dtype=torch.uint8, device="cuda"))
+    before = ws.clone()
+    P.attn_dense_ref(q, k, v, shape, ws=ws)
+    P.attn_dense_ref(q, k, v, other, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(ws, before)
