@@ -104,10 +104,7 @@ PASA_API size_t pasa_score_workspace_bytes(const pasa_shape_t* shape);
 /* host-only.  Bytes of scratch pasa_kv_stats, pasa_sparse_attn_fwd and pasa_attn_dense_ref need (key/value block
  * statistics, group matrices and unit sums, block-mean keys for pasa_block_score_with_stats, room for a selection
  * bitmap: 0.20 GB at 40 heads of 75,600 tokens; with kv_slices > 1 also the per-slice partial results:
- * B*H*kv_slices*n*(d+2)*4 bytes, 12.6 GB at 40 heads of 75,600 tokens with 8 slices); 0 on a bad shape.
- * Shapes of at most 128 query tiles (B*H*ceil(n/128)) get room for partial results as well, at most 18 MB: with it
- * the sparse kernel may share a query tile out among several workgroups.  A workspace without that room is accepted
- * and then every query tile is one workgroup's (the results differ by floating-point summation order only). */
+ * B*H*kv_slices*n*(d+2)*4 bytes, 12.6 GB at 40 heads of 75,600 tokens with 8 slices); 0 on a bad shape. */
 PASA_API size_t pasa_attn_workspace_bytes(const pasa_shape_t* shape);
 
 /*
@@ -198,7 +195,9 @@ PASA_API int pasa_key_prior(const void* k, const void* v, const pasa_shape_t* sh
  *   O_t = Num / Den   (one online-softmax normaliser; b_j = valid tokens of block j)
  * pasa_sparse_attn_fwd recomputes the key/value statistics on every call (pasa_kv_stats, then the
  * attention kernel).  pasa_sparse_attn_fwd_prepared runs the attention kernel alone and requires
- * that `ws` was filled by pasa_kv_stats for the same k, v and shape and not touched since.
+ * that `ws` was filled by pasa_kv_stats for the same k, v and shape and not touched since.  With a bitmap and kv_slices <= 1
+ * it only reads `ws`, as pasa_key_prior and pasa_block_score_with_stats do: such calls may overlap on one set of
+ * statistics.  pasa_kv_stats, pasa_sparse_attn_fwd and prepared calls with index lists alone write it.
  *   idx    int32 [BH, N_B, k_sel], each row strictly ascending, values in [0, N_B), or NULL if mask is given
  *   mask   uint32 [BH, N_B, ceil(N_B/32)], the bitmap of the same selection (as pasa_route writes it), or NULL if
  *          idx is given.  The kernels walk a bitmap: with mask == NULL one is first built from idx in the workspace

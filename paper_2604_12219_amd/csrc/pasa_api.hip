@@ -19,8 +19,6 @@ namespace {
 constexpr size_t kAlign = 256;
 constexpr int kMaxChunks = 8192;   // chunks of 32 key blocks per head (262,144 key blocks)
 constexpr int kMaxGroups = 65535;  // first-order groups per head
-// Key split (attn_parts): workgroups wanted, the most parts of a query tile, and the tile steps a part has to have
-constexpr int kSplitWorkgroups = 256, kMaxParts = 8, kMinSteps = 6;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -52,9 +50,8 @@ int check_group(int group, int nb) {
 float effective_scale(const pasa_shape_t* s) { return s->scale > 0.f ? s->scale : 1.0f / sqrtf((float)s->d); }
 
 struct AttnWorkspace {
-  size_t st, hg, partial, kbar, part_o, part_ml, queue, bitmap, required, total;
+  size_t st, hg, partial, kbar, part_o, part_ml, queue, bitmap, total;
   int n_groups, unit, n_units, n_chunks, n_slices;
-  int max_parts;  // key split: there is room for this many parts between `required` and `total`
 };
 
 // Number of key-range slices of the sparse kernel.  K and V of one head should fit the 4 MB L2 of an
@@ -72,23 +69,6 @@ int check_slices(const pasa_shape_t* s) {
   if (s->kv_slices <= 1) return PASA_OK;
   if (s->kv_slices % 8 != 0 || s->kv_slices > (num_blocks(s) + 31) / 32) return PASA_EUNSUPPORTED;
   return PASA_OK;
-}
-
-// Key split of small grids, sparse path: every query tile is shared out among several workgroups, whose partial results (fp32 numerators,
-// then maxima and normalisers) take this many bytes.
-size_t numerator_bytes(const pasa_shape_t* s, int parts) { return align_up((size_t)s->B * s->H * parts * s->n * s->d * 4); }
-size_t split_bytes(const pasa_shape_t* s, int parts) {
-  return parts > 1 ? numerator_bytes(s, parts) + align_up((size_t)s->B * s->H * parts * s->n * 2 * 4) : 0;
-}
-
-// The largest number of parts a workspace has room for.  A workspace that fits the static scratch array without this room
-// also fits it with it, so that pasa_sparse_attn_fwd_static takes the same shapes.
-int max_parts(const pasa_shape_t* s, size_t required) {
-  const int64_t wgs = (int64_t)s->B * s->H * ((s->n + 127) / 128);
-  int parts = (int)(kSplitWorkgroups / wgs < kMaxParts ? kSplitWorkgroups / wgs : kMaxParts);
-  while (parts > 1 && required <= (size_t)PASA_STATIC_SCRATCH_BYTES && required + split_bytes(s, parts) > (size_t)PASA_STATIC_SCRATCH_BYTES)
-    --parts;
-  return parts > 1 ? parts : 1;
 }
 
 // Blocks summed by one workgroup of the statistics kernel: a whole group, at most 32 blocks, or half of that, a quarter, ...
@@ -143,26 +123,8 @@ AttnWorkspace carve_attn(const pasa_shape_t* s) {
     w.partial = off; off = align_up(off + bh * w.n_units * s->d * s->d * 4);
     w.kbar = off; off = align_up(off + bh * nb * s->d * 4);  // block-mean keys as split bf16 pairs, for pasa_block_score_with_stats
   }
-  w.required = w.total = off;
-  w.max_parts = w.n_slices > 1 ? 1 : max_parts(s, w.required);
-  w.total += split_bytes(s, w.max_parts);
+  w.total = off;
   return w;
-}
-
-// Into how many parts the sparse path cuts the key list of every query tile (1: not at all).  Where query tiles are fewer
-// than compute units the kernel takes as long as one workgroup's serial walk, about a microsecond per tile step; the
-// partial results and their merge cost 2 to 5 us, so a part has to have a few steps of its own, and as the parts each go through
-// a group's whole matrix, more than one workgroup per compute unit does not pay.
-// Attention alone, us, one part / the rule's: 4140 tokens, 15 % of the blocks, 1 head: 26 / 21, 4 heads (132 query tiles):
-// 30, cut in three 33.
-int attn_parts(const pasa_shape_t* s, const AttnWorkspace& w, int k_sel, size_t ws_bytes) {
-  const int64_t wgs = (int64_t)s->B * s->H * ((s->n + 127) / 128);
-  const int64_t steps = (int64_t)k_sel * (s->block / 64) + (s->group > 0 ? w.n_chunks + (int64_t)w.n_groups * (s->d / 64) : 0);
-  int64_t wanted = kSplitWorkgroups / wgs;
-  if (wanted > steps / kMinSteps) wanted = steps / kMinSteps;
-  int parts = wanted < w.max_parts ? (int)wanted : w.max_parts;
-  while (parts > 1 && ws_bytes < w.required + split_bytes(s, parts)) --parts;
-  return parts > 1 ? parts : 1;
 }
 
 // Whether the dense path halves the keys between two teams of waves of a workgroup.  Such a workgroup fills a compute unit (eight
@@ -323,7 +285,7 @@ static int check_attn_args(const pasa_shape_t* shape, bool sparse, const void* w
   }
   if (!ws) return PASA_EINVAL;
   if (!aligned16(ws)) return PASA_EALIGN;
-  if (ws_bytes < carve_attn(s).required) return PASA_EWORKSPACE;
+  if (ws_bytes < carve_attn(s).total) return PASA_EWORKSPACE;
   return PASA_OK;
 }
 
@@ -448,13 +410,6 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     a.queue = reinterpret_cast<uint32_t*>(base + w.queue);
   }
   a.teams = !sparse && dense_teams(&s);
-  const int parts = sparse ? attn_parts(&s, w, k_sel, ws_bytes) : 1;
-  if (parts > 1) {
-    a.split = 1;
-    a.n_slices = parts;
-    a.part_o = reinterpret_cast<float*>(base + w.required);
-    a.part_ml = reinterpret_cast<float*>(base + w.required + numerator_bytes(&s, parts));
-  }
   return pasa_launch_attn(a, sparse, s.d, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 

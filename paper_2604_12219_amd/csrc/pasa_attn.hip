@@ -27,14 +27,11 @@
 // workgroup leaves an unnormalised partial result (running maximum, normaliser share, numerator),
 // and a small second kernel merges the partial results of a row.
 //
-// Key split (grids that leave compute units without a workgroup).  A short sequence with few heads has fewer
-// query tiles than the device has compute units, and the kernel's time is one workgroup's serial walk: a step per
-// tile pair, each as long as the latency of a tile.
-// Sparse path: every query tile is given to several workgroups, each taking every n_parts-th selected block and a run of
-// the chunks of the approximation, and the same second kernel merges their partial results.
-// Dense path: a workgroup has two teams of four waves, one for either half of the keys, each with a ring of its own; the
-// second team hands its result to the first one through LDS.  (Nothing goes through the workspace: callers may share one
-// among dense calls that overlap.)  The rules are in pasa_api.hip (attn_parts, dense_teams).
+// Dense path, grids with at most one query tile per compute unit.  The kernel's time is then one workgroup's serial walk,
+// a step per tile pair, each as long as the latency of a tile.  There a workgroup has two teams of four waves, one for
+// either half of the keys, each with a ring of its own; the second team hands its result to the first one through LDS.
+// (Nothing goes through the workspace: callers may share one among calls that overlap.)  The rule is in pasa_api.hip
+// (dense_teams).
 //
 // Data movement.  All tiles (K, V, block statistics, group matrices) are 64-row tiles that stream
 // through a ring of four 16 KB LDS buffers by direct global->LDS loads: the exact passes consume a
@@ -163,7 +160,7 @@ PASA_DEVICE void approx_chunk_zeroth(uint32_t tile, const LaneOffsets<D>& lo, Wa
   }
   mx = half_swap_max(mx) * c;
   if (__builtin_amdgcn_ballot_w64(mx > w.m)) rescale<D>(w, fmaxf(w.m, mx));
-  const float neg = w.m == -INFINITY ? 0.f : -w.m;  // (a part may have seen nothing yet and find every block selected)
+  const float neg = -w.m;
   float sum = 0.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -318,13 +315,12 @@ struct BitWalk {
 // 2: sparse, two adjacent 64-token query blocks per workgroup.  MULTI: the group has fewer than 32
 // blocks, so a chunk of 32 blocks intersects several groups and the per-block weights of a chunk have
 // to be kept until all of its group matrices have passed.  PART: kWhole: a workgroup walks all keys of its
-// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kSplit: key split of the sparse
-// path (partial results); kTeams (dense): two teams of waves.
-enum : int { kWhole = 0, kSliced = 1, kSplit = 2, kTeams = 3 };
+// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two teams of waves.
+enum : int { kWhole = 0, kSliced = 1, kTeams = 2 };
 constexpr int teams_of(int part) { return part == kTeams ? 2 : 1; }
 template <int D, int MODE, bool MULTI, int PART>
 __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(AttnParams p) {
-  constexpr bool SPARSE = MODE != 0, SLICED = PART == kSliced, SPLIT = PART == kSplit;
+  constexpr bool SPARSE = MODE != 0, SLICED = PART == kSliced;
   constexpr int TEAMS = teams_of(PART);
   static_assert(TEAMS == 1 || MODE == 0, "the sparse passes count on every wave of the workgroup making the same steps");
   constexpr int TILE_BYTES = 64 * 2 * D;
@@ -365,7 +361,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   // query tile selects many more blocks from the slice it lies in -- so one busy XCD would hold up
   // the dispatch to all the others.)
   for (;;) {
-  int bh, qt, slice = 0;  // slice: the key slice, or with key split the part
+  int bh, qt, slice = 0;
   if constexpr (SLICED) {
     // An item of this XCD's queue; once that is empty, of the next non-empty one, so that every item is computed
     // whichever XCDs the workgroups of the launch run on (fewer than eight, a masked or partitioned device).
@@ -390,13 +386,6 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
     bh = hr / rounds;
     // start each slice's sweep over the query tiles at the tiles that lie in the slice itself
     qt = (int)((item % p.q_tiles + (int64_t)slice * p.q_tiles / p.n_slices) % p.q_tiles);
-  } else if constexpr (SPLIT) {  // q_tiles_per_xcd counts (query tile, part) pairs here
-    const int local = blockIdx.x / kXcds;
-    bh = local / p.q_tiles_per_xcd;
-    const int item = xcd * p.q_tiles_per_xcd + local % p.q_tiles_per_xcd;
-    qt = __builtin_amdgcn_readfirstlane(item / p.n_slices);
-    slice = item - qt * p.n_slices;
-    if (qt >= p.q_tiles) return;  // padding workgroup (the whole workgroup leaves before any barrier)
   } else {
     const int local = blockIdx.x / kXcds;
     bh = local / p.q_tiles_per_xcd;
@@ -443,21 +432,20 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   const bool approx_on = SPARSE && p.group > 0;
   const uint16_t* const st = approx_on ? p.st + (int64_t)bh * p.n_chunks * 64 * D : nullptr;
   const uint16_t* const hg = approx_on ? p.hg + (int64_t)bh * p.n_groups * D * D : nullptr;
-  // chunk (= bitmap word) range of this workgroup's key slice; of a part: the chunks whose approximation it takes
+  // chunk (= bitmap word) range of this workgroup's key slice
   // (wave-uniform; the divisions run on the vector unit, so the results are moved to scalar registers explicitly)
   const int c_lo = SPARSE ? __builtin_amdgcn_readfirstlane((int)((int64_t)slice * p.n_chunks / p.n_slices)) : 0;
   const int c_hi = SPARSE ? __builtin_amdgcn_readfirstlane((int)((int64_t)(slice + 1) * p.n_chunks / p.n_slices)) : 0;
-  const int w_lo = SPLIT ? 0 : c_lo, w_hi = SPLIT ? p.n_chunks : c_hi;  // words of the bitmap that the exact passes walk
   const int qb_a = MODE == 2 ? 2 * qt : qt;
   const_u32* const mask_a = SPARSE ? (const_u32*)(p.mask + ((int64_t)bh * p.nb + qb_a) * p.mask_words) : nullptr;
   const_u32* const mask_b = (MODE == 2 && qb_a + 1 < p.nb) ? mask_a + p.mask_words : mask_a;
   const_u32* const mask_row = second ? mask_b : mask_a;  // this wave's own row
-  // the first 64 words of the two rows, lane i word w_lo + i: every walk below starts from them
+  // the first 64 words of the two rows, lane i word c_lo + i: every walk below starts from them
   uint32_t first_a = 0u, first_b = 0u;
   if constexpr (SPARSE) {
-    if (w_lo + lane < w_hi) {
-      first_a = mask_a[w_lo + lane];
-      first_b = mask_b[w_lo + lane];
+    if (c_lo + lane < c_hi) {
+      first_a = mask_a[c_lo + lane];
+      first_b = mask_b[c_lo + lane];
     }
   }
   // The key blocks at the workgroup's own tokens (those that are selected and whole) come first: tokens of a video attend most
@@ -471,23 +459,11 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   if constexpr (SPARSE) {
     const int w = qb_a >> 5;
     const uint32_t whole = MODE == 2 ? ((qb_a + 2) * 64 <= n ? 3u : (qb_a + 1) * 64 <= n ? 1u : 0u) : ((qb_a + 1) * 128 <= n ? 1u : 0u);
-    if (w >= w_lo && w < w_hi) {
+    if (w >= c_lo && w < c_hi) {
       own_w = w;
       own_sel = (uint32_t)__builtin_amdgcn_readfirstlane((int)(mask_a[w] & mask_b[w] & (whole << (qb_a & 31))));
     }
   }
-  // The next block of a walk; with key split every n_parts-th one, from the `offset`-th on.
-  auto first_of = [&](auto& walk, int offset) -> int {
-    if constexpr (SPLIT)
-      for (int i = 0; i < offset; ++i) walk.next(lane);
-    return walk.next(lane);
-  };
-  auto next_of = [&](auto& walk) -> int {
-    if constexpr (SPLIT)
-      for (int i = 1; i < p.n_slices; ++i) walk.next(lane);
-    return walk.next(lane);
-  };
-
   // Tile requests.  The tile for key rows [r0, r0 + 64) is fetched from row tile_row(r0) on: shifted
   // back where it would reach beyond the last token, so that all 64 rows exist (r0 may even lie beyond
   // n: the second tile of the last 128-token block).  The consumer ignores the rows before r0.  Every
@@ -508,8 +484,8 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
     BitWalk<MODE == 2 ? 0 : 3> walk;
     int blk = kNoBlock, sub = 0, dense_next = 0, dense_end = n_dense_tiles;
     if constexpr (SPARSE) {
-      walk.init(mask_a, mask_b, w_lo, w_hi, first_a, first_b, lane, own_w, own_sel);
-      blk = first_of(walk, slice);
+      walk.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b, lane, own_w, own_sel);
+      blk = walk.next(lane);
     } else if constexpr (TEAMS == 2) {  // the first half of the tiles (rounded down) and the rest
       if (team == 0) dense_end = n_dense_tiles / 2;
       else dense_next = n_dense_tiles / 2;
@@ -521,12 +497,12 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
       } else if constexpr (MODE == 1) {  // two tiles per 128-token block
         if (blk == kNoBlock) return -1;
         const int r0 = blk * 128 + sub * 64;
-        if (++sub == 2) { sub = 0; blk = next_of(walk); }
+        if (++sub == 2) { sub = 0; blk = walk.next(lane); }
         return r0;
       } else {
         if (blk == kNoBlock) return -1;
         const int r0 = blk * 64;
-        blk = next_of(walk);
+        blk = walk.next(lane);
         return r0;
       }
     };
@@ -578,11 +554,9 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   if constexpr (MODE == 2) {
     BitWalk<1> only_a;
     BitWalk<2> only_b;
-    only_a.init(mask_a, mask_b, w_lo, w_hi, first_a, first_b, lane);
-    only_b.init(mask_a, mask_b, w_lo, w_hi, first_a, first_b, lane);
-    // (parts in reverse order: the parts that took one shared block more than others get the fewer private ones)
-    const int offset = SPLIT ? p.n_slices - 1 - slice : 0;
-    int a_blk = first_of(only_a, offset), b_blk = first_of(only_b, offset);
+    only_a.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b, lane);
+    only_b.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b, lane);
+    int a_blk = only_a.next(lane), b_blk = only_b.next(lane);
     if (a_blk != kNoBlock || b_blk != kNoBlock) {
       ring_barrier<NI>(0);  // every wave is done with the ring
       request(kb, (a_blk != kNoBlock ? a_blk : b_blk) * 64, 0);
@@ -595,7 +569,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
 #pragma unroll 1
       while (whole(a_blk) && whole(b_blk)) {
         ring_barrier<NI>(0);  // the K tiles have landed; the V slots are free
-        const int a_nxt = next_of(only_a), b_nxt = next_of(only_b);
+        const int a_nxt = only_a.next(lane), b_nxt = only_b.next(lane);
         const int a_rq2 = a_nxt != kNoBlock ? a_nxt : b_nxt != kNoBlock ? b_nxt : a_blk;
         const int b_rq2 = b_nxt != kNoBlock ? b_nxt : a_rq2;
         bf16x8 pf[4];
@@ -610,7 +584,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
 #pragma unroll 1
       while (a_blk != kNoBlock || b_blk != kNoBlock) {
         ring_barrier<NI>(0);  // the K tiles have landed; the V slots are free
-        // With key-range slicing or key split one of the two query blocks can run out of blocks before the other.
+        // With key-range slicing one of the two query blocks can run out of blocks before the other.
         // Its waves then go through the motions on the other block's tiles with an empty key window
         // (all weights zero), and the missing tile requests repeat the other block's: one code path.
         const bool have_a = a_blk != kNoBlock, have_b = b_blk != kNoBlock;
@@ -618,8 +592,8 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
         const bool read_b = second ? have_b : !have_a;  // whose slots this wave reads
         const uint32_t k_tile = slot(read_b ? 2 : 0), v_tile = slot(read_b ? 3 : 1);
         const int a_req = have_a ? a_blk : b_blk, b_req = have_b ? b_blk : a_blk;
-        const int a_nxt = have_a ? next_of(only_a) : kNoBlock;
-        const int b_nxt = have_b ? next_of(only_b) : kNoBlock;
+        const int a_nxt = have_a ? only_a.next(lane) : kNoBlock;
+        const int b_nxt = have_b ? only_b.next(lane) : kNoBlock;
         const int a_rq2 = a_nxt != kNoBlock ? a_nxt : b_nxt != kNoBlock ? b_nxt : a_req;
         const int b_rq2 = b_nxt != kNoBlock ? b_nxt : a_rq2;
         const int t_row = my_blk != kNoBlock ? tile_row(my_blk * 64) : 0;
@@ -845,7 +819,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
       }
   }
   if (q_row < n) {
-    if constexpr (SLICED || SPLIT) {  // leave the partial result of this slice or part to the merge kernel
+    if constexpr (SLICED) {  // leave the partial result of this slice to the merge kernel
       const int64_t prow = ((int64_t)bh * p.n_slices + slice) * n + q_row;
       float* orow = p.part_o + prow * D;
 #pragma unroll
@@ -933,7 +907,6 @@ hipError_t launch_part(const AttnParams& p, int grid, hipStream_t stream) {
   if constexpr (MODE == 0) {
     if (p.teams) return launch<D, MODE, MULTI, kTeams>(p, grid, stream);
   } else {
-    if (p.split) return launch<D, MODE, MULTI, kSplit>(p, grid, stream);
     if (p.n_slices > 1) return launch<D, MODE, MULTI, kSliced>(p, grid, stream);
   }
   return launch<D, MODE, MULTI, kWhole>(p, grid, stream);
@@ -952,9 +925,9 @@ hipError_t launch_d(const AttnParams& p, bool sparse, int grid, hipStream_t stre
 hipError_t pasa_launch_attn(AttnParams p, bool sparse, int d, hipStream_t stream) {
   p.c = p.scale * kLog2e;
   p.q_tiles = (p.n + 127) / 128;  // 128 query rows per workgroup
-  p.q_tiles_per_xcd = (p.q_tiles * (p.split ? p.n_slices : 1) + kXcds - 1) / kXcds;
+  p.q_tiles_per_xcd = (p.q_tiles + kXcds - 1) / kXcds;
   int grid = p.bh * kXcds * p.q_tiles_per_xcd;
-  if (p.n_slices > 1 && !p.split) {  // persistent: two workgroups per CU (64 KB of LDS each), work queues per XCD
+  if (p.n_slices > 1) {  // persistent: two workgroups per CU (64 KB of LDS each), work queues per XCD
     p.items_per_xcd = p.bh * (p.n_slices / kXcds) * p.q_tiles;
     int dev = 0, cus = 0;  // host queries only: nothing is allocated or synchronised
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {

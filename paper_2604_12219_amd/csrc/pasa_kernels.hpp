@@ -25,7 +25,6 @@ struct AttnParams {
   int32_t group, n_groups, n_chunks;
   // key-range slicing (sparse path): slice s covers chunks [s*n_chunks/n_slices, (s+1)*n_chunks/n_slices)
   int32_t n_slices;      // 1 = off (the attention kernel writes the output itself)
-  int32_t split;         // 1: not slices of the key range but parts of every query tile's own list of blocks
   int32_t teams;         // dense path, 1: the keys of a query tile are halved between two teams of waves of a workgroup
   float* part_o;         // fp32 [BH][n_slices][n][d]: unnormalised partial numerators
   float* part_ml;        // fp32 [BH][n_slices][n][2]: running maximum (log2 units) and partial normaliser

@@ -173,3 +173,41 @@ def test_dense_calls_leave_the_workspace_alone(P, n, heads, d, group):
     P.attn_dense_ref(q, k, v, other, ws=ws)
     torch.cuda.synchronize()
     assert torch.equal(ws, before)
+
+
+@pytest.mark.parametrize("n,heads,d,block,group,keep", [(4140, 1, 128, 64, 32, 0.15), (4140, 1, 128, 64, 32, 0.4), (1365, 2, 64, 64, 4, 0.6),
+                                                        (2100, 1, 128, 128, 64, 0.5), (4140, 1, 128, 64, 0, 0.3)])
+def test_prepared_calls_only_read_the_workspace(P, n, heads, d, block, group, keep):
+    """calls with a bitmap on one set of statistics: the workspace keeps every byte, dense calls in between change nothing, and
+    calls on two streams at a time give what they give one after the other"""
+    q, k, v = workloads.make_qkv((1, 1, n), heads, d, seed=n, device="cuda")
+    qs = [q, q.flip(2).contiguous()]
+    shape = P.Shape.of(q, block=block, group=group)
+    ws = P.kv_stats(k, v, shape, ws=torch.full((P.attn_workspace_bytes(shape) + (32 << 20),), 0xA5, dtype=torch.uint8, device="cuda"))
+    before = ws.clone()
+    nb = P.num_blocks(shape)
+    sel = [P.route(P.block_score(x, k, shape), P.topk_count(nb, keep), 3, 0.2) for x in qs]
+
+    def call(i, out=None):
+        idx, mask = sel[i]
+        if group == 0:  # without statistics the whole call has nothing to write either
+            return P.sparse_attn_fwd(qs[i], k, v, shape, idx, mask, ws=ws, out=out)
+        return P.sparse_attn_fwd(qs[i], k, v, shape, idx, mask, ws=ws, out=out, prepared=True)
+
+    want = [call(0), call(1)]
+    P.attn_dense_ref(q, k, v, shape, ws=ws)
+    P.attn_dense_ref(q, k, v, P.Shape.of(q, block=block, group=0), ws=ws)
+    assert torch.equal(call(0), want[0])
+    torch.cuda.synchronize()
+    assert torch.equal(ws, before)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs = [[torch.empty_like(q) for _ in range(20)] for _ in qs]
+    torch.cuda.synchronize()
+    for r in range(20):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                call(i, out=outs[i][r])
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert all(torch.equal(o, want[i]) for o in outs[i])
+    assert torch.equal(ws, before)

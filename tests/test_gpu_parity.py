@@ -378,44 +378,6 @@ def test_key_range_slicing_matches_oracle_and_unsliced_kernel(P, grid, d, block,
     np.testing.assert_allclose(lse.cpu().numpy(), res["lse"], atol=2e-2)
 
 
-SPLIT_CASES = [
-    # n, heads, d, block, group, keep -> parts
-    (1365, 2, 64, 64, 32, 0.6),     # 2: 22 tiles, the last one ragged; chunk and group of parts without one
-    (1365, 1, 128, 64, 4, 1.0),     # 6: small groups; every block selected (a part with nothing but selected blocks)
-    (2100, 1, 128, 128, 32, 0.5),   # 3: blocks of two tiles, odd number of them
-    (64 * 96, 1, 64, 64, 64, 0.15), # 3: two chunks per group
-    (4140, 1, 128, 64, 0, 0.3),     # 3: approximation off
-    (16380, 1, 128, 64, 32, 0.02),  # 2: more chunks than selected blocks, short last chunk
-]
-
-
-@pytest.mark.parametrize("n,heads,d,block,group,keep", SPLIT_CASES)
-def test_key_split_of_small_grids_matches_oracle_and_the_uncut_kernel(P, n, heads, d, block, group, keep):
-    """a workspace with room for partial results (query tiles shared out among workgroups) against one without that room
-    (NaN in both), and against the oracle.  Cut and uncut differ by the rounding of P and of the output to bf16: tolerances
-    as for key-range slicing above, which merges the same way"""
-    q, k, v = _inputs((1, 1, n), heads, d, seed=n)
-    shape = P.Shape.of(q, block=block, group=group)
-    full = P.attn_workspace_bytes(shape)
-    room = heads * n * (d + 2) * 4  # one part's results
-    base = full - room * min(8, 256 // (heads * ((n + 127) // 128)))
-    ws = [torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda") for size in (full, base + room // 2)]
-    nb = P.num_blocks(shape)
-    idx, mask = P.route(P.block_score(q, k, shape), P.topk_count(nb, keep), 3, 0.2)
-    res = oracle.pasa_attention(to_f64(q), to_f64(k), to_f64(v), idx.cpu().numpy(), block, group=group, return_all=True)
-    fn = lambda w: P.sparse_attn_fwd(q, k, v, shape, idx, mask, ws=w, want_lse=True)
-    (cut, cut_lse), (one, one_lse) = fn(ws[0]), fn(ws[1])
-    again, _ = fn(ws[0])
-    torch.cuda.synchronize()
-    assert torch.equal(cut, again) and not torch.equal(cut, one)
-    a, b = cut.float(), one.float()
-    assert (a - b).abs().max().item() <= 2e-2 * b.abs().max().item()
-    assert (a - b).abs().mean().item() <= 1e-3 * b.abs().mean().item()
-    np.testing.assert_allclose(cut_lse.cpu().numpy(), one_lse.cpu().numpy(), atol=1e-3)
-    assert_close(to_f64(cut), res["o"], what=f"cut {n} d={d} b={block} G={group}")
-    np.testing.assert_allclose(cut_lse.cpu().numpy(), res["lse"], atol=2e-2)
-
-
 def _lists(rng, nb, k_sel, keep_own):
     """index lists [1, nb, k_sel]: every row selects (keep_own: both, first, none) of the blocks 2 (i // 2), 2 (i // 2) + 1, the
     ones its workgroup visits first if they are in both rows of the pair, and random others"""
