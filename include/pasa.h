@@ -104,7 +104,10 @@ PASA_API size_t pasa_score_workspace_bytes(const pasa_shape_t* shape);
 /* host-only.  Bytes of scratch pasa_kv_stats, pasa_sparse_attn_fwd and pasa_attn_dense_ref need (key/value block
  * statistics, group matrices and unit sums, block-mean keys for pasa_block_score_with_stats, room for a selection
  * bitmap: 0.20 GB at 40 heads of 75,600 tokens; with kv_slices > 1 also the per-slice partial results:
- * B*H*kv_slices*n*(d+2)*4 bytes, 12.6 GB at 40 heads of 75,600 tokens with 8 slices); 0 on a bad shape. */
+ * B*H*kv_slices*n*(d+2)*4 bytes, 12.6 GB at 40 heads of 75,600 tokens with 8 slices); 0 on a bad shape.
+ * Where the statistics have few blocks to work on, this includes up to 16 MiB in which they keep the sums of smaller
+ * units (more workgroups).  A workspace without that room is accepted by every entry point; the results differ by
+ * floating-point summation order only. */
 PASA_API size_t pasa_attn_workspace_bytes(const pasa_shape_t* shape);
 
 /*
@@ -224,6 +227,7 @@ PASA_API int pasa_sparse_attn_fwd_prepared(const void* q, const void* k, const v
  * intermediates, the prior, the Gumbel bias or their own selection use the stage entry points instead.
  *   keep_ratio in (0, 1]; seed, noise_amp as in pasa_route; out, lse as in pasa_sparse_attn_fwd
  *   ws  pasa_forward_workspace_bytes(shape, keep_ratio) bytes (host-only helper; 0 on invalid arguments), 256-byte aligned
+ *       (without the room for small units, see pasa_attn_workspace_bytes, it is accepted as well)
  * N_B <= 4096 (the limit of pasa_route).
  */
 PASA_API size_t pasa_forward_workspace_bytes(const pasa_shape_t* shape, double keep_ratio);

@@ -50,8 +50,11 @@ int check_group(int group, int nb) {
 float effective_scale(const pasa_shape_t* s) { return s->scale > 0.f ? s->scale : 1.0f / sqrtf((float)s->d); }
 
 struct AttnWorkspace {
-  size_t st, hg, partial, kbar, part_o, part_ml, queue, bitmap, total;
-  int n_groups, unit, n_units, n_chunks, n_slices;
+  // `required` bytes hold everything that later calls read; between `required` and `total` there is room for the sums of units
+  // smaller than `slot_unit`, which the statistics use if the caller's workspace has it
+  size_t st, hg, partial, kbar, part_o, part_ml, queue, bitmap, required, total;
+  int n_groups, n_chunks, n_slices;
+  int slot_unit, n_slots, slots_per_group;  // the unit that the room for unit sums at `partial` is made for, and its units
 };
 
 // Number of key-range slices of the sparse kernel.  K and V of one head should fit the 4 MB L2 of an
@@ -71,21 +74,32 @@ int check_slices(const pasa_shape_t* s) {
   return PASA_OK;
 }
 
+int units_of(int nb, int unit) { return (nb + unit - 1) / unit; }
+
+// The unit that the workspace always has room for.  The size a caller needs is a function of this one alone, so that
+// a workspace does for the same shapes whatever unit the rule below takes.
+int slot_unit(int64_t bh, int nb, int group) {
+  int unit = group < 32 ? group : 32;
+  while (unit > 8 && bh * units_of(nb, unit) < 1024) unit /= 2;
+  return unit;
+}
+
 // Blocks summed by one workgroup of the statistics kernel: a whole group, at most 32 blocks, or half of that, a quarter, ...
-// (a power of two that divides the group).  512 workgroups run at a time, so the sweep takes as many rounds as there are 512
-// units, each as long as a unit and the writing and averaging of its sum, which is worth about 6 blocks.
-// kv_stats_kernel + hg_finish_kernel, us, units of 32 / 16 / 8 / 4: 12 heads of 512 blocks - / 60 / 67 / 83; 5 of 1182 - / 56 / 63 / 79;
-// 3 of 1857 in groups of 64 - / 53 / 60 / 74.
+// (which divides the group, unless the group is the whole sequence).  512 workgroups run at a time, so the sweep takes as many
+// rounds as there are 512 units, each as long as a unit and the writing and averaging of its sum, which is worth about 6 blocks.
+// kv_stats_kernel + hg_finish_kernel, us, units of 32 / 16 / 8 / 4: 12 heads of 512 blocks 73 / 58 / 65 / 81; 5 of 1182 72 / 58 / 65 / 79;
+// 3 of 1857 in groups of 64 75 / 54 / 61 / 74.
 // Below 8 blocks the unit sums are more bytes than the keys and values they come from; that pays only where even units of 8
 // leave most compute units without one and the kernel's time is that of one workgroup's serial sweep: 65 blocks x 4 heads
-// take kv_stats_kernel 20 us with units of 8 and 8.6 us with units of 2.
-int stats_unit(int64_t bh, int nb, int group) {
-  auto units = [&](int unit) { return bh * ((nb + unit - 1) / unit); };
+// take 22.9 us with units of 8 and 15.1 us with units of 2.  Units below slot_unit need room_bytes behind the required part.
+int stats_unit(int64_t bh, int nb, int group, int d, size_t room_bytes) {
+  auto units = [&](int unit) { return bh * units_of(nb, unit); };
   auto cost = [&](int unit) { return (units(unit) + 511) / 512 * (unit + 6); };
   int best = group < 32 ? group : 32;
   for (int unit = best / 2; unit >= 8 && units(2 * unit) < 1024; unit /= 2)  // (with 1024 units the sums are many already)
     if (cost(unit) < cost(best)) best = unit;
-  while (best > 1 && units(best) < 128) best /= 2;
+  const int slot = slot_unit(bh, nb, group);
+  while (best > 1 && units(best) < 128 && (best / 2 >= slot || (size_t)units(best / 2) * d * d * 4 <= room_bytes)) best /= 2;
   return best;
 }
 
@@ -116,14 +130,21 @@ AttnWorkspace carve_attn(const pasa_shape_t* s) {
   if (s->group > 0) {
     const int group = s->group >= nb ? nb : s->group;
     w.n_groups = (nb + group - 1) / group;
-    w.unit = stats_unit((int64_t)bh, nb, group);
-    w.n_units = (nb + w.unit - 1) / w.unit;
+    w.slot_unit = slot_unit((int64_t)bh, nb, group);
+    w.n_slots = units_of(nb, w.slot_unit);
+    w.slots_per_group = s->group >= nb ? w.n_slots : group / w.slot_unit;
     w.st = off; off = align_up(off + bh * w.n_chunks * 64 * s->d * 2);
     w.hg = off; off = align_up(off + bh * w.n_groups * s->d * s->d * 2);
-    w.partial = off; off = align_up(off + bh * w.n_units * s->d * s->d * 4);
+    w.partial = off; off = align_up(off + bh * w.n_slots * s->d * s->d * 4);
     w.kbar = off; off = align_up(off + bh * nb * s->d * 4);  // block-mean keys as split bf16 pairs, for pasa_block_score_with_stats
   }
-  w.total = off;
+  w.required = w.total = off;
+  if (s->group > 0) {
+    // room for small units, unless it would keep the shape from the static scratch array (PASA_STATIC_SCRATCH_BYTES)
+    const size_t room_most = w.required <= (size_t)PASA_STATIC_SCRATCH_BYTES ? (size_t)PASA_STATIC_SCRATCH_BYTES - w.required : ~(size_t)0;
+    const int unit = stats_unit((int64_t)bh, nb, s->group >= nb ? nb : s->group, s->d, room_most);
+    if (unit < w.slot_unit) w.total += align_up(bh * units_of(nb, unit) * s->d * s->d * 4);
+  }
   return w;
 }
 
@@ -285,7 +306,7 @@ static int check_attn_args(const pasa_shape_t* shape, bool sparse, const void* w
   }
   if (!ws) return PASA_EINVAL;
   if (!aligned16(ws)) return PASA_EALIGN;
-  if (ws_bytes < carve_attn(s).total) return PASA_EWORKSPACE;
+  if (ws_bytes < carve_attn(s).required) return PASA_EWORKSPACE;
   return PASA_OK;
 }
 
@@ -323,12 +344,21 @@ static int kv_stats_impl(const void* k, const void* v, const pasa_shape_t* shape
   t.k = static_cast<const uint16_t*>(k); t.v = static_cast<const uint16_t*>(v);
   t.stride_b = s.stride_b; t.stride_h = s.stride_h; t.stride_n = s.stride_n;
   t.bh = s.B * s.H; t.H = s.H; t.n = s.n; t.nb = nb; t.block = s.block; t.tail = s.n - (nb - 1) * s.block; t.d = s.d;
-  t.group = s.group >= nb ? nb : s.group; t.n_groups = w.n_groups; t.unit = w.unit; t.n_units = w.n_units;
+  t.group = s.group >= nb ? nb : s.group; t.n_groups = w.n_groups;
+  t.unit = stats_unit(t.bh, nb, t.group, s.d, ws_bytes - w.required);
+  t.n_units = units_of(nb, t.unit);
+  t.units_per_group = t.n_groups == 1 ? t.n_units : t.group / t.unit;
   t.scale = effective_scale(&s);
   t.n_chunks = w.n_chunks;
   t.st = reinterpret_cast<uint16_t*>(base + w.st);
   t.hg = reinterpret_cast<uint16_t*>(base + w.hg);
-  t.partial = reinterpret_cast<float*>(base + w.partial);
+  t.group_sum = reinterpret_cast<float*>(base + w.partial);
+  t.sum_head = w.n_slots; t.sum_group = w.slots_per_group;
+  if (t.unit >= w.slot_unit) {  // at most as many units as slots, in every group
+    t.partial = t.group_sum; t.partial_head = t.sum_head; t.partial_group = t.sum_group;
+  } else {
+    t.partial = reinterpret_cast<float*>(base + w.required); t.partial_head = t.n_units; t.partial_group = t.units_per_group;
+  }
   t.kbar_split = reinterpret_cast<uint16_t*>(base + w.kbar);
   t.idx = idx; t.k_sel = k_sel; t.mask_words = (nb + 31) / 32;
   t.mask = reinterpret_cast<uint32_t*>(base + w.bitmap);
@@ -354,11 +384,12 @@ int pasa_key_prior(const void* k, const void* v, const pasa_shape_t* shape, floa
   t.k = static_cast<const uint16_t*>(k); t.v = static_cast<const uint16_t*>(v);
   t.stride_b = s.stride_b; t.stride_h = s.stride_h; t.stride_n = s.stride_n;
   t.bh = s.B * s.H; t.H = s.H; t.n = s.n; t.nb = nb; t.block = s.block; t.tail = s.n - (nb - 1) * s.block; t.d = s.d;
-  t.group = s.group >= nb ? nb : s.group; t.n_groups = w.n_groups; t.unit = w.unit; t.n_units = w.n_units;
+  t.group = s.group >= nb ? nb : s.group; t.n_groups = w.n_groups;
   t.prior_unit = prior_unit(t.bh, nb, t.group);
   t.scale = effective_scale(&s);
   t.n_chunks = w.n_chunks;
-  t.partial = reinterpret_cast<float*>(base + w.partial);
+  t.group_sum = reinterpret_cast<float*>(base + w.partial);
+  t.sum_head = w.n_slots; t.sum_group = w.slots_per_group;
   return pasa_launch_key_prior(t, eps, beta, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
@@ -445,7 +476,7 @@ int pasa_sparse_attn_fwd_static(const void* q, const void* k, const void* v, con
 // ---- the whole forward in one call ---------------------------------------------------------------
 namespace {
 struct ForwardWorkspace {
-  size_t scores, idx, mask, score_ws, attn_ws, total;
+  size_t scores, idx, mask, score_ws, attn_ws, required, total;
   int nb, k_sel;
 };
 
@@ -460,14 +491,16 @@ ForwardWorkspace carve_forward(const pasa_shape_t* s, double keep_ratio) {
   pasa_shape_t a = *s;
   const size_t attn = pasa_attn_workspace_bytes(&a), score = pasa_score_workspace_bytes(&a);
   if (attn == 0 || score == 0) return f;
+  const size_t attn_required = carve_attn(&a).required;
   const size_t bh = (size_t)s->B * s->H;
   size_t off = 0;
   f.scores = off; off = align_up(off + bh * f.nb * f.nb * 4);
   f.idx = off; off = align_up(off + bh * f.nb * (size_t)k * 4);
   f.mask = off; off = align_up(off + bh * f.nb * (size_t)((f.nb + 31) / 32) * 4);
   f.score_ws = off; off = align_up(off + score);
-  f.attn_ws = off; off = align_up(off + attn);
-  f.total = off;
+  f.attn_ws = off;
+  f.required = off + attn_required;
+  f.total = off + attn;
   return f;
 }
 }  // namespace
@@ -487,13 +520,13 @@ int pasa_forward(const void* q, const void* k, const void* v, const pasa_shape_t
   if (f.total == 0) return PASA_EUNSUPPORTED;
   if (!q || !k || !v || !out || !ws) return PASA_EINVAL;
   if (!aligned16(ws)) return PASA_EALIGN;
-  if (ws_bytes < f.total) return PASA_EWORKSPACE;
+  if (ws_bytes < f.required) return PASA_EWORKSPACE;
   if (f.nb > kRouteMaxBlocks) return PASA_EUNSUPPORTED;
   char* base = static_cast<char*>(ws);
   float* scores = reinterpret_cast<float*>(base + f.scores);
   int32_t* idx = reinterpret_cast<int32_t*>(base + f.idx);
   uint32_t* mask = reinterpret_cast<uint32_t*>(base + f.mask);
-  const size_t attn_bytes = pasa_attn_workspace_bytes(shape), score_bytes = pasa_score_workspace_bytes(shape);
+  const size_t attn_bytes = ws_bytes - f.attn_ws, score_bytes = pasa_score_workspace_bytes(shape);
   int r;
   if (shape->group > 0) {  // the statistics first: scoring takes the block-mean keys from them
     r = pasa_kv_stats(k, v, shape, base + f.attn_ws, attn_bytes, stream);

@@ -42,14 +42,17 @@ struct StatsParams {
   int32_t bh, H, n, nb, block, tail, d;
   int32_t group;     // > 0
   int32_t n_groups;  // ceil(nb / group)
-  int32_t unit;      // blocks summed by one workgroup: a power of two that divides the group, at most 32
+  int32_t unit;      // blocks summed by one workgroup, at most 32: divides the group unless that is the whole sequence
   int32_t n_units;   // units per head
+  int32_t units_per_group;
   int32_t prior_unit;  // the prior's kernel: blocks that one of its workgroups looks at (as `unit`, of its own)
   float scale;
   int32_t n_chunks;  // ceil(nb / 32)
   uint16_t* st;      // out bf16 [BH][n_chunks][64][d] (see AttnParams::st)
-  float* partial;    // scratch fp32 [BH][n_units][d][d]: sum over the unit's blocks of H_j; once the statistics are done the
-                     // slot of a group's first unit holds the sum over the whole group
+  float* partial;    // scratch fp32, slots of [d][d]: sum over a unit's blocks of H_j; unit i of group g of head bh in slot
+  int32_t partial_head, partial_group;      //  bh * partial_head + g * partial_group + i
+  float* group_sum;  // scratch fp32: sum over the whole group g in slot bh * sum_head + g * sum_group.  In the place of the group's
+  int32_t sum_head, sum_group;              // first unit where the units' sums lie in the same array
   uint16_t* hg;      // out bf16 [BH][n_groups][d][d] (see AttnParams::hg)
   uint16_t* kbar_split;  // out [BH][nb][d] x 4 bytes: block-mean keys as split bf16 pairs in the score kernel's layout
                          // (per 32 elements 32 x hi then 32 x lo), so that scoring need not read K again
@@ -59,7 +62,7 @@ struct StatsParams {
   uint32_t* mask;        // out [BH][nb][mask_words]
 };
 hipError_t pasa_launch_kv_stats(const StatsParams& p, hipStream_t stream);
-// beta [BH][nb] fp32 = log(||H_j - Hg_{g(j)}||_F + eps); needs p.partial as pasa_launch_kv_stats left it
+// beta [BH][nb] fp32 = log(||H_j - Hg_{g(j)}||_F + eps); needs p.group_sum as pasa_launch_kv_stats left it
 hipError_t pasa_launch_key_prior(const StatsParams& p, float eps, float* beta, hipStream_t stream);
 
 struct ScoreParams {

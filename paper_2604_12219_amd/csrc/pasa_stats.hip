@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(256, 2) kv_stats_kernel(StatsParams p) {
       p.st[(((int64_t)bh * p.n_chunks + (j >> 5)) * 64 + (tid >= D ? 32 : 0) + (j & 31)) * D + col] = 0;
   }
 
-  float* out = p.partial + ((int64_t)bh * p.n_units + u) * D * D;
+  float* out = p.partial + ((int64_t)bh * p.partial_head + (int64_t)(u / p.units_per_group) * p.partial_group + u % p.units_per_group) * D * D;
 #pragma unroll
   for (int a = 0; a < TI; ++a)
 #pragma unroll
@@ -184,8 +184,8 @@ __global__ void __launch_bounds__(256, 2) kv_stats_kernel(StatsParams p) {
   }
 }
 
-// partial [BH][n_units][d_in][d_out] fp32 -> hg [BH][n_groups][d_out][d_in] bf16 = (scale * Hg)^T, and the group's fp32 sum
-// into the slot of its first unit (for key_prior_kernel).  Bound by the latency of its loads (a group is 64 KB per unit):
+// unit sums [d_in][d_out] fp32 -> hg [BH][n_groups][d_out][d_in] bf16 = (scale * Hg)^T, and the group's fp32 sum
+// (for key_prior_kernel).  Bound by the latency of its loads (a group is 64 KB per unit):
 // a workgroup takes a 16 x 64 piece of the matrix, four consecutive value columns per thread in 16-byte loads of which
 // eight units' are in flight at once, and turns the piece through LDS, so that the stores are whole 32-byte runs.
 // (One thread per eight key columns of a value column, 4-byte loads one unit after the other, took 21 us for two groups of
@@ -196,13 +196,13 @@ __global__ void __launch_bounds__(256) hg_finish_kernel(StatsParams p) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   __shared__ __attribute__((aligned(16))) uint16_t piece[kFinishOut][kFinishIn + 8];
   const int g = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
-  const int upg = (p.group >= p.nb) ? p.n_units : p.group / p.unit;  // units per group
-  const int u_lo = g * upg, n_u = min(upg, p.n_units - u_lo);
+  const int n_u = min(p.units_per_group, p.n_units - g * p.units_per_group);
   const int blocks_in_group = min((g + 1) * p.group, p.nb) - g * p.group;
   const float f = p.scale / (float)blocks_in_group;
   const int in0 = kFinishIn * (blockIdx.z % (D / kFinishIn)), out0 = kFinishOut * (blockIdx.z / (D / kFinishIn));
   const int in = tid >> 4, out = (tid & 15) * 4;
-  float* const src = p.partial + ((int64_t)bh * p.n_units + u_lo) * D * D + (in0 + in) * D + out0 + out;
+  const int at = (in0 + in) * D + out0 + out;
+  const float* const src = p.partial + ((int64_t)bh * p.partial_head + (int64_t)g * p.partial_group) * D * D + at;
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
   int u = 0;
   for (; u + 8 <= n_u; u += 8) {
@@ -214,7 +214,8 @@ __global__ void __launch_bounds__(256) hg_finish_kernel(StatsParams p) {
   }
 #pragma unroll 4
   for (; u < n_u; ++u) sum += *reinterpret_cast<const f32x4*>(src + (int64_t)u * D * D);
-  *reinterpret_cast<f32x4*>(src) = sum;  // read above by this thread alone
+  // (may be where the first unit's sum was, which this thread alone has read above)
+  *reinterpret_cast<f32x4*>(p.group_sum + ((int64_t)bh * p.sum_head + (int64_t)g * p.sum_group) * D * D + at) = sum;
 #pragma unroll
   for (int e = 0; e < 4; ++e) piece[out + e][in] = __builtin_bit_cast(uint16_t, (__bf16)(sum[e] * f));
   __syncthreads();
@@ -227,7 +228,7 @@ __global__ void __launch_bounds__(256) hg_finish_kernel(StatsParams p) {
 
 // Covariance-aware routing prior (Eq.8): beta_j = log(|| H_j - Hg_{g(j)} ||_F + eps) for every key block.
 // The same sweep as kv_stats_kernel, but H_j is formed per block and compared, element by element in fp32, with the
-// group mean, from the group's sum that the statistics left in the slot of its first unit (`partial`).
+// group mean, from the group's sum that the statistics left.
 // Nothing but beta is written.
 template <int D>
 __global__ void __launch_bounds__(256) key_prior_kernel(StatsParams p, float eps, float* beta) {
@@ -242,9 +243,8 @@ __global__ void __launch_bounds__(256) key_prior_kernel(StatsParams p, float eps
 
   // the group these blocks belong to, and its mean
   const int g = j_lo / p.group;
-  const int upg = (p.group >= p.nb) ? p.n_units : p.group / p.unit;  // unit sums per group
   const float inv_blocks = 1.0f / (float)(min((g + 1) * p.group, p.nb) - g * p.group);
-  const float* const group_sum = p.partial + ((int64_t)bh * p.n_units + g * upg) * D * D;
+  const float* const group_sum = p.group_sum + ((int64_t)bh * p.sum_head + (int64_t)g * p.sum_group) * D * D;
   f32x16 mean[TI][TI];
 #pragma unroll
   for (int a = 0; a < TI; ++a)

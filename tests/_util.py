@@ -1,4 +1,6 @@
 """Helpers shared by the GPU parity tests."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -29,3 +31,16 @@ def assert_close(got, ref, rows=None, what=""):
     assert np.isfinite(got if rows is None else got[:, rows]).all(), f"{what}: non-finite output"
     for h, (mx, mean) in enumerate(rel_errors(got, ref, rows)):
         assert mx <= MAX_REL and mean <= MEAN_REL, f"{what}: head {h}: max_rel={mx:.3e} mean_rel={mean:.3e}"
+
+
+def attn_required_bytes(P, shape):
+    """the smallest attention workspace the entry points take for the shape (host-only calls with a null pointer: too small a
+    workspace is reported before it)"""
+    L, c = P.load_library(), shape.c()
+    lo, hi = 0, P.attn_workspace_bytes(shape)
+    while lo < hi:
+        mid = (lo + hi) // 2
+        rc = L.pasa_kv_stats(None, None, ctypes.byref(c), ctypes.c_void_p(0x1000), mid, None)
+        assert rc in (-1, -3)
+        lo, hi = (mid + 1, hi) if rc == -3 else (lo, mid)
+    return lo

@@ -177,6 +177,84 @@ def test_argument_validation_returns_before_any_launch(P):
         assert isinstance(L.pasa_strerror(code), bytes) and len(L.pasa_strerror(code)) > 0
 
 
+def _align(x):
+    return (x + 255) // 256 * 256
+
+
+def _attn_bytes(s):
+    """what the attention entry points have to be satisfied with: the slices' results, a bitmap, the statistics tiles, the group
+    matrices, the sums of units of at most 32 blocks (halved, down to 8, while that leaves fewer than 1024 of them), key means"""
+    bh, nb = s.B * s.H, -(-s.n // s.block)
+    chunks, total = -(-nb // 32), 0
+    if s.kv_slices > 1:
+        total += _align(bh * s.kv_slices * s.n * s.d * 4)
+        total = _align(total + bh * s.kv_slices * s.n * 8) + 256
+    total += _align(bh * nb * chunks * 4)
+    if s.group > 0:
+        group = min(s.group, nb)
+        unit = min(group, 32)
+        while unit > 8 and bh * -(-nb // unit) < 1024:
+            unit //= 2
+        total += _align(bh * chunks * 64 * s.d * 2) + _align(bh * -(-nb // group) * s.d * s.d * 2)
+        total += _align(bh * -(-nb // unit) * s.d * s.d * 4) + _align(bh * nb * s.d * 4)
+    return total
+
+
+def _forward_bytes(P, s, keep):
+    bh, nb = s.B * s.H, P.num_blocks(s)
+    return (_align(bh * nb * nb * 4) + _align(bh * nb * P.topk_count(nb, keep) * 4) + _align(bh * nb * -(-nb // 32) * 4) +
+            _align(P.score_workspace_bytes(s)) + _attn_bytes(s))
+
+
+def _workspace_shapes(P):
+    import random
+    rng = random.Random(5)
+    shapes = [_shape(P, H=1, n=64000), _shape(P, H=1, n=65536), _shape(P, H=1, n=32768), _shape(P, H=12, n=32760), _shape(P, H=2, n=1024, d=64),
+              _shape(P, H=4, n=4140, group=64), _shape(P, H=1, n=1400, group=1000), _shape(P, H=1, n=15000, kv_slices=0),
+              _shape(P, H=1, n=16384, kv_slices=8), _shape(P, H=1, n=20480, group=16, kv_slices=8)]
+    for _ in range(60):
+        shapes.append(_shape(P, B=rng.choice([1, 1, 2]), H=rng.randint(1, 40), n=int(2 ** rng.uniform(6, 17)), d=rng.choice([64, 128]),
+                             block=rng.choice([64, 128]), group=rng.choice([0, 1, 2, 8, 16, 32, 32, 64, 96, 5000])))
+    return shapes
+
+
+def test_workspaces_of_the_plain_size_are_accepted(P):
+    """room beyond the plain size (sums of small units) is an offer: a workspace without it, sized once for other shapes or by an
+    earlier call, is taken by every entry point, and what the size query gives is never less"""
+    L = P.load_library()
+    fake, odd, out = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1004), ctypes.c_void_p(0x2000)
+    EINVAL, EWORKSPACE, EALIGN = -1, -3, -4
+    for s in _workspace_shapes(P):
+        c, need = s.c(), _attn_bytes(s)
+        assert P.attn_workspace_bytes(s) >= need, s
+        for nbytes, expect in ((need, EINVAL), (need - 1, EWORKSPACE)):  # (a null pointer is reported after the size)
+            assert L.pasa_kv_stats(None, fake, ctypes.byref(c), fake, nbytes, None) == expect, s
+            assert L.pasa_key_prior(None, fake, ctypes.byref(c), 1e-6, fake, fake, nbytes, None) == expect, s
+            assert L.pasa_sparse_attn_fwd(None, fake, fake, ctypes.byref(c), fake, fake, 1, out, None, fake, nbytes, None) == expect, s
+            assert L.pasa_sparse_attn_fwd_prepared(None, fake, fake, ctypes.byref(c), fake, fake, 1, out, None, fake, nbytes, None) == expect, s
+        plain = _forward_bytes(P, s, 0.15)
+        assert L.pasa_forward_workspace_bytes(ctypes.byref(c), 0.15) >= plain
+        for nbytes, expect in ((plain, EALIGN), (plain - 1, EWORKSPACE)):  # (a misaligned key pointer is reported after the size)
+            assert L.pasa_forward(fake, odd, fake, ctypes.byref(c), 0.15, 1, 0.1, out, None, fake, nbytes, None) == expect, s
+
+
+def test_a_workspace_for_the_longest_clip_does_for_shorter_ones(P):
+    L = P.load_library()
+    fake, odd, out = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1004), ctypes.c_void_p(0x2000)
+    longer, shorter = _shape(P, H=1, n=32896), _shape(P, H=1, n=32768)
+    size = L.pasa_forward_workspace_bytes(ctypes.byref(longer.c()), 0.15)
+    assert L.pasa_forward(fake, odd, fake, ctypes.byref(shorter.c()), 0.15, 1, 0.1, out, None, fake, size, None) == -4  # past the size check
+    longer, shorter = _shape(P, H=1, n=65536), _shape(P, H=1, n=64000)
+    assert L.pasa_kv_stats(None, fake, ctypes.byref(shorter.c()), fake, P.attn_workspace_bytes(longer), None) == -1
+
+
+def test_static_scratch_takes_every_shape_of_at_most_its_size(P):
+    """room for small units never keeps a shape from the static scratch"""
+    for s in _workspace_shapes(P):
+        if s.kv_slices <= 1:
+            assert (_attn_bytes(s) <= P.STATIC_SCRATCH_BYTES) == (P.attn_workspace_bytes(s) <= P.STATIC_SCRATCH_BYTES), s
+
+
 def test_binding_raises_a_clear_error_when_the_library_is_missing(P, monkeypatch):
     import paper_2604_12219_amd.pasa as mod
     monkeypatch.setattr(mod, "_lib", None)

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import workloads
-from _util import assert_close, to_f64
+from _util import assert_close, attn_required_bytes, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -172,6 +172,28 @@ def test_statistics_of_small_problems(P, n, heads, d, block, group):
     assert np.all(got[alone] < np.log(1e-2))
     res = oracle.pasa_attention(to_f64(q), to_f64(k), to_f64(v), idx.cpu().numpy(), block, group=group)
     assert_close(to_f64(out), res, what="attention with the statistics of a small problem")
+
+
+@pytest.mark.parametrize("n,heads,d,block,group", [(64 * 129 - 3, 1, 128, 64, 64), (64 * 90, 3, 64, 64, 32), (64 * 21 + 1, 1, 128, 64, 1000),
+                                                   (64 * 300, 4, 128, 64, 96), (128 * 5, 2, 64, 128, 4)])
+def test_statistics_without_room_for_small_units(P, n, heads, d, block, group):
+    """the smallest workspace that is accepted: the statistics take the units that it has room for, nothing behind it is touched, and
+    statistics made with the room are read by calls that are told of the smaller size (and the other way round)"""
+    q, k, v = _inputs((1, 1, n), heads, d, seed=n)
+    shape = P.Shape.of(q, block=block, group=group)
+    full, least = P.attn_workspace_bytes(shape), attn_required_bytes(P, shape)
+    whole = [torch.full((full + 4096,), 0xFF, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    idx, mask = P.route(P.block_score(q, k, shape), 1, 3, 0.2)
+    P.kv_stats(k, v, shape, ws=whole[0][:least])
+    assert bool((whole[0][least:] == 0xFF).all())
+    P.kv_stats(k, v, shape, ws=whole[1][:full])
+    want = oracle.key_prior(to_f64(k), to_f64(v), block, group, eps=1e-6)
+    alone = want < np.log(1e-5)  # a block that is its own group: the norm is rounding noise
+    res = oracle.pasa_attention(to_f64(q), to_f64(k), to_f64(v), idx.cpu().numpy(), block, group=group)
+    for w, size in ((whole[0], full), (whole[0], least), (whole[1], full), (whole[1], least)):
+        beta = P.key_prior(k, v, shape, w[:size]).cpu().numpy()
+        np.testing.assert_allclose(beta[~alone], want[~alone], atol=2e-3, rtol=0)
+        assert_close(to_f64(P.sparse_attn_fwd(q, k, v, shape, idx, mask, ws=w[:size], prepared=True)), res, what=f"{size} bytes")
 
 
 @pytest.mark.parametrize("n,heads,d,block,group", [(64 * 110 - 39, 40, 64, 64, 32),     # units of 16, the prior's of 8
