@@ -268,8 +268,6 @@ struct BitWalk {
   uint64_t nz;      // lanes of the window whose word still has to be visited
   uint32_t cur;     // bits of the current word that are still to be yielded
   int wi;           // index of the current word
-  int own_w;        // blocks yielded ahead of the ascending order: word (-1: none)
-  uint32_t own_bits;  // and bits
   PASA_DEVICE void load_window(int lane) {
     const int i = win + lane;
     uint32_t a = 0u, b = 0u;
@@ -277,21 +275,20 @@ struct BitWalk {
       a = ra[i];
       if constexpr (MODE != 3) b = rb[i];
     }
-    combine(a, b, lane);
+    combine(a, b);
   }
-  PASA_DEVICE void combine(uint32_t a, uint32_t b, int lane) {
+  PASA_DEVICE void combine(uint32_t a, uint32_t b) {
     words = MODE == 3 ? a : MODE == 0 ? (a & b) : MODE == 1 ? (a & ~b) : (b & ~a);
-    if (win + lane == own_w) words &= ~own_bits;
     nz = __builtin_amdgcn_ballot_w64(words != 0u);
   }
   // first_a, first_b: word (w0 + lane) of the two rows, zero at and beyond w1 (fetched once by the caller for all
-  // the walks over the same rows).  head_bits of word head_w: blocks to be yielded first; they have to be in the combination.
-  PASA_DEVICE void init(const_u32* a, const_u32* b, int w0, int w1, uint32_t first_a, uint32_t first_b, int lane, int head_w = -1,
+  // the walks over the same rows).  head_bits of word head_w: blocks to be yielded first, which the caller has taken out of
+  // first_a (so the word is one of these 64).
+  PASA_DEVICE void init(const_u32* a, const_u32* b, int w0, int w1, uint32_t first_a, uint32_t first_b, int head_w = 0,
                         uint32_t head_bits = 0u) {
     ra = a; rb = b; w_lo = w0; w_end = w1;
-    own_w = head_w; own_bits = head_bits;
     win = w0; cur = head_bits; wi = head_w;
-    combine(first_a, first_b, lane);
+    combine(first_a, first_b);
   }
   PASA_DEVICE int next(int lane) {  // kNoBlock when exhausted (and on every later call)
     if (cur == 0u) {
@@ -450,20 +447,26 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   }
   // The key blocks at the workgroup's own tokens (those that are selected and whole) come first: tokens of a video attend most
   // to their neighbourhood, so the running maximum is near its final value from the start and the accumulators are rescaled
-  // less often (a rescale is 64 multiplications and an exchange; all of them together are 3 % of the launch).  Ascending order
-  // throughout / own blocks first, us a call: 12 heads of 32,760 tokens, a fifth of the blocks 1817 / 1801; 5 heads of 75,600
-  // 3147 / 3094; 40 heads of 147,600, blocks of 128 33,650 / 33,010; 3 heads of 118,800 and 40 of 75,600 the same.  The dense path
-  // gains nothing by it (22 tiles in one head: 16.2 / 16.7) and stays ascending.
-  int own_w = -1;
+  // less often (a rescale is 64 multiplications and an exchange; all of them together are 3 % of the launch).  On the other hand
+  // the workgroups of an XCD no longer set out together: with two 64-token blocks per workgroup and more keys than the
+  // L2s hold, 4 % more tile reads miss (40 heads of 75,600 tokens, 15 % of the blocks: 174 -> 181 GB), which costs more than it
+  // gives where the fabric is what bounds the launch.  So two-block workgroups do it while K and V of a head fit the eight L2s
+  // (32 MB).  Ascending throughout / own blocks first, us, on boxes with a high and a low clock: d = 128, blocks of 64: 12 heads of 32,760
+  // tokens 1686 / 1664, 1784 / 1766; 40 of 32,760 5666 / 5575, 5955 / 5800; 40 of 61,200 16,080 / 15,980; 40 of 75,600
+  // 24,911 / 25,390, 26,882 / 26,360; 3 of 118,800 4979 / 5002, 5017 / 4991.  Blocks of 128: 40 of 147,600 33,182 / 32,739,
+  // 35,038 / 34,172; 40 of 32,760 4863 / 4632.  The dense path gains nothing by it (22 tiles in one head: 16.2 / 16.7).
+  int own_w = 0;
   uint32_t own_sel = 0u;
   if constexpr (SPARSE) {
+    const bool own_first = MODE == 1 || (int64_t)n * (4 * D) <= (32 << 20);
     const int w = qb_a >> 5;
-    const uint32_t whole = MODE == 2 ? ((qb_a + 2) * 64 <= n ? 3u : (qb_a + 1) * 64 <= n ? 1u : 0u) : ((qb_a + 1) * 128 <= n ? 1u : 0u);
-    if (w >= c_lo && w < c_hi) {
+    if (own_first && w >= c_lo && w < min(c_hi, c_lo + 64)) {
+      const uint32_t whole = MODE == 2 ? ((qb_a + 2) * 64 <= n ? 3u : (qb_a + 1) * 64 <= n ? 1u : 0u) : ((qb_a + 1) * 128 <= n ? 1u : 0u);
       own_w = w;
       own_sel = (uint32_t)__builtin_amdgcn_readfirstlane((int)(mask_a[w] & mask_b[w] & (whole << (qb_a & 31))));
     }
   }
+
   // Tile requests.  The tile for key rows [r0, r0 + 64) is fetched from row tile_row(r0) on: shifted
   // back where it would reach beyond the last token, so that all 64 rows exist (r0 may even lie beyond
   // n: the second tile of the last 128-token block).  The consumer ignores the rows before r0.  Every
@@ -484,7 +487,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
     BitWalk<MODE == 2 ? 0 : 3> walk;
     int blk = kNoBlock, sub = 0, dense_next = 0, dense_end = n_dense_tiles;
     if constexpr (SPARSE) {
-      walk.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b, lane, own_w, own_sel);
+      walk.init(mask_a, mask_b, c_lo, c_hi, c_lo + lane == own_w ? first_a & ~own_sel : first_a, first_b, own_w, own_sel);
       blk = walk.next(lane);
     } else if constexpr (TEAMS == 2) {  // the first half of the tiles (rounded down) and the rest
       if (team == 0) dense_end = n_dense_tiles / 2;
@@ -511,8 +514,8 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
     if (r_cur >= 0) { request(kb, r_cur, 0); request(vb, r_cur, 1); }
     settle_q();
     int pair = 0;
-    // Tiles whose 64 rows are all keys of the tile: one instruction stream per tile.  (Tiles come in ascending
-    // order, so a tile that reaches beyond the last token can only be among the last ones.)
+    // Tiles whose 64 rows are all keys of the tile: one instruction stream per tile.  (The blocks that come first are
+    // whole and the others ascend, so a tile that reaches beyond the last token can only be among the last ones.)
 #pragma unroll 1
     while (r_cur >= 0 && r_cur + 64 <= n) {
       ring_barrier<NI>(0);  // the pair has landed; every wave is done with the previous pair
@@ -554,8 +557,8 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   if constexpr (MODE == 2) {
     BitWalk<1> only_a;
     BitWalk<2> only_b;
-    only_a.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b, lane);
-    only_b.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b, lane);
+    only_a.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b);
+    only_b.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b);
     int a_blk = only_a.next(lane), b_blk = only_b.next(lane);
     if (a_blk != kNoBlock || b_blk != kNoBlock) {
       ring_barrier<NI>(0);  // every wave is done with the ring
