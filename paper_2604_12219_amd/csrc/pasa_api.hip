@@ -85,16 +85,22 @@ int slot_unit(int64_t bh, int nb, int group) {
 }
 
 // Blocks summed by one workgroup of the statistics kernel: a whole group, at most 32 blocks, or half of that, a quarter, ...
-// (which divides the group, unless the group is the whole sequence).  512 workgroups run at a time, so the sweep takes as many
-// rounds as there are 512 units, each as long as a unit and the writing and averaging of its sum, which is worth about 6 blocks.
-// kv_stats_kernel + hg_finish_kernel, us, units of 32 / 16 / 8 / 4: 12 heads of 512 blocks 73 / 58 / 65 / 81; 5 of 1182 72 / 58 / 65 / 79;
-// 3 of 1857 in groups of 64 75 / 54 / 61 / 74.
+// (which divides the group, unless the group is the whole sequence).  512 workgroups run at a time at d = 128, at d = 64 768
+// before the memory is what counts (registers would allow 1024); so the sweep takes as many rounds as there are 512 or 768 units, each as
+// long as a unit and the writing of its sum, which is worth about 6 blocks.  Units smaller than the group cost a launch that
+// puts them together, about 8 blocks.  kv_stats_kernel + hg_finish_kernel, us, units of 32 / 16 / 8 / 4:
+//   d = 128: 12 heads of 512 blocks 73 / 58 / 65 / 81; 5 of 1182 72 / 58 / 65 / 79; 3 of 1857 in groups of 64 75 / 54 / 61 / 74;
+//     14 of 1182 190 / 181 / 193; 20 of 256 72 / 56 / 60; 16 of 513 97 / 76 / 91 (the rule's 32 is not the best there: 528 units
+//     of 16 are hardly a second round)
+//   d = 64: 12 of 512 38 / 27 / 25 / 29; in groups of 16 - / 25 / 26; 16 of 513 44 / 37 / 34; 24 of 512 46 / 41 / 46;
+//     32 of 512 54 / 56 / 64; 20 of 1182 91 / 101 / 103
 // Below 8 blocks the unit sums are more bytes than the keys and values they come from; that pays only where even units of 8
 // leave most compute units without one and the kernel's time is that of one workgroup's serial sweep: 65 blocks x 4 heads
 // take 22.9 us with units of 8 and 15.1 us with units of 2.  Units below slot_unit need room_bytes behind the required part.
 int stats_unit(int64_t bh, int nb, int group, int d, size_t room_bytes) {
   auto units = [&](int unit) { return bh * units_of(nb, unit); };
-  auto cost = [&](int unit) { return (units(unit) + 511) / 512 * (unit + 6); };
+  const int round = d == 128 ? 512 : 768;
+  auto cost = [&](int unit) { return (units(unit) + round - 1) / round * (unit + 6) + (unit < group ? 8 : 0); };
   int best = group < 32 ? group : 32;
   for (int unit = best / 2; unit >= 8 && units(2 * unit) < 1024; unit /= 2)  // (with 1024 units the sums are many already)
     if (cost(unit) < cost(best)) best = unit;
