@@ -1,6 +1,4 @@
 """Helpers shared by the GPU parity tests."""
-import ctypes
-
 import numpy as np
 import torch
 
@@ -33,14 +31,27 @@ def assert_close(got, ref, rows=None, what=""):
         assert mx <= MAX_REL and mean <= MEAN_REL, f"{what}: head {h}: max_rel={mx:.3e} mean_rel={mean:.3e}"
 
 
-def attn_required_bytes(P, shape):
-    """the smallest attention workspace the entry points take for the shape (host-only calls with a null pointer: too small a
-    workspace is reported before it)"""
-    L, c = P.load_library(), shape.c()
-    lo, hi = 0, P.attn_workspace_bytes(shape)
-    while lo < hi:
-        mid = (lo + hi) // 2
-        rc = L.pasa_kv_stats(None, None, ctypes.byref(c), ctypes.c_void_p(0x1000), mid, None)
-        assert rc in (-1, -3)
-        lo, hi = (mid + 1, hi) if rc == -3 else (lo, mid)
-    return lo
+
+def align256(x):
+    return (x + 255) // 256 * 256
+
+
+def attn_layout(s):
+    """(bytes, offset of the slots for unit sums, slots per head) of the attention workspace that every entry point takes for a
+    shape: the slices' results, a bitmap, the statistics tiles, the group matrices, the sums of units of at most 32 blocks
+    (halved, down to 8, while that leaves fewer than 1024 of them), key means"""
+    bh, nb = s.B * s.H, -(-s.n // s.block)
+    chunks, total, partial, slots = -(-nb // 32), 0, 0, 0
+    if s.kv_slices > 1:
+        total += align256(bh * s.kv_slices * s.n * s.d * 4)
+        total = align256(total + bh * s.kv_slices * s.n * 8) + 256
+    total += align256(bh * nb * chunks * 4)
+    if s.group > 0:
+        group = min(s.group, nb)
+        unit = min(group, 32)
+        while unit > 8 and bh * -(-nb // unit) < 1024:
+            unit //= 2
+        slots = -(-nb // unit)
+        partial = total + align256(bh * chunks * 64 * s.d * 2) + align256(bh * -(-nb // group) * s.d * s.d * 2)
+        total = partial + align256(bh * slots * s.d * s.d * 4) + align256(bh * nb * s.d * 4)
+    return total, partial, slots

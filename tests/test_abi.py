@@ -8,6 +8,7 @@ import re
 import pytest
 
 import oracle
+from _util import align256, attn_layout
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "pasa.h")
@@ -177,33 +178,10 @@ def test_argument_validation_returns_before_any_launch(P):
         assert isinstance(L.pasa_strerror(code), bytes) and len(L.pasa_strerror(code)) > 0
 
 
-def _align(x):
-    return (x + 255) // 256 * 256
-
-
-def _attn_bytes(s):
-    """what the attention entry points have to be satisfied with: the slices' results, a bitmap, the statistics tiles, the group
-    matrices, the sums of units of at most 32 blocks (halved, down to 8, while that leaves fewer than 1024 of them), key means"""
-    bh, nb = s.B * s.H, -(-s.n // s.block)
-    chunks, total = -(-nb // 32), 0
-    if s.kv_slices > 1:
-        total += _align(bh * s.kv_slices * s.n * s.d * 4)
-        total = _align(total + bh * s.kv_slices * s.n * 8) + 256
-    total += _align(bh * nb * chunks * 4)
-    if s.group > 0:
-        group = min(s.group, nb)
-        unit = min(group, 32)
-        while unit > 8 and bh * -(-nb // unit) < 1024:
-            unit //= 2
-        total += _align(bh * chunks * 64 * s.d * 2) + _align(bh * -(-nb // group) * s.d * s.d * 2)
-        total += _align(bh * -(-nb // unit) * s.d * s.d * 4) + _align(bh * nb * s.d * 4)
-    return total
-
-
 def _forward_bytes(P, s, keep):
     bh, nb = s.B * s.H, P.num_blocks(s)
-    return (_align(bh * nb * nb * 4) + _align(bh * nb * P.topk_count(nb, keep) * 4) + _align(bh * nb * -(-nb // 32) * 4) +
-            _align(P.score_workspace_bytes(s)) + _attn_bytes(s))
+    return (align256(bh * nb * nb * 4) + align256(bh * nb * P.topk_count(nb, keep) * 4) + align256(bh * nb * -(-nb // 32) * 4) +
+            align256(P.score_workspace_bytes(s)) + attn_layout(s)[0])
 
 
 def _workspace_shapes(P):
@@ -225,7 +203,7 @@ def test_workspaces_of_the_plain_size_are_accepted(P):
     fake, odd, out = ctypes.c_void_p(0x1000), ctypes.c_void_p(0x1004), ctypes.c_void_p(0x2000)
     EINVAL, EWORKSPACE, EALIGN = -1, -3, -4
     for s in _workspace_shapes(P):
-        c, need = s.c(), _attn_bytes(s)
+        c, need = s.c(), attn_layout(s)[0]
         assert P.attn_workspace_bytes(s) >= need, s
         for nbytes, expect in ((need, EINVAL), (need - 1, EWORKSPACE)):  # (a null pointer is reported after the size)
             assert L.pasa_kv_stats(None, fake, ctypes.byref(c), fake, nbytes, None) == expect, s
@@ -252,7 +230,7 @@ def test_static_scratch_takes_every_shape_of_at_most_its_size(P):
     """room for small units never keeps a shape from the static scratch"""
     for s in _workspace_shapes(P):
         if s.kv_slices <= 1:
-            assert (_attn_bytes(s) <= P.STATIC_SCRATCH_BYTES) == (P.attn_workspace_bytes(s) <= P.STATIC_SCRATCH_BYTES), s
+            assert (attn_layout(s)[0] <= P.STATIC_SCRATCH_BYTES) == (P.attn_workspace_bytes(s) <= P.STATIC_SCRATCH_BYTES), s
 
 
 def test_binding_raises_a_clear_error_when_the_library_is_missing(P, monkeypatch):

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import workloads
-from _util import assert_close, attn_required_bytes, to_f64
+from _util import assert_close, attn_layout, to_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -181,7 +181,7 @@ def test_statistics_without_room_for_small_units(P, n, heads, d, block, group):
     statistics made with the room are read by calls that are told of the smaller size (and the other way round)"""
     q, k, v = _inputs((1, 1, n), heads, d, seed=n)
     shape = P.Shape.of(q, block=block, group=group)
-    full, least = P.attn_workspace_bytes(shape), attn_required_bytes(P, shape)
+    full, least = P.attn_workspace_bytes(shape), attn_layout(shape)[0]
     whole = [torch.full((full + 4096,), 0xFF, dtype=torch.uint8, device="cuda") for _ in range(2)]
     idx, mask = P.route(P.block_score(q, k, shape), 1, 3, 0.2)
     P.kv_stats(k, v, shape, ws=whole[0][:least])
@@ -196,17 +196,20 @@ def test_statistics_without_room_for_small_units(P, n, heads, d, block, group):
         assert_close(to_f64(P.sparse_attn_fwd(q, k, v, shape, idx, mask, ws=w[:size], prepared=True)), res, what=f"{size} bytes")
 
 
-@pytest.mark.parametrize("n,heads,d,block,group", [(64 * 110 - 39, 40, 64, 64, 32),     # units of 16, the prior's of 8
-                                                   (64 * 110, 40, 128, 64, 64),         # the same, four units to a group
-                                                   (128 * 52 + 5, 20, 64, 128, 1000),   # one group of 53 blocks
-                                                   (64 * 110, 40, 64, 64, 16)])         # a unit is a group, the prior's half of one
-def test_statistics_in_larger_units_than_the_prior_takes(P, n, heads, d, block, group):
+@pytest.mark.parametrize("n,heads,d,block,group,unit", [(64 * 110 - 39, 60, 64, 64, 32, 16),  # (the prior's kernel takes 8 blocks in all of these)
+                                                        (64 * 110, 40, 128, 64, 64, 16),      # the same, four units to a group
+                                                        (128 * 52 + 5, 116, 64, 128, 1000, 16),  # one group of 53 blocks
+                                                        (64 * 110, 40, 64, 64, 16, 16)])       # a unit is a group, the prior's half of one
+def test_statistics_in_larger_units_than_the_prior_takes(P, n, heads, d, block, group, unit):
     """more units of 8 than run at a time: the statistics take larger ones, the prior's kernel its own.  First and last head against
     the oracle, tolerances as above"""
     gen = torch.Generator(device="cuda").manual_seed(n)  # (a smooth field along one axis of this length is slow to make)
     q, k, v = (torch.randn((1, heads, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
     shape = P.Shape.of(q, block=block, group=group)
     ws = P.kv_stats(k, v, shape, ws=torch.full((P.attn_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda"))
+    _, at, slots = attn_layout(shape)  # one slot for every unit of 8 blocks: those of larger units stay as they were
+    sums = ws[at:at + heads * slots * d * d * 4].view(torch.int32).view(heads, slots, d * d)
+    assert slots == -(-P.num_blocks(shape) // 8) and int((sums != -1).any(-1).sum()) == heads * -(-P.num_blocks(shape) // unit)
     beta = P.key_prior(k, v, shape, ws)
     idx, mask = P.route(P.block_score(q, k, shape), 1, 3, 0.2)
     out = P.sparse_attn_fwd(q, k, v, shape, idx, mask, ws=ws, prepared=True)
