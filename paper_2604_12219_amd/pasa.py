@@ -148,6 +148,15 @@ def _check_extent(shape: "Shape", **tensors):
             raise ValueError(f"{name}: the shape's strides reach element {last} of a storage that holds {room} from the tensor's start")
 
 
+def _check_strides(shape: "Shape", **tensors):
+    """[B, H, n, d] tensors that the kernels address with the strides of `shape` have to have them (where a dimension has one
+    entry its stride does not matter)"""
+    want = (shape.stride_b, shape.stride_h, shape.stride_n, 1)
+    for name, t in tensors.items():
+        if t.stride() != want and any(size > 1 and a != b for size, a, b in zip(t.shape, t.stride(), want)):
+            raise ValueError(f"{name}: strides {t.stride()}, the kernels would use those of q, {want}")
+
+
 def _stream():
     """the current stream of the current device as an integer (the handle alone, without a torch.cuda.Stream around it)"""
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
@@ -338,7 +347,8 @@ def forward(q, k, v, keep_ratio: float, seed: int, noise_amp: float, block: int 
             scale: float = 0.0, buffers: dict | None = None):
     """The whole hot path: score -> route -> statistics + piecewise attention. Returns (out, idx).
 
-    ``buffers`` (optional dict) caches every intermediate and workspace between calls.
+    q, k and v have the same strides, and out has them too.
+    ``buffers`` (optional dict) caches every intermediate and workspace between calls of the same shape and layout.
     """
     shape = Shape.of(q, block=block, group=group, scale=scale)
     L = load_library()
@@ -346,7 +356,7 @@ def forward(q, k, v, keep_ratio: float, seed: int, noise_amp: float, block: int 
     nb = _num_blocks(c)
     k_sel = topk_count(nb, keep_ratio)
     b = buffers if buffers is not None else {}
-    key = (tuple(q.shape), block, group, k_sel)
+    key = (q.shape, q.stride(), q.device, block, group, k_sel)  # (out has the strides of q)
     if b.get("key") != key:
         b.clear()
         b["key"] = key
@@ -359,6 +369,7 @@ def forward(q, k, v, keep_ratio: float, seed: int, noise_amp: float, block: int 
     # block_score, route and sparse_attn_fwd with the marshalling of the three done once: at 1024 tokens the six launches take
     # the device 27 us, and a call was bound by 40 us of host work (23 now)
     _check_extent(shape, q=q, k=k, v=v, out=b["out"])
+    _check_strides(shape, k=k, v=v, out=b["out"])
     stream, qp, kp, scores, idx, mask = _stream(), _ptr(q), _ptr(k), _ptr(b["scores"]), _ptr(b["idx"]), _ptr(b["mask"])
     _check(L.pasa_block_score(qp, kp, c, None, scores, _ptr(b["ws_score"]), b["ws_score"].numel(), stream), "pasa_block_score")
     _check(L.pasa_route(scores, shape.B * shape.H, nb, k_sel, seed & (2**64 - 1), noise_amp, idx, mask, stream), "pasa_route")

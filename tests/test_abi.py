@@ -294,6 +294,20 @@ def test_binding_checks_that_the_strides_stay_inside_the_tensors():
         mod._check_extent(shape, q=q.float())
 
 
+def test_forward_refuses_keys_and_values_of_another_layout_than_the_queries(P):
+    """the kernels read K and V with the strides of Q: another layout would be misread without an error"""
+    import torch
+    q, k, v = (torch.zeros((1, 2, 128, 64), dtype=torch.bfloat16) for _ in range(3))
+    other = torch.zeros((1, 128, 2, 64), dtype=torch.bfloat16).permute(0, 2, 1, 3)
+    with pytest.raises(ValueError, match="k: strides"):
+        P.forward(q, other, v, 0.5, 1, 0.1)
+    with pytest.raises(ValueError, match="v: strides"):
+        P.forward(q, k, other, 0.5, 1, 0.1)
+    from paper_2604_12219_amd.pasa import _check_strides
+    one = torch.zeros((1, 1, 128, 64), dtype=torch.bfloat16)  # a batch of one head: only the token stride counts
+    _check_strides(P.Shape.of(one), k=one.as_strided((1, 1, 128, 64), (7, 9, 64, 1)))
+
+
 def test_header_is_plain_c(tmp_path):
     """include/pasa.h compiles as C99 with no HIP header in sight, and a C program links against the library by name"""
     import subprocess

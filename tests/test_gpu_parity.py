@@ -530,6 +530,20 @@ def test_forward_convenience_wrapper(P):
     assert_close(to_f64(out), ref, what="forward()")
 
 
+def test_forward_buffers_are_not_shared_between_layouts(P):
+    """one buffers dict, the same shape head-major and token-major"""
+    q, k, v = _inputs((4, 16, 16), 2, 64)
+    want, want_idx = P.forward(q, k, v, keep_ratio=0.25, seed=5, noise_amp=0.2)
+    want = want.clone()
+    buffers = {}
+    for layout in ("heads", "tokens", "heads"):
+        x = (q, k, v) if layout == "heads" else tuple(t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for t in (q, k, v))
+        out, idx = P.forward(*x, keep_ratio=0.25, seed=5, noise_amp=0.2, buffers=buffers)
+        torch.cuda.synchronize()
+        assert out.stride() == x[0].stride()
+        assert torch.equal(out, want) and torch.equal(idx, want_idx), layout
+
+
 # ------------------------------------------------------------------------------------------------
 # calibration signal of the curvature-aware budget: mean L1 distance of two tensors
 # ------------------------------------------------------------------------------------------------
