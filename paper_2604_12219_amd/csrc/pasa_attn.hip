@@ -450,15 +450,17 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   // less often (a rescale is 64 multiplications and an exchange; all of them together are 3 % of the launch).  On the other hand
   // the workgroups of an XCD no longer set out together: with two 64-token blocks per workgroup and more keys than the
   // L2s hold, 4 % more tile reads miss (40 heads of 75,600 tokens, 15 % of the blocks: 174 -> 181 GB), which costs more than it
-  // gives where the fabric is what bounds the launch.  So two-block workgroups do it while K and V of a head fit the eight L2s
-  // (32 MB).  Ascending throughout / own blocks first, us, on boxes with a high and a low clock: d = 128, blocks of 64: 12 heads of 32,760
-  // tokens 1686 / 1664, 1784 / 1766; 40 of 32,760 5666 / 5575, 5955 / 5800; 40 of 61,200 16,080 / 15,980; 40 of 75,600
-  // 24,911 / 25,390, 26,882 / 26,360; 3 of 118,800 4979 / 5002, 5017 / 4991.  Blocks of 128: 40 of 147,600 33,182 / 32,739,
-  // 35,038 / 34,172; 40 of 32,760 4863 / 4632.  The dense path gains nothing by it (22 tiles in one head: 16.2 / 16.7).
+  // gives where memory is what bounds the launch.  So two-block workgroups do it while K and V of a head fit the eight L2s
+  // (32 MB) or those of all heads the memory-side cache (256 MB).  Ascending throughout / own blocks first, us, on boxes with a
+  // high and a low clock: d = 128, blocks of 64: 12 heads of 32,760 tokens 1686 / 1664, 1784 / 1766; 40 of 32,760 5666 / 5575, 5955 / 5800;
+  // 5 of 75,600 (the whole call, routing with the prior) 3175 / 3121; 3 of 118,800 4979 / 5002, 5017 / 4991; 10 of 75,600 6464 / 6452,
+  // 6837 / 6822; 20 of 75,600 12,521 / 12,665, 13,490 / 13,319; 40 of 75,600 24,911 / 25,390, 26,882 / 26,360.  Blocks of 128: 40 of 147,600
+  // 33,182 / 32,739, 35,038 / 34,172; 40 of 32,760 4863 / 4632.  The dense path gains nothing by it (22 tiles in one head: 16.2 / 16.7).
   int own_w = 0;
   uint32_t own_sel = 0u;
   if constexpr (SPARSE) {
-    const bool own_first = MODE == 1 || (int64_t)n * (4 * D) <= (32 << 20);
+    const int64_t kv_bytes = (int64_t)n * (4 * D);  // of a head
+    const bool own_first = MODE == 1 || kv_bytes <= (32 << 20) || kv_bytes * p.bh <= (256 << 20);
     const int w = qb_a >> 5;
     if (own_first && w >= c_lo && w < min(c_hi, c_lo + 64)) {
       const uint32_t whole = MODE == 2 ? ((qb_a + 2) * 64 <= n ? 3u : (qb_a + 1) * 64 <= n ? 1u : 0u) : ((qb_a + 1) * 128 <= n ? 1u : 0u);

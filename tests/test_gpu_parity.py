@@ -432,27 +432,30 @@ def test_blocks_visited_first_are_visited_once(P, n, d, block, kv_slices, keep_o
     np.testing.assert_allclose(lse.cpu().numpy(), res["lse"], atol=2e-2)
 
 
-@pytest.mark.parametrize("n,d,block", [(65536, 128, 64), (65537, 128, 64), (131072, 64, 64), (128 * 2049 + 77, 64, 128)])
-def test_blocks_visited_first_at_the_ends_of_the_rule(P, n, d, block):
-    """keys of 32 MB a head and just above; own blocks in the last word of the walk's first 64 words and beyond it"""
+@pytest.mark.parametrize("n,heads,d,block", [(65536, 9, 128, 64), (65537, 7, 128, 64), (65537, 8, 128, 64), (131072, 1, 64, 64),
+                                              (128 * 2049 + 77, 1, 64, 128)])
+def test_blocks_visited_first_at_the_ends_of_the_rule(P, n, heads, d, block):
+    """keys and values of 32 MB a head and just above, of 256 MB in all and just above; own blocks in the last word of the walk's
+    first 64 words and beyond it.  First and last head"""
     gen = torch.Generator(device="cuda").manual_seed(n)  # (a smooth field along one axis of this length is slow to make)
-    q, k, v = (torch.randn((1, 1, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    q, k, v = (torch.randn((1, heads, n, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
     shape = P.Shape.of(q, block=block, group=32)
     nb = P.num_blocks(shape)
     rng = np.random.default_rng(n)
-    idx = np.empty((1, nb, 7), np.int32)
-    for i in range(nb):  # the workgroup's own pair (or the block alone, and another one, at an odd end) and random others
+    idx = np.empty((heads, nb, 7), np.int32)
+    for i in range(nb):  # the workgroup's own pair (or the block alone at an odd end) and random others, the same in every head
         own = {i - i % 2, min(i - i % 2 + 1, nb - 1)}
         others = [j for j in rng.choice(nb, 9, replace=False) if j not in own]
-        idx[0, i] = sorted(own) + others[:7 - len(own)]
-        idx[0, i].sort()
+        idx[:, i] = np.sort(np.array(sorted(own) + others[:7 - len(own)], np.int32))
     out, lse = P.sparse_attn_fwd(q, k, v, shape, torch.from_numpy(idx).cuda(), None, want_lse=True)
     torch.cuda.synchronize()
     blocks = sorted({0, 1, nb // 2, nb // 2 + 1, nb - 3, nb - 2, nb - 1})
-    res = oracle.pasa_attention(to_f64(q), to_f64(k), to_f64(v), idx, block, group=32, q_blocks=blocks, return_all=True)
     rows = np.concatenate([np.arange(j * block, min((j + 1) * block, n)) for j in blocks])
-    assert_close(to_f64(out), res["o"], rows=rows, what=f"{n} d={d} b={block}")
-    np.testing.assert_allclose(lse[0].cpu().numpy()[rows], res["lse"][0, rows], atol=2e-2)
+    for h in {0, heads - 1}:
+        qh, kh, vh = (to_f64(t[:, h:h + 1]) for t in (q, k, v))
+        res = oracle.pasa_attention(qh, kh, vh, idx[h:h + 1], block, group=32, q_blocks=blocks, return_all=True)
+        assert_close(to_f64(out[:, h:h + 1]), res["o"], rows=rows, what=f"{n} d={d} b={block} head {h}")
+        np.testing.assert_allclose(lse[h].cpu().numpy()[rows], res["lse"][0, rows], atol=2e-2)
 
 
 @pytest.mark.parametrize("n,heads,batch,d,block,group", [(63, 1, 1, 64, 64, 32), (1345, 3, 1, 128, 64, 32), (1345, 2, 2, 64, 64, 1),
