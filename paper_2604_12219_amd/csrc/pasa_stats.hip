@@ -155,7 +155,9 @@ __global__ void __launch_bounds__(256, 2) kv_stats_kernel(StatsParams p) {
       p.st[(((int64_t)bh * p.n_chunks + (j >> 5)) * 64 + (tid >= D ? 32 : 0) + (j & 31)) * D + col] = 0;
   }
 
-  float* out = p.partial + ((int64_t)bh * p.partial_head + (int64_t)(u / p.units_per_group) * p.partial_group + u % p.units_per_group) * D * D;
+  int slot = u;
+  if (p.partial_group != p.units_per_group) slot += u / p.units_per_group * (p.partial_group - p.units_per_group);
+  float* out = p.partial + ((int64_t)bh * p.partial_head + slot) * D * D;
 #pragma unroll
   for (int a = 0; a < TI; ++a)
 #pragma unroll
