@@ -308,6 +308,17 @@ def test_forward_refuses_keys_and_values_of_another_layout_than_the_queries(P):
     _check_strides(P.Shape.of(one), k=one.as_strided((1, 1, 128, 64), (7, 9, 64, 1)))
 
 
+def test_stream_handle_without_the_raw_getter(monkeypatch):
+    """a torch without the raw-handle getter: the handle of torch.cuda.current_stream()"""
+    import types
+
+    import torch
+    import paper_2604_12219_amd.pasa as binding
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream() == 77
+
+
 def test_header_is_plain_c(tmp_path):
     """include/pasa.h compiles as C99 with no HIP header in sight, and a C program links against the library by name"""
     import subprocess
