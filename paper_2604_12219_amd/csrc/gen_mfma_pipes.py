@@ -367,8 +367,10 @@ def flat(stream):
 #   Z = Kbar Q^T  (rows 0..31 of the statistics tile; the next tile of the stream is requested in the shadow)
 #   a_j = exp2(c z_j - m) for the unselected blocks, 0 for the selected ones; l += b sum a_j; A = sum a_j
 #   O += VS^T a   (rows 32..63), the first half of it while the second half of the a_j is still being computed
-# A selected block takes part in the running maximum: its mean-key logit cannot exceed the largest logit of
-# its keys, which the exact pass has already seen, so it never raises it.  Lane (x, h) holds block 8g + 4h + r
+# A selected block takes part in the running maximum, which is taken over the unmasked logits: its mean-key logit
+# exceeds the largest logit of its keys, which this workgroup's exact passes have seen, by the rounding of the mean
+# at most, so the maximum stays that of terms that are summed.  (Were the maximum masked, a selected block's a_j
+# could overflow before its mask is applied.)  Lane (x, h) holds block 8g + 4h + r
 # in register 4g + r, so with the bitmap word shifted right by 4h the block's bit is bit 8g + r for every lane.
 # Registers: Z v[168:183], per-element masks v[184:199], P^T v[200:207], the rest as in fused_step.
 def stats_step(D):

@@ -5,12 +5,12 @@
 //                                 blocks, laid out so the attention kernel streams it like a K tile)
 //   Hg_g   = mean_{j in group g} H_j,  H_j = sum_n (K_{j,n} - Kbar_j)^T V_{j,n} = K_j^T V_j - Kbar_j^T VS_j
 //
-// H_j is never written to memory.  A workgroup owns a "unit" of consecutive blocks (a whole group
-// when the group has at most 32 blocks, else 32 blocks of it), accumulates sum_j K_j^T V_j on the
+// H_j is never written to memory.  A workgroup owns a "unit" of consecutive blocks (a whole group or a
+// part of one, at most 32 blocks: stats_unit in pasa_api.hip), accumulates sum_j K_j^T V_j on the
 // matrix cores with fp32 accumulators (both operands are fetched from the row-major LDS tiles with
 // transposing LDS reads, the contraction runs over tokens), subtracts the rank-one term of every
-// block in fp32, and writes the unit's sum.  A second small kernel averages the units of a group,
-// applies the logit scale and stores the transposed matrix as bf16, row-major [value column][key
+// block in fp32, and writes the unit's sum.  Unless a unit is a whole group, a second small kernel
+// averages the units of a group, applies the logit scale and stores the transposed matrix as bf16, row-major [value column][key
 // column], which the attention kernel streams through LDS exactly like a K tile.
 #include "pasa_device.hpp"
 #include "pasa_kernels.hpp"
