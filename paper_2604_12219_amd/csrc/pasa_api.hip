@@ -360,10 +360,10 @@ static int kv_stats_impl(const void* k, const void* v, const pasa_shape_t* shape
   t.hg = reinterpret_cast<uint16_t*>(base + w.hg);
   t.group_sum = reinterpret_cast<float*>(base + w.partial);
   t.sum_head = w.n_slots; t.sum_group = w.slots_per_group;
-  if (t.unit >= w.slot_unit) {  // at most as many units as slots, in every group
-    t.partial = t.group_sum; t.partial_head = t.sum_head; t.partial_group = t.sum_group;
+  if (t.unit >= w.slot_unit) {  // a unit takes the slot of its first block
+    t.partial = t.group_sum; t.partial_head = t.sum_head; t.partial_step = t.unit / w.slot_unit;
   } else {
-    t.partial = reinterpret_cast<float*>(base + w.required); t.partial_head = t.n_units; t.partial_group = t.units_per_group;
+    t.partial = reinterpret_cast<float*>(base + w.required); t.partial_head = t.n_units; t.partial_step = 1;
   }
   t.kbar_split = reinterpret_cast<uint16_t*>(base + w.kbar);
   t.idx = idx; t.k_sel = k_sel; t.mask_words = (nb + 31) / 32;

@@ -49,8 +49,8 @@ struct StatsParams {
   float scale;
   int32_t n_chunks;  // ceil(nb / 32)
   uint16_t* st;      // out bf16 [BH][n_chunks][64][d] (see AttnParams::st)
-  float* partial;    // scratch fp32, slots of [d][d]: sum over a unit's blocks of H_j; unit i of group g of head bh in slot
-  int32_t partial_head, partial_group;      //  bh * partial_head + g * partial_group + i
+  float* partial;    // scratch fp32, slots of [d][d]: sum over a unit's blocks of H_j; unit u of head bh in slot
+  int32_t partial_head, partial_step;       //  bh * partial_head + u * partial_step
   float* group_sum;  // scratch fp32: sum over the whole group g in slot bh * sum_head + g * sum_group.  In the place of the group's
   int32_t sum_head, sum_group;              // first unit where the units' sums lie in the same array
   uint16_t* hg;      // out bf16 [BH][n_groups][d][d] (see AttnParams::hg)

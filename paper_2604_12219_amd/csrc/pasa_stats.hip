@@ -155,9 +155,7 @@ __global__ void __launch_bounds__(256, 2) kv_stats_kernel(StatsParams p) {
       p.st[(((int64_t)bh * p.n_chunks + (j >> 5)) * 64 + (tid >= D ? 32 : 0) + (j & 31)) * D + col] = 0;
   }
 
-  int slot = u;
-  if (p.partial_group != p.units_per_group) slot += u / p.units_per_group * (p.partial_group - p.units_per_group);
-  float* out = p.partial + ((int64_t)bh * p.partial_head + slot) * D * D;
+  float* out = p.partial + ((int64_t)bh * p.partial_head + u * p.partial_step) * D * D;
 #pragma unroll
   for (int a = 0; a < TI; ++a)
 #pragma unroll
@@ -198,24 +196,25 @@ __global__ void __launch_bounds__(256) hg_finish_kernel(StatsParams p) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   __shared__ __attribute__((aligned(16))) uint16_t piece[kFinishOut][kFinishIn + 8];
   const int g = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
-  const int n_u = min(p.units_per_group, p.n_units - g * p.units_per_group);
+  const int u_lo = g * p.units_per_group, n_u = min(p.units_per_group, p.n_units - u_lo);
   const int blocks_in_group = min((g + 1) * p.group, p.nb) - g * p.group;
   const float f = p.scale / (float)blocks_in_group;
   const int in0 = kFinishIn * (blockIdx.z % (D / kFinishIn)), out0 = kFinishOut * (blockIdx.z / (D / kFinishIn));
   const int in = tid >> 4, out = (tid & 15) * 4;
   const int at = (in0 + in) * D + out0 + out;
-  const float* const src = p.partial + ((int64_t)bh * p.partial_head + (int64_t)g * p.partial_group) * D * D + at;
+  const float* const src = p.partial + ((int64_t)bh * p.partial_head + u_lo * p.partial_step) * D * D + at;
+  const int64_t step = (int64_t)p.partial_step * D * D;
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
   int u = 0;
   for (; u + 8 <= n_u; u += 8) {
     f32x4 x[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + (int64_t)(u + i) * D * D);
+    for (int i = 0; i < 8; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + (u + i) * step);
 #pragma unroll
     for (int i = 0; i < 8; ++i) sum += x[i];
   }
 #pragma unroll 4
-  for (; u < n_u; ++u) sum += *reinterpret_cast<const f32x4*>(src + (int64_t)u * D * D);
+  for (; u < n_u; ++u) sum += *reinterpret_cast<const f32x4*>(src + u * step);
   // (may be where the first unit's sum was, which this thread alone has read above)
   *reinterpret_cast<f32x4*>(p.group_sum + ((int64_t)bh * p.sum_head + (int64_t)g * p.sum_group) * D * D + at) = sum;
 #pragma unroll
