@@ -451,7 +451,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   // the workgroups of an XCD no longer set out together: with two 64-token blocks per workgroup and more keys than the
   // L2s hold, 4 % more tile reads miss (40 heads of 75,600 tokens, 15 % of the blocks: 174 -> 181 GB), which costs more than it
   // gives where memory is what bounds the launch.  So two-block workgroups do it while K and V of a head fit the eight L2s
-  // (32 MB) or those of all heads the memory-side cache (256 MB).  Ascending throughout / own blocks first, us, on boxes with a
+  // (32 MB) or those of all heads the memory-side cache (256 MB).  Ascending throughout / own blocks first, us, on cards with a
   // high and a low clock: d = 128, blocks of 64: 12 heads of 32,760 tokens 1686 / 1664, 1784 / 1766; 40 of 32,760 5666 / 5575, 5955 / 5800;
   // 5 of 75,600 (the whole call, routing with the prior) 3175 / 3121; 3 of 118,800 4979 / 5002, 5017 / 4991; 10 of 75,600 6464 / 6452,
   // 6837 / 6822; 20 of 75,600 12,521 / 12,665, 13,490 / 13,319; 40 of 75,600 24,911 / 25,390, 26,882 / 26,360.  Blocks of 128: 40 of 147,600
