@@ -326,6 +326,209 @@ def fused_step(D):
     return lines
 
 
+# ---- the pipelined step: the same work, with the logits one tile ahead of P V ----
+# In the chain logits -> maximum -> exponentials -> P V of one tile only the matrix work of OTHER keys can run beside the
+# softmax.  So a step takes P V of tile t and the logits of tile t + 1, and the softmax in between has MFMAs on both sides
+# that do not wait for it.  Half h = 32 keys; on entry P(2t) is ready and the logits of half 2t + 1 are complete:
+#   logits of half 2t + 2 -> S0,  O += V[0:32]^T P(2t),        softmax of half 2t + 1: S1 -> P1
+#   logits of half 2t + 3 -> S1,  O += V[32:64]^T P(2t + 1),   softmax of half 2t + 2: S0 -> P0
+# The vector instructions (about 680 cycles of issue at 4 each, 8 for an exponential) are spread evenly over the shadows of
+# the 32 MFMAs (32 cycles each, of which they leave 24 for other vector instructions).
+# A half that raises the maximum leaves the factor for the accumulators: it is applied after the P V of the half
+# before it, in the shadow of the logits that follow; the second half's is handed to the next step (corr, flag).  The rare blocks
+# (.subsection) lie behind the kernel, so the usual way has no taken branch in it.
+# LDS: the ring's K slots are 0 and 2, the V slots 1 and 3; a step of parity `par` reads V from slot 2 par + 1 and K from
+# the other K slot, so every fetch is a lane address that stays the same for all tiles plus an immediate offset.
+class Cold:
+    """blocks that are jumped to and from, kept out of the instruction stream"""
+    def __init__(self, prefix):
+        self.prefix, self.n, self.lines = prefix, 0, []
+
+    def block(self, branch, body):
+        """-> instructions that run `body` if `branch` jumps"""
+        t = f".L{self.prefix}{self.n}"
+        self.n += 1
+        self.lines += [f"{t}_%=:"] + body + [f"s_branch {t}r_%="]
+        return [f"{branch} {t}_%=", f"{t}r_%=:"]
+
+    def text(self):
+        return [".subsection 1"] + self.lines + [".subsection 0"] if self.lines else []
+
+
+def growth(cold, flag, corr):
+    """after max_stream: where the maximum grew for some lane, m, l and the factor `corr` for the accumulators; `flag` is not
+    zero then.  (The lane's own maximum decides, see raise_max.)"""
+    t0, t1, t2 = (vr(FS_T + i) for i in range(3))
+    body = [f"v_mov_b32 {t1}, {t0}", "s_nop 1", f"v_permlane32_swap_b32 {t0}, {t1}", "s_nop 0",
+            f"v_max3_f32 {t1}, %[m], {t0}, {t1}", f"v_sub_f32 {t2}, %[m], {t1}", f"v_exp_f32 {corr}, {t2}",
+            f"v_mov_b32 %[m], {t1}", "s_nop 0", f"v_mul_f32 %[l], %[l], {corr}"]
+    return tuple([f"v_cmp_gt_f32 vcc, {t0}, %[m]", f"s_mov_b64 {flag}, vcc"] + cold.block("s_cbranch_vccnz", body))
+
+
+def pending(cold, flag, corr, n_o, nop):
+    """accumulators *= corr if flag is not zero"""
+    return tuple([f"s_cmp_lg_u64 {flag}, 0"] +
+                 cold.block("s_cbranch_scc1", [nop] + [f"v_mul_f32 {vr(FS_O + i)}, {vr(FS_O + i)}, {corr}" for i in range(n_o)]))
+
+
+def cost(item):
+    if isinstance(item, tuple):
+        return 8
+    return 8 if item.startswith("v_exp") else 4
+
+
+def pour(after, n_slots, stream, first=0, begin=0.0, end=1.0):
+    """distributes the items of `stream` over the slots so that the issue cycles grow linearly from slot begin * n_slots
+    to end * n_slots"""
+    total = sum(cost(x) for x in stream)
+    done = 0
+    for item in stream:
+        k = int((begin + (end - begin) * done / total) * n_slots)
+        after.setdefault(max(first, min(k, n_slots - 1)), []).extend(list(item) if isinstance(item, tuple) else [item])
+        done += cost(item)
+
+
+def pipe_run(D, mf, before, after, dmas, cold, par, prologue=()):
+    """MFMA k of `mf` with its operand fetch issued six MFMAs ahead (load: ("k", step, half) from the K slot, ("v", 16-row
+    step, column tile) from the V slot)"""
+    lines, issued, nbuf = [], [], 6
+    k_off, v_off = (1 - par) * 128 * D * 2, par * 128 * D * 2
+
+    def issue(k):
+        f = k % nbuf
+        kind, a, b = mf[k]["load"]
+        if kind == "k":
+            lines.append(f"ds_read_b128 {F(f)}, %[ka{a}]{off(k_off + b * 64 * D)}")
+            issued.append(1)
+        else:
+            lines.append(f"ds_read_b64_tr_b16 {Flo(f)}, %[va{2 * b}]{off(v_off + a * 32 * D)}")
+            lines.append(f"ds_read_b64_tr_b16 {Fhi(f)}, %[va{2 * b + 1}]{off(v_off + a * 32 * D)}")
+            issued.append(2)
+
+    n = len(mf)
+    for k in range(min(nbuf, n)):
+        issue(k)
+    lines += list(prologue)
+    dmas = list(dmas)
+    for k in range(n):
+        outstanding = sum(issued[k + 1:])
+        assert outstanding <= 15
+        lines.append(f"s_waitcnt lgkmcnt({outstanding})")
+        lines += before.get(k, [])
+        m = mf[k]
+        lines.append(f"{MFMA} {m['acc']}, {F(k % nbuf)}, {m['b']}, {'0' if m['first'] else m['acc']}")
+        if dmas:
+            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * 4096)}")
+        if k + nbuf < n:
+            issue(k + nbuf)
+        elif dmas:
+            lines.append("s_nop 0")
+        if dmas:
+            which, jj = dmas.pop(0)
+            lines.append(f"global_load_lds_dwordx4 %[x{jj}], %[{which}b]")
+        lines += after.get(k, [])
+    assert not dmas
+    return lines
+
+
+def qk_mfmas(D, half):
+    return [dict(acc=vr(FS_S0 if half == 0 else FS_S1, 16), first=(st == 0), b=f"%[q{st}]", load=("k", st, half)) for st in range(D // 16)]
+
+
+def pv_mfmas(D, half):
+    return [dict(acc=vr(FS_O + 16 * t, 16), first=False, b=vr((FS_P0 if half == 0 else FS_P1) + 4 * ks2, 4), load=("v", 2 * half + ks2, t))
+            for ks2 in range(2) for t in range(D // 32)]
+
+
+def pipe_step(D, par):
+    nt = D // 32
+    ni = (64 // (1024 // (2 * D))) // 4
+    n_o = 16 * nt
+    mf = qk_mfmas(D, 0) + pv_mfmas(D, 0) + qk_mfmas(D, 1) + pv_mfmas(D, 1)
+    n, q = len(mf), len(mf) // 4
+    cold = Cold(f"ps{par}_")
+    corr1 = vr(FS_T + 3)
+    after = {}
+    after[1] = list(pending(cold, "%[flag]", "%[corr]", n_o, "s_nop 3"))  # left by the step before
+    # (done with S1 before the MFMAs of the second half write it; S0 is long complete)
+    pour(after, n, [growth(cold, "%[flag1]", corr1)] + exp_stream(FS_S1, FS_P1), first=1, end=0.5)
+    pour(after, n, max_stream(FS_S0) + [growth(cold, "%[flag]", "%[corr]")] + exp_stream(FS_S0, FS_P0), begin=0.5)
+    k = 2 * q + 1  # the P V of half 2t is through
+    after[k] = list(pending(cold, "%[flag1]", corr1, n_o, "s_nop 3")) + after.get(k, [])
+    dmas = [("k", j) for j in range(ni)] + [("v", j) for j in range(ni)]
+    lines = pipe_run(D, mf, {}, after, dmas, cold, par, prologue=max_stream(FS_S1))
+    return lines + cold.text()
+
+
+def pipe_start(D):
+    """logits of the first tile (K slot 0) and the softmax of its first half"""
+    mf = qk_mfmas(D, 0) + qk_mfmas(D, 1)
+    n, q = len(mf), len(mf) // 2
+    cold = Cold("pb")
+    after = {}
+    pour(after, n, max_stream(FS_S0) + [growth(cold, "%[flag]", "%[corr]")] + exp_stream(FS_S0, FS_P0), first=q + 1, begin=(q + 1) / n)
+    return pipe_run(D, mf, {}, after, [], cold, 1) + [NOP_AFTER] + cold.text()
+
+
+def pipe_end(D, par):
+    """P V of the last tile (V slot 2 par + 1) and the softmax of its second half"""
+    n_o = 16 * (D // 32)
+    mf = pv_mfmas(D, 0) + pv_mfmas(D, 1)
+    n, q = len(mf), len(mf) // 2
+    cold = Cold(f"pe{par}_")
+    after = {}
+    pour(after, q, [growth(cold, "%[flag]", "%[corr]")] + exp_stream(FS_S1, FS_P1))
+    before = {q: list(pending(cold, "%[flag]", "%[corr]", n_o, NOP_AFTER)) + ["s_nop 1"]}
+    lines = pipe_run(D, mf, before, after, [], cold, par,
+                     prologue=list(pending(cold, "%[flag]", "%[corr]", n_o, NOP_AFTER)) + max_stream(FS_S1) + ["s_nop 1"])
+    return lines + [NOP_AFTER] + cold.text()
+
+
+def both_parities(name, make):
+    """one statement for the two parities: the compiler keeps the fixed registers in place over a loop around one statement"""
+    return [f"s_cmp_lg_u32 %[par], 0", f"s_cbranch_scc1 .L{name}odd_%="] + make(0) + [f"s_branch .L{name}done_%=", f".L{name}odd_%=:"] + \
+        make(1) + [f".L{name}done_%=:"]
+
+
+def pipe_functions():
+    out = []
+    clobber = lambda regs: ", ".join([f'"v{r}"' for r in regs] + ['"memory"', '"scc"', '"vcc"', '"m0"'])
+    s0, p1, rest = range(FS_S0, FS_S0 + 16), range(FS_P1, FS_P1 + 8), list(range(FS_T, 256))
+    for D in (128, 64):
+        ns, nt = D // 16, D // 32
+        ni = (64 // (1024 // (2 * D))) // 4
+        state = (f"f32x16 (&o)[{nt}], float& m, float& l, PipeState& st")
+        ml = ['[m] "+v"(m)', '[l] "+v"(l)']
+        sb = '"+{v[184:199]}"(st.s1)'
+        pa = [f'"+{{v[{200 + 4 * k}:{203 + 4 * k}]}}"(st.p0[{k}])' for k in range(2)]
+        carry = ['[corr] "+v"(st.corr)', '[flag] "+s"(st.flag)']
+        kin = [f'[ka{s}] "v"(ka[{s}])' for s in range(ns)] + q_inputs(D)
+        vin = [f'[va{s}] "v"(va[{s}])' for s in range(2 * nt)]
+        cin = ['[c] "s"(c)']
+        dma = ['[kb] "s"(kb)', '[vb] "s"(vb)', '[lk] "s"(lk)', '[lv] "s"(lv)'] + [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
+
+        def emit(comment, head, pre, lines, outs, ins, clob):
+            text = "\n".join(f'      "{l}\\n\\t"' for l in lines)
+            out.append(f"{comment}PASA_DEVICE void {head} {{\n{pre}  asm volatile(\n{text}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n"
+                       f"      : {clobber(clob)});\n}}\n\n")
+
+        emit("// Start of a run of pipelined steps: logits of the tile in K slot 0, softmax of its first half.  ka, va: the lane's addresses of\n"
+             "// the row fragments in K slot 0 and of the column fragments in V slot 1; corr, flag of the state are outputs.\n",
+             f"pipe_start(const uint32_t (&ka)[{ns}], const bf16x8 (&q)[{ns}], float& m, float& l, float c, PipeState& st)", "",
+             pipe_start(D), ml + ['"=&{v[184:199]}"(st.s1)'] + [x.replace("+", "=&") for x in pa] + ['[corr] "=&v"(st.corr)', '[flag] "=&s"(st.flag)'],
+             kin + cin, list(s0) + list(range(FS_P1, FS_P1 + 8)) + rest)
+        par_in = ['[par] "s"(par)']
+        emit("// P V of the tile in V slot 2 par + 1, logits of the next one, in K slot 2 - 2 par; two more tiles are requested (see rows_x_q_dma).\n",
+             f"pipe_step(int par, const uint32_t (&ka)[{ns}], const uint32_t (&va)[{2 * nt}], const bf16x8 (&q)[{ns}], {state}, float c,\n"
+             f"                          const void* kb, const void* vb, const uint32_t (&x)[{ni}], uint32_t lk, uint32_t lv)",
+             "  uint64_t flag1;\n", both_parities("ps", lambda par: pipe_step(D, par)), o_ops(nt) + ml + [sb] + pa + carry + ['[flag1] "=&s"(flag1)'],
+             kin + vin + cin + dma + par_in, list(s0) + list(p1) + rest)
+        emit("// End of a run: P V of the tile in V slot 2 par + 1.\n",
+             f"pipe_end(int par, const uint32_t (&va)[{2 * nt}], {state}, float c)", "", both_parities("pe", lambda par: pipe_end(D, par)),
+             o_ops(nt) + ml + [sb] + pa + carry, vin + cin + par_in, list(s0) + list(p1) + rest)
+    return "".join(out)
+
+
 def run_pipe(D, mf, before, after, dmas):
     """MFMA k of `mf` with its operand fetch issued six MFMAs ahead; `before[k]` / `after[k]` are instruction
     lists placed right before / after MFMA k; `dmas`: tile-load instructions (slot tag, index), one per MFMA
@@ -518,7 +721,10 @@ def gen():
     out = []
     out.append("// GENERATED by gen_mfma_pipes.py -- do not edit.  Software-pipelined LDS-read + MFMA sequences of the\n"
                "// attention kernel (gfx950).  Every function is one asm statement; v226..v255 are its operand buffers.\n"
-               "#pragma once\n#include \"pasa_device.hpp\"\n\nnamespace pipes {\n")
+               "#pragma once\n#include \"pasa_device.hpp\"\n\nnamespace pipes {\n\n"
+               "// What one pipelined step hands to the next: the logits of the second half of the tile whose P V comes next, the weights of\n"
+               "// its first half, and the factor for the accumulators (where flag is not zero).\n"
+               "struct PipeState {\n  f32x16 s1;\n  bf16x8 p0[2];\n  float corr;\n  uint64_t flag;\n};\n\n")
     for D in (128, 64):
         ni = (64 // (1024 // (2 * D))) // 4
         # rows_x_q
@@ -556,6 +762,7 @@ def gen():
               ['[kb] "s"(kb)', '[vb] "s"(vb)', '[lk] "s"(lk)', '[lv] "s"(lv)'] + [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
         out.append(asm_block(cols_x_p(D, 4, 0, ni), outs, ins, ("memory", "scc", "m0")))
         out.append("}\n\n")
+    out.append(pipe_functions())
     for D in (128, 64):
         ns, nt = D // 16, D // 32
         ni = (64 // (1024 // (2 * D))) // 4

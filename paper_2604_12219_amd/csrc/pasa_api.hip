@@ -447,6 +447,7 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     a.queue = reinterpret_cast<uint32_t*>(base + w.queue);
   }
   a.teams = !sparse && dense_teams(&s);
+  a.wide = !sparse && !a.teams;
   return pasa_launch_attn(a, sparse, s.d, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 

@@ -511,24 +511,69 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
         return r0;
       }
     };
-    int r_cur = plan();
-    load_q();
-    if (r_cur >= 0) { request(kb, r_cur, 0); request(vb, r_cur, 1); }
-    settle_q();
-    int pair = 0;
-    // Tiles whose 64 rows are all keys of the tile: one instruction stream per tile.  (The blocks that come first are
-    // whole and the others ascend, so a tile that reaches beyond the last token can only be among the last ones.)
+    auto whole = [&](int r) -> bool { return r >= 0 && r + 64 <= n; };
+    int r_cur = plan(), pair = 0;
+    if constexpr (MODE == 0) {
+      // Tiles whose 64 rows are all keys of the tile: pipelined steps, each with P V of one tile and the logits of the next.
+      // K of tile t is in slot 2 (t & 1), V in the slot after it.  Against steps of one tile (fused_step), 12 heads of 32,760
+      // tokens: 3.90 -> 3.47 ms with all-zero inputs (clock at its maximum: 3130 -> 2780 cycles a step of two workgroups, 2048 of
+      // them MFMAs), 5.89 -> 5.65 ms with random ones (where the power limit sets the clock, so that what a step moves and
+      // switches counts more than its cycles); 4140 tokens, 4 heads: 74.7 -> 67.6 us.
+      if (r_cur >= 0) request(kb, r_cur, 0);
+      load_q();
+      settle_q();
+      if (whole(r_cur)) {
+        uint32_t ka[D / 16], va[D / 16];
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) ka[s] = (slot(0) + lo.k) ^ (uint32_t)(s << 5);
+#pragma unroll
+        for (int t = 0; t < D / 32; ++t) {
+          va[2 * t] = (slot(1) + lo.v[0]) ^ (uint32_t)(t << 6);
+          va[2 * t + 1] = (slot(1) + lo.v[1]) ^ (uint32_t)(t << 6);
+        }
+        pipes::PipeState ps;
+        int r_nxt = plan();
+        request(vb, r_cur, 1);
+        request(kb, r_nxt >= 0 ? r_nxt : r_cur, 2);
+        ring_barrier<NI>(2);  // the first K tile has landed
+        pipes::pipe_start(ka, w.qf, w.m, w.l, p.c, ps);
+        // V of the tile and K of the next one have landed; the next V and the K after it are requested into the other slots
+        // (where there is none: once more one that exists, unused)
 #pragma unroll 1
-    while (r_cur >= 0 && r_cur + 64 <= n) {
-      ring_barrier<NI>(0);  // the pair has landed; every wave is done with the previous pair
-      const int r_nxt = plan();
-      // the next pair is requested into the other two slots (after the last pair: once more the same, unused)
-      const int r_req = r_nxt >= 0 ? r_nxt : r_cur;
-      const uint32_t k_tile = slot(2 * pair), v_tile = slot(2 * pair + 1);
-      pipes::fused_step(k_tile + lo.k, v_tile + lo.v[0], v_tile + lo.v[1], w.qf, w.o, w.m, w.l, p.c, tile_ptr(kb, r_req),
-                        tile_ptr(vb, r_req), x_kv, slot_wave(2 * pair + 2), slot_wave(2 * pair + 3));
-      r_cur = r_nxt;
-      ++pair;
+        while (whole(r_nxt)) {
+          ring_barrier<NI>(0);
+          const int r_k = plan();
+          pipes::pipe_step(pair, ka, va, w.qf, w.o, w.m, w.l, ps, p.c, tile_ptr(kb, r_k >= 0 ? r_k : r_nxt), tile_ptr(vb, r_nxt), x_kv,
+                           slot_wave(2 * pair), slot_wave(2 * pair + 3));
+          r_nxt = r_k;
+          pair ^= 1;
+        }
+        ring_barrier<NI>(0);
+        if (r_nxt >= 0) request(vb, r_nxt, 2 * pair + 3);
+        pipes::pipe_end(pair, va, w.o, w.m, w.l, ps, p.c);
+        r_cur = r_nxt;
+        ++pair;
+      } else if (r_cur >= 0) {
+        request(vb, r_cur, 1);
+      }
+    } else {
+      load_q();
+      if (r_cur >= 0) { request(kb, r_cur, 0); request(vb, r_cur, 1); }
+      settle_q();
+      // Tiles whose 64 rows are all keys of the tile: one instruction stream per tile.  (The blocks that come first are
+      // whole and the others ascend, so a tile that reaches beyond the last token can only be among the last ones.)
+#pragma unroll 1
+      while (whole(r_cur)) {
+        ring_barrier<NI>(0);  // the pair has landed; every wave is done with the previous pair
+        const int r_nxt = plan();
+        // the next pair is requested into the other two slots (after the last pair: once more the same, unused)
+        const int r_req = r_nxt >= 0 ? r_nxt : r_cur;
+        const uint32_t k_tile = slot(2 * pair), v_tile = slot(2 * pair + 1);
+        pipes::fused_step(k_tile + lo.k, v_tile + lo.v[0], v_tile + lo.v[1], w.qf, w.o, w.m, w.l, p.c, tile_ptr(kb, r_req),
+                          tile_ptr(vb, r_req), x_kv, slot_wave(2 * pair + 2), slot_wave(2 * pair + 3));
+        r_cur = r_nxt;
+        ++pair;
+      }
     }
     // The last tile(s), shifted back to end at the last token: their leading rows are not keys of the tile.
 #pragma unroll 1
