@@ -45,7 +45,7 @@ def off(n):
     return f" offset:{n}" if n else ""
 
 
-def rows_x_q(D, two_halves, dma):
+def rows_x_q(D, two_halves, dma, waves=4):
     """acc(s) += rowfrag(rows 0..31 [and 32..63], step s) x q[s].
     two_halves: c0 <- rows 0..31, c1 <- rows 32..63.  Otherwise rows 0..31 only, even steps -> c0, odd -> c1.
     dma: number of tile-load instructions per tile of this wave (0 = none); requests a K-like and a V-like
@@ -75,6 +75,7 @@ def rows_x_q(D, two_halves, dma):
         lines.append(f"ds_read_b128 {F(i % nbuf)}, {addr(s)}{off(o)}")
 
     dmas = [("k", j) for j in range(dma)] + [("v", j) for j in range(dma)]
+    stride = waves * 1024  # a wave's tile-load instructions are this far apart in LDS
     n = len(frags)
     for i in range(min(nbuf, n)):
         issue(i)
@@ -87,7 +88,7 @@ def rows_x_q(D, two_halves, dma):
         seen.add(acc)
         lines.append(f"{MFMA} %[{acc}], {F(i % nbuf)}, %[q{s}], {src_c}")
         if dmas:  # in the shadow of the MFMA: one tile-load instruction (M0 = its LDS destination)
-            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * 4096)}")
+            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * stride)}")
         if i + nbuf < n:
             issue(i + nbuf)
         elif dmas:
@@ -388,7 +389,7 @@ def pour(after, n_slots, stream, first=0, begin=0.0, end=1.0):
         done += cost(item)
 
 
-def pipe_run(D, mf, before, after, dmas, cold, par, prologue=()):
+def pipe_run(D, mf, before, after, dmas, cold, par, prologue=(), waves=4):
     """MFMA k of `mf` with its operand fetch issued six MFMAs ahead (load: ("k", step, half) from the K slot, ("v", 16-row
     step, column tile) from the V slot)"""
     lines, issued, nbuf = [], [], 6
@@ -418,7 +419,7 @@ def pipe_run(D, mf, before, after, dmas, cold, par, prologue=()):
         m = mf[k]
         lines.append(f"{MFMA} {m['acc']}, {F(k % nbuf)}, {m['b']}, {'0' if m['first'] else m['acc']}")
         if dmas:
-            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * 4096)}")
+            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * waves * 1024)}")
         if k + nbuf < n:
             issue(k + nbuf)
         elif dmas:
@@ -440,9 +441,14 @@ def pv_mfmas(D, half):
             for ks2 in range(2) for t in range(D // 32)]
 
 
-def pipe_step(D, par):
+def tile_loads(D, waves):
+    """tile-load instructions of one wave"""
+    return D // 8 // waves
+
+
+def pipe_step(D, par, waves):
     nt = D // 32
-    ni = (64 // (1024 // (2 * D))) // 4
+    ni = tile_loads(D, waves)
     n_o = 16 * nt
     mf = qk_mfmas(D, 0) + pv_mfmas(D, 0) + qk_mfmas(D, 1) + pv_mfmas(D, 1)
     n, q = len(mf), len(mf) // 4
@@ -456,7 +462,7 @@ def pipe_step(D, par):
     k = 2 * q + 1  # the P V of half 2t is through
     after[k] = list(pending(cold, "%[flag1]", corr1, n_o, "s_nop 3")) + after.get(k, [])
     dmas = [("k", j) for j in range(ni)] + [("v", j) for j in range(ni)]
-    lines = pipe_run(D, mf, {}, after, dmas, cold, par, prologue=max_stream(FS_S1))
+    lines = pipe_run(D, mf, {}, after, dmas, cold, par, prologue=max_stream(FS_S1), waves=waves)
     return lines + cold.text()
 
 
@@ -496,7 +502,6 @@ def pipe_functions():
     s0, p1, rest = range(FS_S0, FS_S0 + 16), range(FS_P1, FS_P1 + 8), list(range(FS_T, 256))
     for D in (128, 64):
         ns, nt = D // 16, D // 32
-        ni = (64 // (1024 // (2 * D))) // 4
         state = (f"f32x16 (&o)[{nt}], float& m, float& l, PipeState& st")
         ml = ['[m] "+v"(m)', '[l] "+v"(l)']
         sb = '"+{v[184:199]}"(st.s1)'
@@ -505,7 +510,7 @@ def pipe_functions():
         kin = [f'[ka{s}] "v"(ka[{s}])' for s in range(ns)] + q_inputs(D)
         vin = [f'[va{s}] "v"(va[{s}])' for s in range(2 * nt)]
         cin = ['[c] "s"(c)']
-        dma = ['[kb] "s"(kb)', '[vb] "s"(vb)', '[lk] "s"(lk)', '[lv] "s"(lv)'] + [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
+        dma = lambda ni: ['[kb] "s"(kb)', '[vb] "s"(vb)', '[lk] "s"(lk)', '[lv] "s"(lv)'] + [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
 
         def emit(comment, head, pre, lines, outs, ins, clob):
             text = "\n".join(f'      "{l}\\n\\t"' for l in lines)
@@ -518,18 +523,21 @@ def pipe_functions():
              pipe_start(D), ml + ['"=&{v[184:199]}"(st.s1)'] + [x.replace("+", "=&") for x in pa] + ['[corr] "=&v"(st.corr)', '[flag] "=&s"(st.flag)'],
              kin + cin, list(s0) + list(range(FS_P1, FS_P1 + 8)) + rest)
         par_in = ['[par] "s"(par)']
-        emit("// P V of the tile in V slot 2 par + 1, logits of the next one, in K slot 2 - 2 par; two more tiles are requested (see rows_x_q_dma).\n",
-             f"pipe_step(int par, const uint32_t (&ka)[{ns}], const uint32_t (&va)[{2 * nt}], const bf16x8 (&q)[{ns}], {state}, float c,\n"
-             f"                          const void* kb, const void* vb, const uint32_t (&x)[{ni}], uint32_t lk, uint32_t lv)",
-             "  uint64_t flag1;\n", both_parities("ps", lambda par: pipe_step(D, par)), o_ops(nt) + ml + [sb] + pa + carry + ['[flag1] "=&s"(flag1)'],
-             kin + vin + cin + dma + par_in, list(s0) + list(p1) + rest)
+        for waves in (4, 8):
+            ni = tile_loads(D, waves)
+            emit(f"// P V of the tile in V slot 2 par + 1, logits of the next one, in K slot 2 - 2 par; two more tiles are requested (see\n"
+                 f"// rows_x_q_dma) by the {waves} waves of the workgroup.\n",
+                 f"pipe_step(int par, const uint32_t (&ka)[{ns}], const uint32_t (&va)[{2 * nt}], const bf16x8 (&q)[{ns}], {state}, float c,\n"
+                 f"                          const void* kb, const void* vb, const uint32_t (&x)[{ni}], uint32_t lk, uint32_t lv)",
+                 "  uint64_t flag1;\n", both_parities("ps", lambda par: pipe_step(D, par, waves)),
+                 o_ops(nt) + ml + [sb] + pa + carry + ['[flag1] "=&s"(flag1)'], kin + vin + cin + dma(ni) + par_in, list(s0) + list(p1) + rest)
         emit("// End of a run: P V of the tile in V slot 2 par + 1.\n",
              f"pipe_end(int par, const uint32_t (&va)[{2 * nt}], {state}, float c)", "", both_parities("pe", lambda par: pipe_end(D, par)),
              o_ops(nt) + ml + [sb] + pa + carry, vin + cin + par_in, list(s0) + list(p1) + rest)
     return "".join(out)
 
 
-def run_pipe(D, mf, before, after, dmas):
+def run_pipe(D, mf, before, after, dmas, waves):
     """MFMA k of `mf` with its operand fetch issued six MFMAs ahead; `before[k]` / `after[k]` are instruction
     lists placed right before / after MFMA k; `dmas`: tile-load instructions (slot tag, index), one per MFMA
     shadow from the first MFMA on."""
@@ -546,7 +554,7 @@ def run_pipe(D, mf, before, after, dmas):
         m = mf[k]
         lines.append(f"{MFMA} {m['acc']}, {F(k % pipe.nbuf)}, {m['b']}, {'0' if m['first'] else m['acc']}")
         if dmas:
-            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * 4096)}")
+            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * waves * 1024)}")
         if k + pipe.nbuf < n:
             pipe.issue(k + pipe.nbuf, mf[k + pipe.nbuf]["load"])
         elif dmas:
@@ -576,9 +584,9 @@ def flat(stream):
 # could overflow before its mask is applied.)  Lane (x, h) holds block 8g + 4h + r
 # in register 4g + r, so with the bitmap word shifted right by 4h the block's bit is bit 8g + r for every lane.
 # Registers: Z v[168:183], per-element masks v[184:199], P^T v[200:207], the rest as in fused_step.
-def stats_step(D):
+def stats_step(D, waves):
     ns, nt = D // 16, D // 32
-    ni = (64 // (1024 // (2 * D))) // 4
+    ni = tile_loads(D, waves)
     n_o = 16 * nt
     S, U, P = FS_S0, FS_S1, FS_P0
     s = lambda i: vr(S + i)
@@ -617,7 +625,7 @@ def stats_step(D):
     after = {}
     spread(after, ns, ns + nt - 1, second_half)
     spread(after, ns + nt, ns + 2 * nt - 1, fin)
-    lines = run_pipe(D, mf, before, after, [("s", j) for j in range(ni)])
+    lines = run_pipe(D, mf, before, after, [("s", j) for j in range(ni)], waves)
     lines.append(NOP_AFTER)
     return lines
 
@@ -625,9 +633,9 @@ def stats_step(D):
 # ---- first-order step: 64 value columns of one group,  O^T[part] += A ((scale Hg)^T[part] Q^T) ----
 # Rows 0..31 of the tile first, then rows 32..63 with the update from the first product in the shadow of
 # their MFMAs.  The next tile of the stream is requested in the shadow of the first MFMAs.
-def first_order_step(D, part):
+def first_order_step(D, part, waves):
     ns = D // 16
-    ni = (64 // (1024 // (2 * D))) // 4
+    ni = tile_loads(D, waves)
     mf = []
     for half in range(2):
         for st in range(ns):
@@ -635,7 +643,7 @@ def first_order_step(D, part):
     o0, o1 = FS_O + 32 * part, FS_O + 32 * part + 16
     after = {}
     spread(after, ns + 1, 2 * ns - 1, [f"v_fmac_f32 {vr(o0 + r)}, %[A], {vr(FS_S0 + r)}" for r in range(16)])
-    lines = run_pipe(D, mf, {}, after, [("s", j) for j in range(ni)])
+    lines = run_pipe(D, mf, {}, after, [("s", j) for j in range(ni)], waves)
     lines.append(NOP_AFTER)
     lines += [f"v_fmac_f32 {vr(o1 + r)}, %[A], {vr(FS_S1 + r)}" for r in range(16)]
     return lines
@@ -732,14 +740,18 @@ def gen():
                    f"PASA_DEVICE void rows_x_q(uint32_t a, const bf16x8 (&q)[{D // 16}], f32x16& c0, f32x16& c1) {{\n")
         out.append(asm_block(rows_x_q(D, True, 0), c_ops(), ['[a] "v"(a)'] + q_inputs(D), ("memory",)))
         out.append("}\n\n")
-        out.append(f"// the same, and in the shadow of the first MFMAs this wave's share of the next K tile (from kb into the slot\n"
-                   f"// at LDS address lk) and V tile (vb, lv) is requested; x = the lane's byte offsets of its {ni} loads per tile\n"
-                   f"PASA_DEVICE void rows_x_q_dma(uint32_t a, const bf16x8 (&q)[{D // 16}], f32x16& c0, f32x16& c1, const void* kb,\n"
-                   f"                             const void* vb, const uint32_t (&x)[{ni}], uint32_t lk, uint32_t lv) {{\n")
-        ins = ['[a] "v"(a)'] + q_inputs(D) + ['[kb] "s"(kb)', '[vb] "s"(vb)', '[lk] "s"(lk)', '[lv] "s"(lv)'] + \
-              [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
-        out.append(asm_block(rows_x_q(D, True, ni), c_ops(), ins, ("memory", "scc", "m0")))
-        out.append("}\n\n")
+        for waves in (4, 8):
+            ni = tile_loads(D, waves)
+            out.append(f"// the same, and in the shadow of the first MFMAs this wave's share of the next K tile (from kb into the slot\n"
+                       f"// at LDS address lk) and V tile (vb, lv) is requested; x = the lane's byte offsets of its {ni} loads per tile\n"
+                       f"// ({waves} waves)\n"
+                       f"PASA_DEVICE void rows_x_q_dma(uint32_t a, const bf16x8 (&q)[{D // 16}], f32x16& c0, f32x16& c1, const void* kb,\n"
+                       f"                             const void* vb, const uint32_t (&x)[{ni}], uint32_t lk, uint32_t lv) {{\n")
+            ins = ['[a] "v"(a)'] + q_inputs(D) + ['[kb] "s"(kb)', '[vb] "s"(vb)', '[lk] "s"(lk)', '[lv] "s"(lv)'] + \
+                  [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
+            out.append(asm_block(rows_x_q(D, True, ni, waves), c_ops(), ins, ("memory", "scc", "m0")))
+            out.append("}\n\n")
+        ni = tile_loads(D, 4)
         out.append(f"// rows 0..31 only: c0 + c1 = (tile rows 0..31) x Q^T (even contraction steps in c0, odd ones in c1)\n"
                    f"PASA_DEVICE void rows32_x_q(uint32_t a, const bf16x8 (&q)[{D // 16}], f32x16& c0, f32x16& c1) {{\n")
         out.append(asm_block(rows_x_q(D, False, 0), c_ops(), ['[a] "v"(a)'] + q_inputs(D), ("memory",)))
@@ -797,9 +809,9 @@ def gen():
         clob = ", ".join([f'"v{r}"' for r in range(168, 200)] + [f'"v{r}"' for r in range(216, 256)] +
                          ['"memory"', '"scc"', '"vcc"', '"m0"'])
         out.append(f"  asm volatile(\n{text}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n      : {clob});\n}}\n\n")
-    for D in (128, 64):
+    for D, waves in ((128, 4), (64, 4)):
         ns, nt = D // 16, D // 32
-        ni = (64 // (1024 // (2 * D))) // 4
+        ni = tile_loads(D, waves)
         dma_ins = ['[sb] "s"(sb)', '[ls] "s"(ls)'] + [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
         out.append(f"// Zeroth-order step of the approximation for a chunk of 32 existing, full key blocks.  ak, av0, av1: the\n"
                    f"// statistics tile's address + row-fragment / column-fragment offsets; unsel: bit x set iff block x of the\n"
@@ -811,7 +823,7 @@ def gen():
         outs = o_ops(nt) + ['[m] "+v"(m)', '[l] "+v"(l)', '[A] "=&v"(A)']
         ins = ['[ak] "v"(ak)', '[av0] "v"(av0)', '[av1] "v"(av1)', '[c] "s"(c)', '[unsel] "s"(unsel)', '[sh] "v"(sh)',
                '[bf] "s"(bf)'] + q_inputs(D) + dma_ins
-        text = "\n".join(f'      "{l}\\n\\t"' for l in stats_step(D))
+        text = "\n".join(f'      "{l}\\n\\t"' for l in stats_step(D, waves))
         clob = ", ".join([f'"v{r}"' for r in range(FUSED_CLOBBER_LO, 256)] + ['"memory"', '"scc"', '"vcc"', '"m0"'])
         out.append(f"  asm volatile(\n{text}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n      : {clob});\n}}\n\n")
         for part in range(D // 64):
@@ -821,7 +833,7 @@ def gen():
                        f"                                 const void* sb, const uint32_t (&x)[{ni}], uint32_t ls) {{\n")
             outs = [o_ops(nt)[2 * part], o_ops(nt)[2 * part + 1]]
             ins = ['[ak] "v"(ak)', '[A] "v"(A)'] + q_inputs(D) + dma_ins
-            text = "\n".join(f'      "{l}\\n\\t"' for l in first_order_step(D, part))
+            text = "\n".join(f'      "{l}\\n\\t"' for l in first_order_step(D, part, waves))
             out.append(f"  asm volatile(\n{text}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n      : {clob});\n}}\n\n")
     out.append("}  // namespace pipes\n")
     return "".join(out)

@@ -166,6 +166,19 @@ bool dense_teams(const pasa_shape_t* s) {
   return (int64_t)s->B * s->H * q_tiles_per_xcd <= 32 && key_tiles >= (s->d == 128 ? 12 : 8);
 }
 
+// Whether the dense path takes workgroups of 256 query rows (eight waves, a compute unit to themselves) instead of two of 128 on a
+// compute unit.  Both keep a compute unit equally busy, but the wide one brings every K and V tile into LDS once instead of twice,
+// and where the power limit sets the clock that is worth 3.5 %: 12 heads of 32,760 tokens 5512 -> 5325 us at d = 128.  It loses where its
+// rounds (32 compute units of the XCD with the most tiles at a time) come out longer than those of half the size.  us, narrow / wide:
+//   d = 128: 7 heads of 4140 (35 narrow / 21 wide tiles on an XCD) 113 / 111; 12 (60 / 36) 132 / 229; 24 (120 / 72) 257 / 357;
+//     6 of 9900 (60 / 30) 291 / 281; 26 (260 / 130) 1273 / 1362; 2 of 32,760 (64 / 32) 976 / 936; 3 (96 / 48) 1475 / 1562
+//   d = 64: 7 of 4140 82.5 / 80.0; 12 86.6 / 159; 6 of 9900 195 / 193; 2 of 32,760 616 / 594
+bool dense_wide(const pasa_shape_t* s) {
+  const int64_t bh = (int64_t)s->B * s->H, n = s->n;
+  const int64_t wide = (bh * ((n + 2047) / 2048) + 31) / 32, narrow = (bh * ((n + 1023) / 1024) + 31) / 32;  // rounds; half rounds
+  return 62 * wide <= 32 * narrow;
+}
+
 constexpr int kMaxDevices = 64;
 std::atomic<void*> g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each device, null until looked up
 std::mutex g_scratch_mutex;
@@ -447,7 +460,7 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     a.queue = reinterpret_cast<uint32_t*>(base + w.queue);
   }
   a.teams = !sparse && dense_teams(&s);
-  a.wide = !sparse && !a.teams;
+  a.wide = !sparse && !a.teams && dense_wide(&s);
   return pasa_launch_attn(a, sparse, s.d, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 

@@ -33,6 +33,8 @@
 // (Nothing goes through the workspace: callers may share one among calls that overlap.)  The rule is in pasa_api.hip
 // (dense_teams).
 //
+// Dense path, grids that keep the device busy with workgroups of 256 query rows: eight waves share every tile (dense_wide).
+//
 // Data movement.  All tiles (K, V, block statistics, group matrices) are 64-row tiles that stream
 // through a ring of four 16 KB LDS buffers by direct global->LDS loads: the exact passes consume a
 // (K, V) pair per step while the next pair lands in the other two buffers, the approximation pass
@@ -49,7 +51,6 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kXcds = 8;    // accelerator complex dies of an MI355X, each with its own L2
-constexpr int kWaves = 4;   // waves per workgroup
 constexpr int kRing = 4;    // LDS tile buffers
 constexpr int kNoBlock = 0x7fffffff;
 
@@ -209,12 +210,12 @@ PASA_DEVICE void dma_1k(const void* sbase, uint32_t voff, uint32_t lds_addr) {
                : "memory", "m0");
 }
 
-template <int D>
+template <int D, int WAVES>
 struct TileDma {
   static constexpr int CPR = D / 8;                 // 16-byte chunks per row
   static constexpr int RPI = 1024 / (2 * D);        // rows per instruction
-  static constexpr int NI = 64 / RPI / kWaves;      // instructions per wave and tile
-  static constexpr int STEP = kWaves * RPI;         // a lane's rows in consecutive instructions are this far apart
+  static constexpr int NI = 64 / RPI / WAVES;      // instructions per wave and tile
+  static constexpr int STEP = WAVES * RPI;         // a lane's rows in consecutive instructions are this far apart
   static_assert(STEP % 16 == 0, "a lane's swizzle must be the same in all of its instructions");
 
   int row0;       // the lane's row in the wave's first instruction
@@ -234,7 +235,7 @@ struct TileDma {
   // lds_wave: LDS address of the slot plus wave*1024.
   PASA_DEVICE static void request(const void* base, const uint32_t (&x)[NI], uint32_t lds_wave) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) dma_1k(base, x[i], lds_wave + (uint32_t)(i * kWaves * 1024));
+    for (int i = 0; i < NI; ++i) dma_1k(base, x[i], lds_wave + (uint32_t)(i * WAVES * 1024));
   }
 };
 
@@ -312,28 +313,30 @@ struct BitWalk {
 // 2: sparse, two adjacent 64-token query blocks per workgroup.  MULTI: the group has fewer than 32
 // blocks, so a chunk of 32 blocks intersects several groups and the per-block weights of a chunk have
 // to be kept until all of its group matrices have passed.  PART: kWhole: a workgroup walks all keys of its
-// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two teams of waves.
-enum : int { kWhole = 0, kSliced = 1, kTeams = 2 };
+// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two teams of waves; kWide (dense): eight waves, 256 query rows.
+enum : int { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3 };
 constexpr int teams_of(int part) { return part == kTeams ? 2 : 1; }
+constexpr int waves_of(int part) { return part == kWide ? 8 : 4; }  // of a team
 template <int D, int MODE, bool MULTI, int PART>
-__global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(AttnParams p) {
+__global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_kernel(AttnParams p) {
   constexpr bool SPARSE = MODE != 0, SLICED = PART == kSliced;
-  constexpr int TEAMS = teams_of(PART);
+  constexpr int TEAMS = teams_of(PART), WAVES = waves_of(PART);
+  typedef TileDma<D, WAVES> Dma;
   static_assert(TEAMS == 1 || MODE == 0, "the sparse passes count on every wave of the workgroup making the same steps");
   constexpr int TILE_BYTES = 64 * 2 * D;
-  constexpr int NI = TileDma<D>::NI;
+  constexpr int NI = Dma::NI;
   constexpr int HPARTS = D / 64;  // 64-row tiles per group matrix
   __shared__ __attribute__((aligned(1024))) char ring[TEAMS * kRing * TILE_BYTES];
 
   __shared__ int s_item, s_queue;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (kWaves * 64));
-  const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) - team * kWaves);  // within the team
+  const int team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / (WAVES * 64));
+  const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) - team * WAVES);  // within the team
   const int ql = lane & 31, h = lane >> 5;
   const uint32_t ring_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + (uint32_t)(team * kRing * TILE_BYTES);
   LaneOffsets<D> lo;
   lo.init(lane);
-  TileDma<D> dma;
+  Dma dma;
   dma.init(wave, lane);
   const uint32_t row_bytes = (uint32_t)(p.stride_n * 2);
   uint32_t x_kv[NI];  // lane offsets of the loads of a whole K or V tile
@@ -394,7 +397,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   const uint16_t* const kb = p.k + head_off;
   const uint16_t* const vb = p.v + head_off;
   const int n = p.n;
-  const int q_row = qt * 128 + wave * 32 + ql;
+  const int q_row = qt * (WAVES * 32) + wave * 32 + ql;
 
   WaveState<D> w;
   // The queries are fetched together with the first tile pair (below): the two latencies overlap.
@@ -477,7 +480,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   auto tile_ptr = [&](const uint16_t* base, int r0) -> const char* {
     return reinterpret_cast<const char*>(base) + (uint32_t)tile_row(r0) * row_bytes;
   };
-  auto request = [&](const uint16_t* base, int r0, int sl) { TileDma<D>::request(tile_ptr(base, r0), x_kv, slot_wave(sl)); };
+  auto request = [&](const uint16_t* base, int r0, int sl) { Dma::request(tile_ptr(base, r0), x_kv, slot_wave(sl)); };
 
 
   // ---------------- exact attention, part 1: tiles that all four waves need ----------------
@@ -718,7 +721,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
       };
       ring_barrier<NI>(0);  // every wave is done with the ring
       for (int i = 0; i < 3; ++i) {
-        TileDma<D>::request(rq_ptr(), x_ws, slot_wave(i));
+        Dma::request(rq_ptr(), x_ws, slot_wave(i));
         rq_advance();
       }
       const float bf = (float)p.block;
@@ -777,7 +780,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
           if (++p_group > (min(32 * p_chunk + 32, p.nb) - 1) / p.group) { ++p_chunk; p_part = -1; }
         }
       }
-      TileDma<D>::request(src, x_ws, slot_wave(issued));
+      Dma::request(src, x_ws, slot_wave(issued));
       ++issued;
       return desc;
     };
@@ -840,7 +843,7 @@ __global__ void __launch_bounds__(teams_of(PART) * kWaves * 64, 2) attn_kernel(A
   float l_tot = half_swap_sum(w.l);
   if constexpr (TEAMS == 2) {  // the second team leaves its result in its own ring (as large as that), m and l in the other's
     typedef float f32x4 __attribute__((ext_vector_type(4)));
-    static_assert(kWaves * 64 * D / 2 * sizeof(float) == kRing * TILE_BYTES, "half of D value columns per lane");
+    static_assert(WAVES * 64 * D / 2 * sizeof(float) == kRing * TILE_BYTES, "half of D value columns per lane");
     f32x4* const xo = reinterpret_cast<f32x4*>(ring + kRing * TILE_BYTES) + wave * (D / 8) * 64 + lane;
     float2* const xml = reinterpret_cast<float2*>(ring) + wave * 64 + lane;
     ring_barrier<NI>(0);  // no load into a ring is in flight and nobody reads one any more
@@ -948,7 +951,7 @@ __global__ void __launch_bounds__(256) merge_kernel(AttnParams p) {
 
 template <int D, int MODE, bool MULTI, int PART>
 hipError_t launch(const AttnParams& p, int grid, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_kernel<D, MODE, MULTI, PART>), dim3(grid), dim3(teams_of(PART) * kWaves * 64), 0, stream, p);
+  hipLaunchKernelGGL((attn_kernel<D, MODE, MULTI, PART>), dim3(grid), dim3(teams_of(PART) * waves_of(PART) * 64), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -956,6 +959,7 @@ template <int D, int MODE, bool MULTI>
 hipError_t launch_part(const AttnParams& p, int grid, hipStream_t stream) {
   if constexpr (MODE == 0) {
     if (p.teams) return launch<D, MODE, MULTI, kTeams>(p, grid, stream);
+    if (p.wide) return launch<D, MODE, MULTI, kWide>(p, grid, stream);
   } else {
     if (p.n_slices > 1) return launch<D, MODE, MULTI, kSliced>(p, grid, stream);
   }
@@ -974,7 +978,8 @@ hipError_t launch_d(const AttnParams& p, bool sparse, int grid, hipStream_t stre
 
 hipError_t pasa_launch_attn(AttnParams p, bool sparse, int d, hipStream_t stream) {
   p.c = p.scale * kLog2e;
-  p.q_tiles = (p.n + 127) / 128;  // 128 query rows per workgroup
+  const int tile = p.wide ? 256 : 128;  // query rows per workgroup
+  p.q_tiles = (p.n + tile - 1) / tile;
   p.q_tiles_per_xcd = (p.q_tiles + kXcds - 1) / kXcds;
   int grid = p.bh * kXcds * p.q_tiles_per_xcd;
   if (p.n_slices > 1) {  // persistent: two workgroups per CU (64 KB of LDS each), work queues per XCD

@@ -65,6 +65,21 @@ def test_dense_in_two_teams_against_one_walk_per_query_tile(P, n, d):
     np.testing.assert_allclose(two_lse.cpu().numpy(), one_lse[:32].cpu().numpy(), atol=1e-3)
 
 
+@pytest.mark.parametrize("n,d", [(1025, 128), (1089, 64), (1280, 128), (1281, 64), (1537, 128), (2047, 128), (2048, 64)])
+def test_dense_in_wide_workgroups(P, n, d):
+    """32 heads take workgroups of 256 query rows, 33 those of 128 (one wide workgroup more than an XCD has compute units): a row meets its
+    keys in the same order in both.  Last wide tiles of 1, 65, 128, 255 and 256 rows, last key tiles of 1, 63 and 64 keys, odd and even numbers of them"""
+    q2, k2, v2 = _inputs((1, 1, n), 2, d, seed=n)
+    q, k, v = (torch.cat([t] * 17, dim=1)[:, :33].contiguous() for t in (q2, k2, v2))
+    wide, wide_lse = P.attn_dense_ref(q[:, :32], k[:, :32], v[:, :32], P.Shape.of(q[:, :32]), want_lse=True)
+    narrow, narrow_lse = P.attn_dense_ref(q, k, v, P.Shape.of(q), want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(wide, narrow[:, :32]) and torch.equal(wide_lse, narrow_lse[:32])
+    ref, ref_lse = oracle.dense_attention(to_f64(q2), to_f64(k2), to_f64(v2), return_lse=True)
+    assert_close(to_f64(wide[:, 30:]), ref, what=f"wide dense n={n} d={d}")
+    np.testing.assert_allclose(wide_lse[30:32].cpu().numpy(), ref_lse, atol=2e-2)
+
+
 def test_dense_respects_strides_and_scale(P):
     q, k, v = _inputs((2, 9, 10), 2, 128)
     B, H, n, d = q.shape
