@@ -356,20 +356,21 @@ class Cold:
         return [".subsection 1"] + self.lines + [".subsection 0"] if self.lines else []
 
 
-def growth(cold, flag, corr):
+def growth(cold, flag, corr, also=()):
     """after max_stream: where the maximum grew for some lane, m, l and the factor `corr` for the accumulators; `flag` is not
-    zero then.  (The lane's own maximum decides, see raise_max.)"""
+    zero then (without a flag: corr is 1 where there is nothing to do).  (The lane's own maximum decides, see raise_max.)"""
     t0, t1, t2 = (vr(FS_T + i) for i in range(3))
     body = [f"v_mov_b32 {t1}, {t0}", "s_nop 1", f"v_permlane32_swap_b32 {t0}, {t1}", "s_nop 0",
             f"v_max3_f32 {t1}, %[m], {t0}, {t1}", f"v_sub_f32 {t2}, %[m], {t1}", f"v_exp_f32 {corr}, {t2}",
-            f"v_mov_b32 %[m], {t1}", "s_nop 0", f"v_mul_f32 %[l], %[l], {corr}"]
-    return tuple([f"v_cmp_gt_f32 vcc, {t0}, %[m]", f"s_mov_b64 {flag}, vcc"] + cold.block("s_cbranch_vccnz", body))
+            f"v_mov_b32 %[m], {t1}", "s_nop 0", f"v_mul_f32 %[l], %[l], {corr}"] + [f"v_mul_f32 {r}, {r}, {corr}" for r in also]
+    note = f"s_mov_b64 {flag}, vcc" if flag else f"v_mov_b32 {corr}, 1.0"
+    return tuple([f"v_cmp_gt_f32 vcc, {t0}, %[m]", note] + cold.block("s_cbranch_vccnz", body))
 
 
 def pending(cold, flag, corr, n_o, nop):
-    """accumulators *= corr if flag is not zero"""
-    return tuple([f"s_cmp_lg_u64 {flag}, 0"] +
-                 cold.block("s_cbranch_scc1", [nop] + [f"v_mul_f32 {vr(FS_O + i)}, {vr(FS_O + i)}, {corr}" for i in range(n_o)]))
+    """accumulators *= corr if flag is not zero (without a flag: if corr is not 1 in some lane)"""
+    test = [f"s_cmp_lg_u64 {flag}, 0"] if flag else [f"v_cmp_neq_f32 vcc, 1.0, {corr}"]
+    return tuple(test + cold.block("s_cbranch_scc1" if flag else "s_cbranch_vccnz", [nop] + [f"v_mul_f32 {vr(FS_O + i)}, {vr(FS_O + i)}, {corr}" for i in range(n_o)]))
 
 
 def cost(item):
@@ -534,6 +535,375 @@ def pipe_functions():
         emit("// End of a run: P V of the tile in V slot 2 par + 1.\n",
              f"pipe_end(int par, const uint32_t (&va)[{2 * nt}], {state}, float c)", "", both_parities("pe", lambda par: pipe_end(D, par)),
              o_ops(nt) + ml + [sb] + pa + carry, vin + cin + par_in, list(s0) + list(p1) + rest)
+    return "".join(out)
+
+
+# ---- half of a pipelined step, for workgroups whose groups of waves work on tiles of their own (quad passes, d = 128) ----
+# Half `par` of a step: logits of 32 keys of the group's next tile -> S[par], P V of 32 keys of its current tile with P[par], and the
+# softmax of S[1 - par] -> P[1 - par] in between.  A run of steps starts with P[0], S[1] of its first tile (quad_start0/1) and ends
+# with P V alone (quad_end0/1, which leave nothing pending).  sk, sv: LDS addresses of the group's K and V half slots; kl, vl: the
+# lane's offsets of the fragments in a half slot.
+# Layout of a half slot: blocks of four rows (one tile-load instruction), padded by 16 bytes so that the four blocks that
+# a row fragment touches in one go start four banks apart; inside a row the 16-byte chunk c lies at c ^ ((row & 3) << 2).  So the
+# contraction steps 2 j and 2 j + 1 of a row fragment are 32 bytes apart and a column fragment's rows further down an immediate
+# offset away: four lane addresses each (eight additions per half step instead of sixteen).
+QUAD_BLOCK = 1040               # bytes of a padded block of four rows
+QUAD_HALF = 8 * QUAD_BLOCK
+QUAD_SLOTS = 18                 # half slots of the ring
+QUAD_D = 128
+
+
+QUAD_RUNS = ((1, 1), (2, 2), (3, 1), (4, 1), (3, 3), (4, 4))  # tiles of even and odd steps
+
+
+def quad_depth(width):
+    """batches of `width` half tiles that the ring holds"""
+    return QUAD_SLOTS // width
+
+
+def quad_loads(kind, a, t, f):
+    """instructions that fetch MFMA operand f: row fragment of step a ("k"), column fragment of 16-row step a, column tile t ("v")"""
+    if kind == "k":
+        return [f"ds_read_b128 {F(f)}, {vr(FS_A + a // 2)}{off(32 * (a % 2))}"]
+    return [f"ds_read_b64_tr_b16 {Flo(f)}, {vr(FS_A + 4 + t)}{off(4 * QUAD_BLOCK * a)}",
+            f"ds_read_b64_tr_b16 {Fhi(f)}, {vr(FS_A + 4 + t)}{off(4 * QUAD_BLOCK * a + 2 * QUAD_BLOCK)}"]
+
+
+def quad_run(mf, before, after, prologue, dmas=(), early=()):
+    """dmas: (operand of the lane offsets, operand of the base, LDS offset), in the shadows from the second MFMA on; early: instructions
+    before the fragment fetches (LDS reads among them have landed by the first MFMA)"""
+    lines, issued, nbuf = list(early), [], 6
+    kinds = {m["load"][0] for m in mf}
+    if "k" in kinds:
+        lines += [f"v_add_u32 {vr(FS_A + j)}, %[sk], %[kl{j}]" for j in range(4)]
+    if "v" in kinds:
+        lines += [f"v_add_u32 {vr(FS_A + 4 + j)}, %[sv], %[vl{j}]" for j in range(4)]
+
+    def issue(k):
+        ls = quad_loads(*mf[k]["load"], k % nbuf)
+        lines.extend(ls)
+        issued.append(len(ls))
+
+    dmas = list(dmas)
+    n = len(mf)
+    for k in range(min(nbuf, n)):
+        issue(k)
+    lines += list(prologue)
+    for k in range(n):
+        outstanding = sum(issued[k + 1:])
+        assert outstanding <= 15
+        lines.append(f"s_waitcnt lgkmcnt({outstanding})")
+        lines += before.get(k, [])
+        m = mf[k]
+        lines.append(f"{MFMA} {m['acc']}, {F(k % nbuf)}, {m['b']}, {'0' if m['first'] else m['acc']}")
+        load = dmas.pop(0) if dmas and k > 0 else None
+        if load:
+            lines.append(f"s_add_u32 m0, %[ld], {hex(load[2])}")
+        if k + nbuf < n:
+            issue(k + nbuf)
+        elif load:
+            lines.append("s_nop 0")
+        if load:
+            lines.append(f"global_load_lds_dwordx4 {load[0]}, {load[1]}")
+        lines += after.get(k, [])
+    assert not dmas
+    return lines
+
+
+def quad_parts(par):
+    D = QUAD_D
+    ns, nt = D // 16, D // 32
+    Sx, Sy = (FS_S0, FS_S1) if par == 0 else (FS_S1, FS_S0)
+    Px, Py = (FS_P0, FS_P1) if par == 0 else (FS_P1, FS_P0)
+    qk = [dict(acc=vr(Sx, 16), first=(st == 0), b=f"%[q{st}]", load=("k", st, 0)) for st in range(ns)]
+    pv = [dict(acc=vr(FS_O + 16 * t, 16), first=False, b=vr(Px + 4 * ks, 4), load=("v", ks, t)) for ks in range(2) for t in range(nt)]
+    grow = lambda cold: growth(cold, None, "%[corr]")
+    pend = lambda cold, nop: list(pending(cold, None, "%[corr]", 16 * nt, nop))
+    return qk, pv, Sy, Py, grow, pend
+
+
+def quad_both(cold, par, dmas=(), early=(), first=()):
+    """first: instructions in the shadow of the first MFMA"""
+    qk, pv, Sy, Py, grow, pend = quad_parts(par)
+    after = {0: list(first), 1: pend(cold, "s_nop 3")}
+    pour(after, len(qk + pv), [grow(cold)] + exp_stream(Sy, Py), first=1)
+    return quad_run(qk + pv, {}, after, max_stream(Sy), dmas, early)
+
+
+def quad_steady(kind, cold):
+    """steps of a run with na and nb tiles in turn, %[count] > 0 times one (na = nb) or two of them.  A half step of half p requests the
+    batch depth - 1 further on, which belongs to half p of its step if depth is odd and to the other half if it is even; the
+    tiles of a step (byte offsets xk, those of the step before in xv) come from the step list (lane address la) when its
+    half 0 is requested.  ko, vo: where in a batch the group's K and V half tiles lie; for the step after the next they come from the list's
+    group bits (lane address lc) in half 1: one tile is everybody's, of four every group has the one with its number."""
+    na, nb = QUAD_RUNS[kind]
+    width = na + nb
+    depth, batch = quad_depth(width), width * QUAD_HALF
+    lead = depth - 1
+    n_of = lambda t: (na, nb)[t % 2]
+    lines = [f".Lqt{kind}_%=:"]
+    for s in range(1 if na == nb else 2):  # step s: P V of its tiles, logits of step s + 1
+        for par in range(2):
+            half, tr = (par + lead) % 2, s + 1 + (par + lead) // 2  # the requested batch: K of step tr, V of step tr - 1
+            nk, nv = n_of(tr), n_of(tr - 1)
+            lines += [f"s_waitcnt vmcnt({(depth - 2) * width}) lgkmcnt(0)", "s_barrier", "s_add_u32 %[sk], %[sb], %[ko]", "s_add_u32 %[sv], %[sb], %[vo]"]
+            early, first = [], []
+            if half == 0:
+                early += [f"ds_read_u16 %[w{j}], %[la]{off(2 * j)}" for j in range(nk)]
+                first += [f"v_mov_b32 %[xv{j}], %[xk{j}]" for j in range(nv)]
+                for j in range(nk):
+                    first += [f"v_and_b32 %[w{j}], 0xfff, %[w{j}]", f"v_mul_lo_u32 %[w{j}], %[w{j}], %[tb]"]
+                first += [f"v_add_u32 %[xk{j}], %[x], %[w{j}]" for j in range(nk)] + [f"v_add_u32 %[la], {2 * nk}, %[la]"]
+            n2 = n_of(s + 2)
+            if par == 1:
+                if n2 in (2, 3):
+                    early += [f"ds_read_u16 %[e{j}], %[lc]{off(2 * j)}" for j in range(n2 - 1)]
+                    first += [f"v_readfirstlane_b32 %[u{j}], %[e{j}]" for j in range(n2 - 1)] + [f"v_add_u32 %[lc], {2 * (n2 + (n_of(s + 3) if na != nb else 0))}, %[lc]"]
+                    if n2 == 3:
+                        first += ["s_bitcmp1_b32 %[u1], %[bit]", "s_cselect_b32 %[u1], 1, 2", f"s_mul_i32 %[u1], %[u1], {QUAD_HALF}"]
+                    else:
+                        first += [f"s_movk_i32 %[u1], {QUAD_HALF}"]
+                    first += ["s_bitcmp1_b32 %[u0], %[bit]", "s_cselect_b32 %[u0], 0, %[u1]"]
+                else:
+                    first += ["s_mov_b32 %[u0], 0" if n2 == 1 else "s_mov_b32 %[u0], %[go]"]
+            dmas = [(f"%[xk{j}]", f"%[kb{half}]", j * QUAD_HALF) for j in range(nk)] + \
+                   [(f"%[xv{j}]", f"%[vb{half}]", (nk + j) * QUAD_HALF) for j in range(nv)]
+            stream = quad_both(cold, par, dmas, early, first)
+            # the next batch, and the slot of this one for the next request
+            lines += stream + [f"s_add_u32 %[ld], %[sb], %[wp]", f"s_add_u32 %[sb], %[sb], {batch}", f"s_cmp_eq_u32 %[sb], %[end]",
+                               f"s_cselect_b32 %[sb], %[ring], %[sb]"]
+            if par == 1:
+                lines += [f"s_add_u32 %[vo], %[ko], {n2 * QUAD_HALF}", "s_mov_b32 %[ko], %[u0]"]
+    return lines + ["s_sub_u32 %[count], %[count], 1", "s_cmp_lg_u32 %[count], 0", f"s_cbranch_scc1 .Lqt{kind}_%="]
+
+
+def quad_all_steady():
+    cold = Cold("qy")
+    lines = ["s_cmp_eq_u32 %[count], 0", "s_cbranch_scc1 .Lqtdone_%="]
+    for kind in range(len(QUAD_RUNS)):
+        lines += [f"s_cmp_lg_u32 %[kind], {kind}", f"s_cbranch_scc1 .Lqtnot{kind}_%="] + quad_steady(kind, cold) + ["s_branch .Lqtdone_%=", f".Lqtnot{kind}_%=:"]
+    return lines + [".Lqtdone_%=:"] + cold.text()
+
+
+def quad_if_active(tag, lines):
+    return ["s_cmp_eq_u32 %[active], 0", f"s_cbranch_scc1 .L{tag}skip_%="] + lines + [f".L{tag}skip_%=:"]
+
+
+def quad_start(par):
+    qk, pv, Sy, Py, grow, pend = quad_parts(par)
+    if par == 0:
+        return quad_if_active("qs0", quad_run(qk, {}, {}, []) + [NOP_AFTER])
+    cold = Cold("qs")
+    after = {}
+    pour(after, len(qk), [grow(cold)] + exp_stream(Sy, Py))
+    return quad_if_active("qs1", quad_run(qk, {}, after, max_stream(Sy)) + [NOP_AFTER]) + cold.text()
+
+
+def quad_plain(par):
+    cold = Cold(f"qb{par}")
+    return quad_if_active(f"qb{par}", quad_both(cold, par)) + cold.text()
+
+
+def quad_end(par):
+    qk, pv, Sy, Py, grow, pend = quad_parts(par)
+    cold = Cold(f"qe{par}")
+    after = {}
+    if par == 0:
+        pour(after, len(pv), [grow(cold)] + exp_stream(Sy, Py))
+        lines = quad_run(pv, {}, after, pend(cold, NOP_AFTER) + max_stream(Sy) + ["s_nop 1"])
+    else:
+        lines = quad_run(pv, {}, {}, pend(cold, NOP_AFTER) + ["s_nop 1"])
+    return quad_if_active(f"qe{par}", lines + [NOP_AFTER]) + cold.text()
+
+
+def quad_functions():
+    D = QUAD_D
+    ns, nt = D // 16, D // 32
+    out = ["// What the half steps of the quad passes hand on (see PipeState).\n"
+           "struct QuadState {\n  f32x16 s0, s1;\n  bf16x8 p0[2], p1[2];\n  float corr;  // factor the accumulators still have to be multiplied by\n};\n\n"
+           f"constexpr int kQuadBlock = {QUAD_BLOCK};  // bytes of a padded block of four rows of a half slot\n"
+           f"constexpr int kQuadSlots = {QUAD_SLOTS};  // half slots of the ring\n"
+           f"constexpr int kQuadKinds = {len(QUAD_RUNS)};  // kinds of runs: tiles of their even and odd steps\n"
+           f"constexpr int kQuadEven[] = {{{', '.join(str(r[0]) for r in QUAD_RUNS)}}}, kQuadOdd[] = {{{', '.join(str(r[1]) for r in QUAD_RUNS)}}};\n\n"]
+    all_state = ['"+{v[168:183]}"(st.s0)', '"+{v[184:199]}"(st.s1)'] + [f'"+{{v[{200 + 4 * k}:{203 + 4 * k}]}}"(st.p0[{k}])' for k in range(2)] + \
+        [f'"+{{v[{208 + 4 * k}:{211 + 4 * k}]}}"(st.p1[{k}])' for k in range(2)] + ['[corr] "+v"(st.corr)']
+    kin = [f'[kl{j}] "v"(kl[{j}])' for j in range(4)] + q_inputs(D)
+    vin = [f'[vl{j}] "v"(vl[{j}])' for j in range(4)]
+    cin, skin, svin, act = ['[c] "s"(c)'], ['[sk] "s"(sk)'], ['[sv] "s"(sv)'], ['[active] "s"(active)']
+    ml = ['[m] "+v"(m)', '[l] "+v"(l)']
+    clob = ", ".join([f'"v{r}"' for r in range(FS_A, 256)] + ['"memory"', '"scc"', '"vcc"', '"m0"'])
+    qargs = f"const uint32_t (&kl)[4], const bf16x8 (&q)[{ns}]"
+    oargs = f"f32x16 (&o)[{nt}], float& m, float& l, QuadState& st, float c"
+
+    def emit(comment, head, pre, lines, outs, ins):
+        text = "\n".join(f'      "{l}\\n\\t"' for l in lines)
+        out.append(f"{comment}PASA_DEVICE void {head} {{\n{pre}  asm volatile(\n{text}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n"
+                   f"      : {clob});\n}}\n\n")
+
+    for par in range(2):
+        emit(f"// First step of a run, half {par} (active = 0: nothing).\n",
+             f"quad_start{par}(int active, uint32_t sk, {qargs}, float& m, float& l, QuadState& st, float c)", "",
+             quad_start(par), ml + all_state, kin + cin + skin + act)
+        emit(f"// Step of a run, half {par} (active = 0: nothing).\n",
+             f"quad_half{par}(int active, uint32_t sk, uint32_t sv, {qargs}, const uint32_t (&vl)[4], {oargs})", "",
+             quad_plain(par), o_ops(nt) + ml + all_state, kin + vin + cin + skin + svin + act)
+        emit(f"// Last step of a run, half {par} (active = 0: nothing).\n", f"quad_end{par}(int active, uint32_t sv, const uint32_t (&vl)[4], {oargs})", "",
+             quad_end(par), o_ops(nt) + ml + all_state, vin + cin + svin + act)
+    tiles = [f'[{w}{j}] "+v"(t.{w}[{j}])' for w in ("xk", "xv") for j in range(4)] + ['[la] "+v"(t.la)', '[lc] "+v"(t.lc)'] + \
+        [f'[w{j}] "=&v"(w[{j}])' for j in range(4)] + [f'[e{j}] "=&v"(e[{j}])' for j in range(2)] + \
+        [f'[u{j}] "=&s"(u[{j}])' for j in range(2)] + ['[sk] "=&s"(sk)', '[sv] "=&s"(sv)'] + \
+        [f'[{v}] "+s"(t.{v})' for v in ("count", "sb", "ld", "ko", "vo")]
+    dma = ['[x] "v"(x)', '[tb] "s"(tb)', '[kb0] "s"(kb0)', '[kb1] "s"(kb1)', '[vb0] "s"(vb0)', '[vb1] "s"(vb1)', '[wp] "s"(wp)',
+           '[ring] "s"(ring)', '[end] "s"(end)', '[kind] "s"(kind)', '[bit] "s"(bit)', '[go] "s"(go)']
+    out.append("// What quad_steady works on: steps to do; LDS addresses of the first batch and of the wave's part of the batch before it; places of\n"
+               "// the group's K and V half tiles in a batch; tiles requested last and lane addresses in the step list (see gen_mfma_pipes.py).\n"
+               "struct QuadSteady {\n  int count;\n  uint32_t sb, ld, ko, vo;\n  uint32_t xk[4], xv[4], la, lc;\n};\n\n")
+    emit("// t.count times the steps of a run of some kind (quad_steady in gen_mfma_pipes.py), with their barriers; every half step requests the wave's part of the batch that takes the slots of\n"
+         "// the batch before it.  ring, end: LDS addresses of the first and past the last batch; wp: the wave's part of a half slot; x, tb: byte offset\n"
+         "// of the lane in it, bytes of a tile; kb0, kb1, vb0, vb1: K and V and the same 32 rows further down; bit: of the group in a list entry; go: place of the\n"
+         "// group's half tile among four.\n",
+         f"quad_steady(int kind, uint32_t ring, uint32_t end, uint32_t wp, uint32_t bit, uint32_t go, {qargs}, const uint32_t (&vl)[4],\n"
+         f"                             {oargs}, const void* kb0, const void* kb1, const void* vb0, const void* vb1,\n"
+         f"                             uint32_t x, uint32_t tb, QuadSteady& t)",
+         "  uint32_t w[4], e[2], u[2], sk, sv;\n", quad_all_steady(), o_ops(nt) + ml + all_state + tiles, kin + vin + cin + dma)
+    return "".join(out)
+
+
+# ---- approximation of the unselected blocks in the quad kernel: a chunk of 32 key blocks per step ----
+# On their own the parts of a chunk leave the matrix cores idle during its softmax, and with one workgroup on a compute unit nobody else
+# uses them.  So a step takes O += VS^T a and the first-order term of chunk c, and the logits and the weights a of chunk c + 1 in the
+# shadow of the 32 MFMAs of the first-order term:
+#   O += VS(c)^T a(c);  Z = Kbar(c + 1) Q^T;  W = (scale Hg)^T Q^T, 32 rows at a time, O += A W;  softmax of Z -> a(c + 1), A(c + 1)
+# kind 0: that; 1: the group goes on beyond chunk c (no first-order term yet: the weights add up); 2: no next chunk.
+# Registers: Z v[152:167], W v[168:199] (two of the four 32-row parts at a time), mask temporaries v[208:211], the rest as elsewhere.  The
+# factor for the accumulators where chunk c + 1 raises the maximum (corr) is applied at the beginning of the next step.
+FS_Z, FS_U = 152, 208
+
+
+def approx_weights():
+    """items for the logits v[Z:Z+15]: weights and their sums (see stats_step for the mask): P^T -> P0, l += b sum, T6 = sum over both lanes"""
+    z, u = (lambda i: vr(FS_Z + i)), (lambda i: vr(FS_U + i % 4))
+    t1, t4, t5, t6, t7 = (vr(FS_T + i) for i in (1, 4, 5, 6, 7))
+    out = [f"v_lshrrev_b32 {t5}, %[sh], %[unsel]"]
+    for i in range(21):  # software pipeline over the 16 elements
+        if i < 16:
+            out += [f"v_fma_f32 {z(i)}, {z(i)}, %[c], -%[m]", f"v_bfe_i32 {u(i)}, {t5}, {8 * (i // 4) + i % 4}, 1"]
+        if 1 <= i <= 16:
+            out.append(f"v_exp_f32 {z(i - 1)}, {z(i - 1)}")
+        e = i - 3
+        if 0 <= e < 16:
+            out.append(f"v_and_b32 {z(e)}, {z(e)}, {u(e)}")
+        e = i - 4
+        if 0 <= e < 16:
+            if e == 1:
+                out.append(f"v_add_f32 {t4}, {z(0)}, {z(1)}")
+            elif e == 3:
+                out.append(f"v_add_f32 {t7}, {z(2)}, {z(3)}")
+            elif e > 3:
+                out.append(f"v_add_f32 {t4 if e % 2 == 0 else t7}, {t4 if e % 2 == 0 else t7}, {z(e)}")
+            if e % 2 == 1:
+                out.append(f"v_cvt_pk_bf16_f32 {vr(FS_P0 + e // 2)}, {z(e - 1)}, {z(e)}")
+    return out + [f"v_add_f32 {t4}, {t4}, {t7}", "s_nop 0", f"v_fmac_f32 %[l], %[bf], {t4}", f"v_mov_b32 {t1}, {t4}",
+                  ("s_nop 1", f"v_permlane32_swap_b32 {t4}, {t1}", "s_nop 0"), f"v_add_f32 {t6}, {t4}, {t1}"]
+
+
+def approx_run(mf, after, prologue):
+    """MFMA k of `mf` with its operand fetch issued six MFMAs ahead; load: (tile operand, step, offset) of a row fragment or
+    ("v", 16-row step, column tile); the lane addresses of a tile are made when its first fragment is fetched"""
+    lines, issued, nbuf, tile = [], [], 6, [None]
+
+    def issue(k):
+        f = k % nbuf
+        kind, a, b = mf[k]["load"]
+        if kind != tile[0]:
+            tile[0] = kind
+            if kind == "v":
+                for t in range(1, 4):
+                    lines.append(f"v_xor_b32 {vr(FS_A + 2 * t - 2)}, {hex(t << 6)}, %[av0]")
+                    lines.append(f"v_xor_b32 {vr(FS_A + 2 * t - 1)}, {hex(t << 6)}, %[av1]")
+            else:
+                lines.extend(f"v_xor_b32 {vr(FS_A + st - 1)}, {hex(st << 5)}, %[{kind}]" for st in range(1, 8))
+        if kind == "v":
+            a0, a1 = ("%[av0]", "%[av1]") if b == 0 else (vr(FS_A + 2 * b - 2), vr(FS_A + 2 * b - 1))
+            lines.append(f"ds_read_b64_tr_b16 {Flo(f)}, {a0}{off(a * 32 * QUAD_D)}")
+            lines.append(f"ds_read_b64_tr_b16 {Fhi(f)}, {a1}{off(a * 32 * QUAD_D)}")
+            issued.append(2)
+        else:
+            lines.append(f"ds_read_b128 {F(f)}, {f'%[{kind}]' if a == 0 else vr(FS_A + a - 1)}{off(b)}")
+            issued.append(1)
+
+    n = len(mf)
+    for k in range(min(nbuf, n)):
+        issue(k)
+    lines += list(prologue)
+    for k in range(n):
+        outstanding = sum(issued[k + 1:])
+        assert outstanding <= 15
+        m = mf[k]
+        lines += [f"s_waitcnt lgkmcnt({outstanding})", f"{MFMA} {m['acc']}, {F(k % nbuf)}, {m['b']}, {'0' if m['first'] else m['acc']}"]
+        if k + nbuf < n:
+            issue(k + nbuf)
+        lines += after.get(k, [])
+    return lines
+
+
+def approx_body(kind, cold):
+    """kind: "both", "more" (no first-order term yet), "last" (no next chunk), "start" (nothing but the first chunk's weights)"""
+    D = QUAD_D
+    pv = [dict(acc=vr(FS_O + 16 * t, 16), first=False, b=vr(FS_P0 + 4 * ks, 4), load=("v", 2 + ks, t)) for ks in range(2) for t in range(4)]
+    qk = [dict(acc=vr(FS_Z, 16), first=(st == 0), b=f"%[q{st}]", load=("ak", st, 0)) for st in range(8)]
+    hg = [dict(acc=vr(FS_S0 if k % 2 == 0 else FS_S1, 16), first=(st == 0), b=f"%[q{st}]", load=(f"ah{k // 2}", st, (k % 2) * 64 * D))
+          for k in range(4) for st in range(8)]
+    corr = "%[corr]"
+    pend = [] if kind == "start" else list(pending(cold, None, corr, 64, NOP_AFTER)) + ["s_nop 1"]
+    update = lambda k: [f"v_fmac_f32 {vr(FS_O + 16 * k + r)}, %[A], {vr((FS_S0 if k % 2 == 0 else FS_S1) + r)}" for r in range(16)]
+    mf = {"both": pv + qk + hg, "more": pv + qk, "last": pv + hg, "start": qk}[kind]
+    n, after, tail = len(mf), {}, []
+    if kind in ("both", "last"):
+        h0 = n - 32
+        for k in range(3):
+            spread(after, h0 + 8 * (k + 1) + 1, h0 + 8 * (k + 2) - 1, update(k))
+        tail += [NOP_AFTER] + update(3)
+    if kind != "last":
+        grow = growth(cold, None, corr, also=["%[A]"] if kind == "more" else [])
+        z0 = n if kind in ("more", "start") else 18  # Z is complete
+        items = max_stream(FS_Z) + [grow] + approx_weights()
+        if kind == "both":
+            pour(after, n, items, first=z0, begin=z0 / n, end=(n - 1) / n)
+        else:
+            tail += [NOP_AFTER] + flat(items)
+        tail.append(f"v_add_f32 %[A], %[A], {vr(FS_T + 6)}" if kind == "more" else f"v_mov_b32 %[A], {vr(FS_T + 6)}")
+    return approx_run(mf, after, pend) + tail
+
+
+def approx_functions():
+    D = QUAD_D
+    ns, nt = D // 16, D // 32
+    clob = ", ".join([f'"v{r}"' for r in list(range(FS_Z, FS_P0)) + list(range(FS_P1, 256))] + ['"memory"', '"scc"', '"vcc"', '"m0"'])
+    pa = lambda mode: [f'"{mode}{{v[{200 + 4 * k}:{203 + 4 * k}]}}"(p[{k}])' for k in range(2)]
+    out = []
+    cold = Cold("as")
+    lines = approx_body("start", cold) + [NOP_AFTER] + cold.text()
+    text = lambda ls: "\n".join(f'      "{l}\\n\\t"' for l in ls)
+    common = q_inputs(D) + ['[c] "s"(c)', '[unsel] "s"(unsel)', '[sh] "v"(sh)', '[bf] "s"(bf)']
+    def emit(comment, head, ls, outs, ins):
+        out.append(f"{comment}PASA_DEVICE void {head} {{\n  asm volatile(\n{text(ls)}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n      : {clob});\n}}\n\n")
+    emit("// Weights of the first chunk of 32 existing, full key blocks (statistics tile + row-fragment offset ak): P^T fragments p, their sum A, and the\n"
+         "// factor corr that the accumulators still have to be multiplied by.  unsel, sh, bf: see stats_step.\n",
+         f"approx_start(uint32_t ak, const bf16x8 (&q)[{ns}], bf16x8 (&p)[2], float& m, float& l, float& corr, float& A, float c,\n"
+         "                              uint32_t unsel, uint32_t sh, float bf)", lines,
+         pa("=&") + ['[m] "+v"(m)', '[l] "+v"(l)', '[corr] "=&v"(corr)', '[A] "=&v"(A)'], ['[ak] "v"(ak)'] + common)
+    cold = Cold("ap")
+    lines = ["s_cmp_eq_u32 %[kind], 0", "s_cbranch_scc0 .Lapother_%="] + approx_body("both", cold) + [".Lapdone_%=:"]
+    far = [".Lapother_%=:", "s_cmp_eq_u32 %[kind], 1", "s_cbranch_scc0 .Laplast_%="] + approx_body("more", cold) + ["s_branch .Lapdone_%=", ".Laplast_%=:"] + \
+        approx_body("last", cold) + [NOP_AFTER, "s_branch .Lapdone_%="]
+    lines += [".subsection 1"] + far + cold.lines + [".subsection 0"]
+    emit("// Step of the approximation (kind 0, 1, 2: see gen_mfma_pipes.py).  ak: statistics tile of the next chunk; av0, av1: of this chunk + column-fragment\n"
+         "// offsets; ah0, ah1: the two halves of the group's matrix; A: weight of the group so far, on return that of the next chunk's.\n",
+         f"approx_step(int kind, uint32_t ak, uint32_t av0, uint32_t av1, uint32_t ah0, uint32_t ah1, const bf16x8 (&q)[{ns}], f32x16 (&o)[{nt}],\n"
+         "                             bf16x8 (&p)[2], float& m, float& l, float& corr, float& A, float c, uint32_t unsel, uint32_t sh, float bf)", lines,
+         o_ops(nt) + pa("+") + ['[m] "+v"(m)', '[l] "+v"(l)', '[corr] "+v"(corr)', '[A] "+v"(A)'],
+         ['[kind] "s"(kind)', '[ak] "v"(ak)', '[av0] "v"(av0)', '[av1] "v"(av1)', '[ah0] "v"(ah0)', '[ah1] "v"(ah1)'] + common)
     return "".join(out)
 
 
@@ -775,6 +1145,8 @@ def gen():
         out.append(asm_block(cols_x_p(D, 4, 0, ni), outs, ins, ("memory", "scc", "m0")))
         out.append("}\n\n")
     out.append(pipe_functions())
+    out.append(quad_functions())
+    out.append(approx_functions())
     for D in (128, 64):
         ns, nt = D // 16, D // 32
         ni = (64 // (1024 // (2 * D))) // 4
@@ -809,14 +1181,14 @@ def gen():
         clob = ", ".join([f'"v{r}"' for r in range(168, 200)] + [f'"v{r}"' for r in range(216, 256)] +
                          ['"memory"', '"scc"', '"vcc"', '"m0"'])
         out.append(f"  asm volatile(\n{text}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n      : {clob});\n}}\n\n")
-    for D, waves in ((128, 4), (64, 4)):
+    for D, waves in ((128, 4), (128, 8), (64, 4), (64, 8)):
         ns, nt = D // 16, D // 32
         ni = tile_loads(D, waves)
         dma_ins = ['[sb] "s"(sb)', '[ls] "s"(ls)'] + [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
         out.append(f"// Zeroth-order step of the approximation for a chunk of 32 existing, full key blocks.  ak, av0, av1: the\n"
                    f"// statistics tile's address + row-fragment / column-fragment offsets; unsel: bit x set iff block x of the\n"
                    f"// chunk is NOT selected; sh = 4 * (lane >> 5); bf = tokens per block; A <- sum of the chunk's weights a_j.\n"
-                   f"// One more tile (from sb into the slot at LDS address ls) is requested meanwhile.\n"
+                   f"// One more tile (from sb into the slot at LDS address ls) is requested meanwhile ({waves} waves).\n"
                    f"PASA_DEVICE void stats_step(uint32_t ak, uint32_t av0, uint32_t av1, const bf16x8 (&q)[{ns}], f32x16 (&o)[{nt}],\n"
                    f"                           float& m, float& l, float c, uint32_t unsel, uint32_t sh, float bf, float& A,\n"
                    f"                           const void* sb, const uint32_t (&x)[{ni}], uint32_t ls) {{\n")

@@ -179,6 +179,19 @@ bool dense_wide(const pasa_shape_t* s) {
   return 62 * wide <= 32 * narrow;
 }
 
+// Whether the sparse path takes workgroups of four query blocks of 64 tokens (pasa_quad.hpp) instead of two: they fetch fewer tiles, but plan
+// their steps first (15 us a workgroup, with the starts and ends of its runs of steps).  So the selection has to be long, and the more so the
+// smaller a head: its keys and values are in the L2s then anyway.  Attention alone, us, two / four:
+//   32,760 tokens (x 512 blocks): 12 heads, 77 blocks 1331 / 1383, 179 blocks 2615 / 2620; 47,040: 8 heads, 110: 1898 / 1865, 257: 3844 / 3586;
+//   20 heads, 110: 4628 / 4755; 60,480: 8 heads, 47: 1467 / 1565, 142: 3169 / 3124; 75,600: 5 heads, 59: 1448 / 1453, 177: 3228 / 2982; 20 heads,
+//   59: 5732 / 6006, 177: 12,666 / 12,099; 118,800: 3 heads, 93: 2137 / 2183, 279: 5210 / 4702; 147,600: 6 heads, 115: 6853 / 6688, 346: 16,168 / 13,852
+// Blocks of 128 tokens: 147,600 tokens, 6 heads, 58 blocks 4780 / 4889, 173: 11,014 / 11,338 (not taken).
+bool sparse_quad(const pasa_shape_t* s, int32_t k_sel) {
+  const int nb = num_blocks(s);
+  return s->d == 128 && s->block == 64 && s->kv_slices <= 1 && s->n >= 64 && s->n / 64 <= kQuadMaxTiles && (s->group == 0 || s->group >= 32) && nb >= k_sel &&
+         k_sel >= 100 && (int64_t)k_sel * s->n >= 8000000;
+}
+
 constexpr int kMaxDevices = 64;
 std::atomic<void*> g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each device, null until looked up
 std::mutex g_scratch_mutex;
@@ -460,7 +473,7 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     a.queue = reinterpret_cast<uint32_t*>(base + w.queue);
   }
   a.teams = !sparse && dense_teams(&s);
-  a.wide = !sparse && !a.teams && dense_wide(&s);
+  a.wide = sparse ? sparse_quad(&s, k_sel) : !a.teams && dense_wide(&s);
   return pasa_launch_attn(a, sparse, s.d, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 

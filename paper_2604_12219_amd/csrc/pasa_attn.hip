@@ -45,6 +45,9 @@
 #include "pasa_device.hpp"
 #include "pasa_kernels.hpp"
 #include "pasa_mfma_pipes.hpp"
+#include "pasa_quad.hpp"
+
+#include <type_traits>
 
 namespace {
 
@@ -201,15 +204,7 @@ PASA_DEVICE void first_order_part(uint32_t tile, const LaneOffsets<D>& lo, WaveS
 // i.e. RPI = 1024/(2D) whole tile rows; the XOR swizzle of the LDS layout is applied on the global
 // side (which 16-byte chunk of its row a lane fetches).  Wave w issues instructions w, w+4, ... of a
 // tile; a lane's rows in them are a multiple of 16 apart, so its swizzle is the same in all of them.
-// The loads are written as inline assembly so that the compiler's wait-count insertion does not see
-// them (it would serialise every LDS read behind all pending loads); ordering is by the counted
-// waits in ring_barrier().  A wait count the compiler derives for its own loads can only become
-// stricter by loads it does not know about (loads complete in issue order), never too weak.
-PASA_DEVICE void dma_1k(const void* sbase, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(sbase)
-               : "memory", "m0");
-}
-
+// (dma_1k in pasa_device.hpp)
 template <int D, int WAVES>
 struct TileDma {
   static constexpr int CPR = D / 8;                 // 16-byte chunks per row
@@ -313,10 +308,11 @@ struct BitWalk {
 // 2: sparse, two adjacent 64-token query blocks per workgroup.  MULTI: the group has fewer than 32
 // blocks, so a chunk of 32 blocks intersects several groups and the per-block weights of a chunk have
 // to be kept until all of its group matrices have passed.  PART: kWhole: a workgroup walks all keys of its
-// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two teams of waves; kWide (dense): eight waves, 256 query rows.
-enum : int { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3 };
+// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two teams of waves; kWide (dense): eight waves, 256 query rows; kQuad (sparse):
+// eight waves, four query blocks of 64 tokens (pasa_quad.hpp).
+enum : int { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3, kQuad = 4 };
 constexpr int teams_of(int part) { return part == kTeams ? 2 : 1; }
-constexpr int waves_of(int part) { return part == kWide ? 8 : 4; }  // of a team
+constexpr int waves_of(int part) { return part >= kWide ? 8 : 4; }  // of a team
 template <int D, int MODE, bool MULTI, int PART>
 __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_kernel(AttnParams p) {
   constexpr bool SPARSE = MODE != 0, SLICED = PART == kSliced;
@@ -326,7 +322,12 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   constexpr int TILE_BYTES = 64 * 2 * D;
   constexpr int NI = Dma::NI;
   constexpr int HPARTS = D / 64;  // 64-row tiles per group matrix
-  __shared__ __attribute__((aligned(1024))) char ring[TEAMS * kRing * TILE_BYTES];
+  constexpr bool QUAD = PART == kQuad;
+  static_assert(!QUAD || (D == kQuadDim && MODE == 2 && !MULTI), "");
+  constexpr int GROUPS = QUAD ? kQuadGroups : 1;  // groups of waves with a query block of their own
+  struct PlainShared { __attribute__((aligned(1024))) char ring[TEAMS * kRing * TILE_BYTES]; };
+  __shared__ std::conditional_t<QUAD, QuadShared, PlainShared> shared;
+  char* const ring = shared.ring;
 
   __shared__ int s_item, s_queue;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -427,7 +428,7 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   // MODE 2: waves 0, 1 work for query block 2 qt (row a of the bitmap), waves 2, 3 for block 2 qt + 1
   // (row b).  If the last query tile has no second block, row b := row a; waves 2, 3 then repeat the
   // walk of the first block with all-zero queries (their rows lie beyond n and are never stored).
-  const bool second = MODE == 2 && (wave >> 1);
+  const bool second = MODE == 2 && !QUAD && (wave >> 1);
   const int n_dense_tiles = (n + 63) / 64;
   const bool approx_on = SPARSE && p.group > 0;
   const uint16_t* const st = approx_on ? p.st + (int64_t)bh * p.n_chunks * 64 * D : nullptr;
@@ -436,13 +437,14 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   // (wave-uniform; the divisions run on the vector unit, so the results are moved to scalar registers explicitly)
   const int c_lo = SPARSE ? __builtin_amdgcn_readfirstlane((int)((int64_t)slice * p.n_chunks / p.n_slices)) : 0;
   const int c_hi = SPARSE ? __builtin_amdgcn_readfirstlane((int)((int64_t)(slice + 1) * p.n_chunks / p.n_slices)) : 0;
-  const int qb_a = MODE == 2 ? 2 * qt : qt;
+  const int group = wave / (WAVES / GROUPS);
+  const int qb_a = QUAD ? min(GROUPS * qt + group, p.nb - 1) : MODE == 2 ? 2 * qt : qt;  // (kQuad: the wave's own query block)
   const_u32* const mask_a = SPARSE ? (const_u32*)(p.mask + ((int64_t)bh * p.nb + qb_a) * p.mask_words) : nullptr;
-  const_u32* const mask_b = (MODE == 2 && qb_a + 1 < p.nb) ? mask_a + p.mask_words : mask_a;
+  const_u32* const mask_b = (MODE == 2 && !QUAD && qb_a + 1 < p.nb) ? mask_a + p.mask_words : mask_a;
   const_u32* const mask_row = second ? mask_b : mask_a;  // this wave's own row
   // the first 64 words of the two rows, lane i word c_lo + i: every walk below starts from them
   uint32_t first_a = 0u, first_b = 0u;
-  if constexpr (SPARSE) {
+  if constexpr (SPARSE && !QUAD) {
     if (c_lo + lane < c_hi) {
       first_a = mask_a[c_lo + lane];
       first_b = mask_b[c_lo + lane];
@@ -461,7 +463,7 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   // 33,182 / 32,739, 35,038 / 34,172; 40 of 32,760 4863 / 4632.  The dense path gains nothing by it (22 tiles in one head: 16.2 / 16.7).
   int own_w = 0;
   uint32_t own_sel = 0u;
-  if constexpr (SPARSE) {
+  if constexpr (SPARSE && !QUAD) {
     const int64_t kv_bytes = (int64_t)n * (4 * D);  // of a head
     const bool own_first = MODE == 1 || kv_bytes <= (32 << 20) || kv_bytes * p.bh <= (256 << 20);
     const int w = qb_a >> 5;
@@ -483,12 +485,45 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   auto request = [&](const uint16_t* base, int r0, int sl) { Dma::request(tile_ptr(base, r0), x_kv, slot_wave(sl)); };
 
 
+  // ---------------- exact attention, query blocks of eight waves: see pasa_quad.hpp ----------------
+  if constexpr (QUAD) {
+    load_q();
+    const uint32_t* rows[GROUPS];
+    const uint32_t* const head_rows = p.mask + (int64_t)bh * p.nb * p.mask_words;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g)
+      rows[g] = head_rows + (int64_t)min(GROUPS * qt + g, p.nb - 1) * p.mask_words;  // (beyond the last one: its steps once more, never stored)
+    const int n_whole = p.tail == p.block ? p.nb : p.nb - 1;
+    quad_plan(shared, rows, n_whole, wave, lane);
+    settle_q();
+    QuadPasses(shared, kb, vb, row_bytes, group, wave, lane, p.c).all(w.qf, w.o, w.m, w.l);
+    // the ragged last key block: fetched shifted back, for all groups; weights zero where it is not selected
+    if (n_whole < p.nb) {
+      uint32_t any = 0u;
+#pragma unroll
+      for (int g = 0; g < GROUPS; ++g) any |= rows[g][n_whole >> 5];
+      if ((uniform((int)any) >> (n_whole & 31)) & 1) {
+        const bool mine = (mask_row[n_whole >> 5] >> (n_whole & 31)) & 1u;
+        const int r0 = n_whole * 64;
+        ring_barrier<NI>(0);  // every wave is done with the ring
+        request(kb, r0, 0);
+        request(vb, r0, 1);
+        ring_barrier<NI>(0);
+        f32x16 s0, s1;
+        bf16x8 pf[4];
+        pipes::rows_x_q(slot(0) + lo.k, w.qf, s0, s1);
+        exact_tile_softmax<D>(s0, s1, w, p.c, mine ? r0 - tile_row(r0) : 64, n - tile_row(r0), lane, pf);
+        pipes::cols_x_p64(slot(1) + lo.v[0], slot(1) + lo.v[1], pf, w.o);
+      }
+    }
+  }
+
   // ---------------- exact attention, part 1: tiles that all four waves need ----------------
   // (every tile of the dense path; the blocks of a 128-token query block; with two 64-token query
   // blocks the key blocks that BOTH selected).  One barrier per (K tile, V tile) pair; while a pair is
   // consumed the next pair is on its way into the other two ring slots, requested in the shadow of
   // the first MFMAs.  The order in which key blocks are visited does not matter to an online softmax.
-  {
+  if constexpr (!QUAD) {
     BitWalk<MODE == 2 ? 0 : 3> walk;
     int blk = kNoBlock, sub = 0, dense_next = 0, dense_end = n_dense_tiles;
     if constexpr (SPARSE) {
@@ -604,7 +639,7 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   // buffer cannot be refilled while it is in use, hence two barriers per step: the V tiles of a step
   // are requested after the first and land during the logits and the softmax, the K tiles of the next
   // step are requested after the second and land during P V.
-  if constexpr (MODE == 2) {
+  if constexpr (MODE == 2 && !QUAD) {
     BitWalk<1> only_a;
     BitWalk<2> only_b;
     only_a.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b);
@@ -676,7 +711,59 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   // sequence of tiles (the statistics of a group's chunks, then the HPARTS tiles of its matrix), each handled by
   // one instruction stream that also requests the tile three further down the stream.  (The last chunk of the
   // sequence may be short; it takes the general loop.)
-  if constexpr (SPARSE && !MULTI) {
+  if constexpr (QUAD) {
+    // The same tiles one chunk at a time, one barrier each (pipes::approx_step): value sums and first-order term of the chunk, logits
+    // and weights of the next one.  A ring of nine tiles: four in use, three of the next chunk landing.
+    const int c_fast = approx_on ? p.n_chunks - 1 : 0;
+    if (c_fast > 0) {
+      constexpr int kTiles = 9;
+      const int cpg = (p.group & 31) == 0 ? p.group >> 5 : p.n_chunks;
+      int next_slot = 0;
+      auto take = [&](const uint16_t* tile) -> int {  // requests a workspace tile into the next slot
+        const int sl = next_slot;
+        Dma::request(uniform(tile), x_ws, ring_wave + (uint32_t)(sl * TILE_BYTES));
+        next_slot = sl + 1 == kTiles ? 0 : sl + 1;
+        return sl;
+      };
+      auto at = [&](int sl) -> uint32_t { return ring_base + (uint32_t)(sl * TILE_BYTES); };
+      int rq_c = 0, rq_left = cpg, rq_g = 0;  // the chunk whose step's tiles are requested next: chunks to the end of its group, its group
+      int st_next = 0, h0 = 0, h1 = 0;        // slots of the tiles requested last
+      bool ends = false;
+      auto request_step = [&]() {
+        if (rq_c >= c_fast) return;
+        if (rq_c + 1 < c_fast) st_next = take(st + (int64_t)(rq_c + 1) * 64 * D);
+        ends = rq_left == 1 || rq_c + 1 == c_fast;  // the group's matrix follows its last chunk (or the last one here)
+        if (ends) {
+          h0 = take(hg + (int64_t)rq_g * D * D);
+          h1 = take(hg + ((int64_t)rq_g * D + 64) * D);
+        }
+        ++rq_c;
+        if (--rq_left == 0) { ++rq_g; rq_left = cpg; }
+      };
+      ring_barrier<NI>(0);  // every wave is done with the ring
+      int st_cur = take(st);
+      request_step();
+      const float bf = (float)p.block;
+      const uint32_t sh = (uint32_t)(4 * h);
+      float A, corr;
+      bf16x8 pa[2];
+      ring_barrier<NI>(0);
+      pipes::approx_start(at(st_cur) + lo.k, w.qf, pa, w.m, w.l, corr, A, p.c, ~mask_row[0], sh, bf);
+#pragma unroll 1
+      for (int chunk = 0; chunk < c_fast; ++chunk) {
+        const int cur = st_cur, nxt = st_next, g0 = h0, g1 = h1;
+        const int kind = chunk + 1 == c_fast ? 2 : ends ? 0 : 1;
+        const uint32_t unsel = ~mask_row[min(chunk + 1, p.n_chunks - 1)];
+        ring_barrier<NI>(0);  // the tiles of the step have landed; every wave is done with the step before
+        request_step();
+        st_cur = nxt;
+        pipes::approx_step(uniform(kind), at(nxt) + lo.k, at(cur) + lo.v[0], at(cur) + lo.v[1], at(g0) + lo.k, at(g1) + lo.k, w.qf, w.o, pa, w.m, w.l,
+                           corr, A, p.c, (uint32_t)uniform((int)unsel), sh, bf);
+      }
+      c_slow = c_fast;
+    }
+  }
+  if constexpr (SPARSE && !MULTI && !QUAD) {
     const int c_fast = approx_on ? min(c_hi, p.n_chunks - 1) : 0;
     if (c_lo < c_fast) {
       // chunks per group (a group size that is not a multiple of 32 is the single group that spans all blocks)
@@ -962,6 +1049,8 @@ hipError_t launch_part(const AttnParams& p, int grid, hipStream_t stream) {
     if (p.wide) return launch<D, MODE, MULTI, kWide>(p, grid, stream);
   } else {
     if (p.n_slices > 1) return launch<D, MODE, MULTI, kSliced>(p, grid, stream);
+    if constexpr (D == kQuadDim && MODE == 2 && !MULTI)
+      if (p.wide) return launch<D, MODE, MULTI, kQuad>(p, grid, stream);
   }
   return launch<D, MODE, MULTI, kWhole>(p, grid, stream);
 }

@@ -111,6 +111,16 @@ PASA_DEVICE f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // M index (row of the 32x32 result) held in register `reg` (0..15) of a lane in half-wave h
 PASA_DEVICE int mfma_row(int reg, int h) { return 8 * (reg >> 2) + 4 * h + (reg & 3); }
 
+// One direct global -> LDS load: 64 lanes x 16 bytes land at consecutive LDS addresses from lds_addr on.
+// The loads are written as inline assembly so that the compiler's wait-count insertion does not see
+// them (it would serialise every LDS read behind all pending loads); ordering is by the counted
+// waits before the barriers.  A wait count the compiler derives for its own loads can only become
+// stricter by loads it does not know about (loads complete in issue order), never too weak.
+PASA_DEVICE void dma_1k(const void* sbase, uint32_t voff, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(sbase)
+               : "memory", "m0");
+}
+
 // One row of the selection bitmap from its ascending index list, by one wavefront: clears the row's words, then sets its
 // bits (integer atomic OR inside the row: the result does not depend on the order)
 PASA_DEVICE void mask_row_from_idx(const int32_t* irow, int nb, int k_sel, int mask_words, uint32_t* mrow, int lane) {

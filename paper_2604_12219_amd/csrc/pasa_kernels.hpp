@@ -26,13 +26,14 @@ struct AttnParams {
   // key-range slicing (sparse path): slice s covers chunks [s*n_chunks/n_slices, (s+1)*n_chunks/n_slices)
   int32_t n_slices;      // 1 = off (the attention kernel writes the output itself)
   int32_t teams;         // dense path, 1: the keys of a query tile are halved between two teams of waves of a workgroup
-  int32_t wide;          // dense path, 1: workgroups of 256 query rows
+  int32_t wide;          // 1: workgroups of 256 query rows (dense: one key walk for all of them; sparse: pasa_quad.hpp)
   float* part_o;         // fp32 [BH][n_slices][n][d]: unnormalised partial numerators
   float* part_ml;        // fp32 [BH][n_slices][n][2]: running maximum (log2 units) and partial normaliser
   uint32_t* queue;       // [8] work-item counters, one per XCD (reset by the launcher)
   int32_t items_per_xcd; // filled in by the launcher
 };
 
+constexpr int kQuadMaxTiles = 4096;  // whole key blocks of a head that a workgroup of four query blocks can plan (pasa_quad.hpp)
 // dense (sparse = false) or piecewise sparse attention; d in {64,128}, block in {64,128}
 hipError_t pasa_launch_attn(AttnParams p, bool sparse, int d, hipStream_t stream);
 

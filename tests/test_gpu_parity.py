@@ -447,6 +447,70 @@ def test_blocks_visited_first_are_visited_once(P, n, d, block, kv_slices, keep_o
     np.testing.assert_allclose(lse.cpu().numpy(), res["lse"], atol=2e-2)
 
 
+def _bitmap(chosen):
+    """[BH, nb, nb] booleans -> [BH, nb, words] int32"""
+    bh, nb, _ = chosen.shape
+    bits = torch.nn.functional.pad(chosen, (0, -nb % 32)).view(bh, nb, -1, 32).long() << torch.arange(32, device=chosen.device)
+    word = bits.sum(-1)
+    return torch.where(word >= 2 ** 31, word - 2 ** 32, word).to(torch.int32)
+
+
+@pytest.mark.parametrize("n,heads,group,kind", [
+    (22720, 2, 32, "routed"), (22721, 1, 64, "routed"), (22783, 1, 1000, "routed"), (22848, 2, 0, "routed"), (22912, 1, 32, "routed"),
+    (22720, 1, 32, "uneven"), (22849, 2, 0, "uneven"), (22975, 1, 32, "uneven"), (25600, 1, 32, "same"), (25601, 1, 32, "apart"),
+    (24000, 1, 64, "one"), (24001, 1, 32, "empty"), (262144, 1, 32, "few"), (262145, 1, 0, "few")])
+def test_workgroups_of_four_query_blocks_against_two(P, n, heads, group, kind):
+    """The number of selected blocks that the caller declares decides between workgroups of four and of two query blocks; the kernels read
+    the bitmap, so the same bitmap is given to both.  Numbers of query blocks with 0 to 3 left over, ragged last blocks of 1 and 63 tokens; equal numbers
+    of selected blocks (routed), very different ones in neighbouring rows, none and all of them (uneven), four rows alike, four rows without a common
+    block, one block, no whole block at all in some rows (empty), as many key blocks as can be planned and a ragged one more"""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + heads)
+    q, k, v = (torch.randn((1, heads, n, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    shape = P.Shape.of(q, block=64, group=group)
+    nb = P.num_blocks(shape)
+    u = torch.rand((heads, nb, nb), generator=g, device="cuda")
+    rows = torch.arange(nb, device="cuda")[:, None]
+    if kind == "routed":
+        idx, mask = P.route(P.block_score(q, k, shape), 60, 7, 0.5)
+    else:
+        density = {"same": 0.2, "apart": 0.2, "few": 40 / nb}.get(kind, 0.1)
+        if kind == "uneven":
+            density = torch.tensor([0.0, 0.004, 0.02, 0.3, 1.1], device="cuda")[torch.randint(0, 5, (nb, 1), generator=g, device="cuda")]
+        if kind == "same":
+            u = u[:, :1].expand(-1, nb, -1)
+        chosen = u < density
+        if kind == "apart":
+            chosen = chosen & (torch.arange(nb, device="cuda")[None, :] % 4 == rows % 4)
+        if kind == "one":
+            chosen = (rows * 7 + 3) % nb == torch.arange(nb, device="cuda")[None, :]
+            chosen = chosen.expand(heads, -1, -1).clone()
+        if kind == "empty":  # nothing but the ragged last block
+            chosen = chosen & (rows % 3 == 0)
+        if kind in ("uneven", "empty"):
+            chosen = chosen.clone()
+            chosen[:, :, nb - 1] |= ~chosen.any(-1)
+        mask = _bitmap(chosen)
+    ws = torch.empty(P.attn_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    P.kv_stats(k, v, shape, ws=ws)
+    out4, lse4 = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, want_lse=True, prepared=True, k_sel=353)
+    again = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, prepared=True, k_sel=353)
+    out2, lse2 = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, want_lse=True, prepared=True, k_sel=1)
+    torch.cuda.synchronize()
+    assert torch.equal(out4, again)
+    if kind not in ("one", "empty"):
+        assert not torch.equal(out4, out2)  # (so both did run)
+    # P is rounded to bf16 relative to the maximum so far, so differently in the two orders.  The values are white noise, whose weighted mean is as small
+    # as the error that the rounding makes of it: 2^-9 / sqrt(3) of the result for each, 1.6e-3 for both, and 2^-9 / sqrt(12) twice for the
+    # output's own rounding: 1.8e-3 in the 2-norm, which bounds the mean of the absolute values
+    a, b = out4.float(), out2.float()
+    assert torch.isfinite(a).all()
+    for h in range(heads):
+        assert (a[0, h] - b[0, h]).abs().max().item() <= 2e-2 * b[0, h].abs().max().item()
+        assert (a[0, h] - b[0, h]).abs().mean().item() <= 2e-3 * b[0, h].abs().mean().item()
+    np.testing.assert_allclose(lse4.cpu().numpy(), lse2.cpu().numpy(), atol=1e-3)
+
+
 @pytest.mark.parametrize("n,heads,d,block", [(65536, 9, 128, 64), (65537, 7, 128, 64), (65537, 8, 128, 64), (131072, 1, 64, 64),
                                               (128 * 2049 + 77, 1, 64, 128)])
 def test_blocks_visited_first_at_the_ends_of_the_rule(P, n, heads, d, block):
