@@ -551,12 +551,15 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
     };
     auto whole = [&](int r) -> bool { return r >= 0 && r + 64 <= n; };
     int r_cur = plan(), pair = 0;
-    if constexpr (MODE == 0) {
+    if constexpr (MODE == 0 || (MODE == 1 && PART == kWhole)) {
       // Tiles whose 64 rows are all keys of the tile: pipelined steps, each with P V of one tile and the logits of the next.
       // K of tile t is in slot 2 (t & 1), V in the slot after it.  Against steps of one tile (fused_step), 12 heads of 32,760
       // tokens: 3.90 -> 3.47 ms with all-zero inputs (clock at its maximum: 3130 -> 2780 cycles a step of two workgroups, 2048 of
       // them MFMAs), 5.89 -> 5.65 ms with random ones (where the power limit sets the clock, so that what a step moves and
-      // switches counts more than its cycles); 4140 tokens, 4 heads: 74.7 -> 67.6 us.
+      // switches counts more than its cycles); 4140 tokens, 4 heads: 74.7 -> 67.6 us.  Blocks of 128 tokens,
+      // 147,600 tokens: 6 heads, 58 blocks 4850 -> 4698, 173 blocks 11,310 -> 10,821.
+      // (Two 64-token blocks a workgroup gain nothing: their shared pass is short, and a run of pipelined steps starts and ends with half
+      // empty ones: 4 heads of 4140 tokens 29.6 -> 30.1 us, 12 of 32,760 1660 -> 1647.)
       if (r_cur >= 0) request(kb, r_cur, 0);
       load_q();
       settle_q();
