@@ -822,12 +822,13 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
 #pragma unroll 1
       for (int chunk = c_lo; chunk < c_fast; ++chunk) {
         float A;
+        const float m_before = w.m;
         ring_barrier<NI>(2);
         pipes::stats_step(slot(t) + lo.k, slot(t) + lo.v[0], slot(t) + lo.v[1], w.qf, w.o, w.m, w.l, p.c, ~mask_row[chunk], sh, bf,
                           A, rq_ptr(), x_ws, slot_wave(t + 3));
         rq_advance();
         ++t;
-        A_group += A;
+        A_group = fmaf(A_group, __builtin_amdgcn_exp2f(m_before - w.m), A);  // (the weights before are relative to the maximum before)
         if (--left != 0 && chunk + 1 < c_fast) continue;
         left = cpg;
         ring_barrier<NI>(2);
