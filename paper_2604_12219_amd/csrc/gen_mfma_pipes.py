@@ -278,9 +278,9 @@ def spread(after, k0, k1, stream):
             after.setdefault(k0 + i, []).extend(list(item) if isinstance(item, tuple) else [item])
 
 
-def fused_step(D):
+def fused_step(D, waves):
     ns, nt = D // 16, D // 32
-    ni = (64 // (1024 // (2 * D))) // 4
+    ni = tile_loads(D, waves)
     n_o = 16 * nt
     mf = []
     for half in range(2):
@@ -313,7 +313,7 @@ def fused_step(D):
         m = mf[k]
         lines.append(f"{MFMA} {m['acc']}, {F(k % pipe.nbuf)}, {m['b']}, {'0' if m['first'] else m['acc']}")
         if dmas:
-            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * 4096)}")
+            lines.append(f"s_add_u32 m0, %[l{dmas[0][0]}], {hex(dmas[0][1] * waves * 1024)}")
         if k + pipe.nbuf < n:
             pipe.issue(k + pipe.nbuf, mf[k + pipe.nbuf]["load"])
         elif dmas:
@@ -1147,13 +1147,13 @@ def gen():
     out.append(pipe_functions())
     out.append(quad_functions())
     out.append(approx_functions())
-    for D in (128, 64):
+    for D, waves in ((128, 4), (128, 2), (64, 4), (64, 2)):
         ns, nt = D // 16, D // 32
-        ni = (64 // (1024 // (2 * D))) // 4
+        ni = tile_loads(D, waves)
         out.append(f"// One whole 64-key tile (all keys valid) against the wave's 32 queries: logits, online softmax, P V.\n"
                    f"// ak, av0, av1: K tile address + row-fragment offset, V tile address + the two column-fragment offsets;\n"
                    f"// m, l: running maximum (log2 units) and normaliser share; c = scale * log2(e); kb/vb/x/lk/lv: the next pair\n"
-                   f"// of tiles to request (see rows_x_q_dma).\n"
+                   f"// of tiles to request (see rows_x_q_dma), by {waves} waves.\n"
                    f"PASA_DEVICE void fused_step(uint32_t ak, uint32_t av0, uint32_t av1, const bf16x8 (&q)[{ns}], f32x16 (&o)[{nt}],\n"
                    f"                           float& m, float& l, float c, const void* kb, const void* vb,\n"
                    f"                           const uint32_t (&x)[{ni}], uint32_t lk, uint32_t lv) {{\n"
@@ -1162,7 +1162,7 @@ def gen():
                ['[m] "+v"(m)', '[l] "+v"(l)', '[flag] "=&s"(flag)']
         ins = ['[ak] "v"(ak)', '[av0] "v"(av0)', '[av1] "v"(av1)', '[c] "s"(c)'] + q_inputs(D) + \
               ['[kb] "s"(kb)', '[vb] "s"(vb)', '[lk] "s"(lk)', '[lv] "s"(lv)'] + [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
-        text = "\n".join(f'      "{l}\\n\\t"' for l in fused_step(D))
+        text = "\n".join(f'      "{l}\\n\\t"' for l in fused_step(D, waves))
         clob = ", ".join([f'"v{r}"' for r in range(FUSED_CLOBBER_LO, 256)] + ['"memory"', '"scc"', '"vcc"', '"m0"'])
         out.append(f"  asm volatile(\n{text}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n      : {clob});\n}}\n\n")
     for D in (128, 64):

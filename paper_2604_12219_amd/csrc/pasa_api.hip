@@ -179,6 +179,16 @@ bool dense_wide(const pasa_shape_t* s) {
   return 62 * wide <= 32 * narrow;
 }
 
+// Whether the sparse path with blocks of 64 tokens takes a ring of eight tiles instead of four.  The workgroup then has a compute unit to itself, so
+// only where no compute unit would get two (see dense_teams), and it pays where the walk is long enough: the blocks of one of the two query blocks then
+// take one barrier a step, and shared tiles arrive three steps ahead.  us, four / eight:
+//   d = 128: 4140 tokens, 4 heads, 3 of 65 blocks 18.6 / 19.4, 10: 30.3 / 29.4, 26: 52.4 / 49.8; 9900, 3 heads, 8 of 155: 32.5 / 31.8, 62: 102 / 97.5;
+//     32,760, 1 head, 26 of 512: 76.4 / 72.3; 2048, 16 heads, 13 of 32: 32.5 / 34.6
+//   d = 64: 4140, 4 heads, 3: 12.3 / 12.2, 10: 20.8 / 19.4, 26: 37.0 / 33.9; 9900, 3 heads, 62: 75.4 / 67.0; 32,760, 1 head, 77: 104 / 90.9
+bool sparse_deep(const pasa_shape_t* s, int32_t k_sel) {
+  return s->block == 64 && s->kv_slices <= 1 && num_blocks(s) >= 64 && k_sel >= 8 && (int64_t)s->B * s->H * (((int64_t)s->n + 1023) / 1024) <= 32;
+}
+
 // Whether the sparse path takes workgroups of four query blocks of 64 tokens (pasa_quad.hpp) instead of two: they fetch fewer tiles, but plan
 // their steps first (15 us a workgroup, with the starts and ends of its runs of steps).  So the selection has to be long, and the more so the
 // smaller a head: its keys and values are in the L2s then anyway.  Attention alone, us, two / four:
@@ -473,7 +483,8 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     a.queue = reinterpret_cast<uint32_t*>(base + w.queue);
   }
   a.teams = !sparse && dense_teams(&s);
-  a.wide = sparse ? sparse_quad(&s, k_sel) : !a.teams && dense_wide(&s);
+  a.deep = sparse && sparse_deep(&s, k_sel);
+  a.wide = sparse ? !a.deep && sparse_quad(&s, k_sel) : !a.teams && dense_wide(&s);
   return pasa_launch_attn(a, sparse, s.d, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 

@@ -202,8 +202,7 @@ PASA_DEVICE void first_order_part(uint32_t tile, const LaneOffsets<D>& lo, WaveS
 // ---- direct global -> LDS tile loads ------------------------------------------------------------
 // One instruction moves 1 KB: 64 lanes x 16 bytes land at consecutive LDS addresses starting at M0,
 // i.e. RPI = 1024/(2D) whole tile rows; the XOR swizzle of the LDS layout is applied on the global
-// side (which 16-byte chunk of its row a lane fetches).  Wave w issues instructions w, w+4, ... of a
-// tile; a lane's rows in them are a multiple of 16 apart, so its swizzle is the same in all of them.
+// side (which 16-byte chunk of its row a lane fetches).  Wave w issues instructions w, w+WAVES, ... of a tile.
 // (dma_1k in pasa_device.hpp)
 template <int D, int WAVES>
 struct TileDma {
@@ -211,20 +210,19 @@ struct TileDma {
   static constexpr int RPI = 1024 / (2 * D);        // rows per instruction
   static constexpr int NI = 64 / RPI / WAVES;      // instructions per wave and tile
   static constexpr int STEP = WAVES * RPI;         // a lane's rows in consecutive instructions are this far apart
-  static_assert(STEP % 16 == 0, "a lane's swizzle must be the same in all of its instructions");
-
-  int row0;       // the lane's row in the wave's first instruction
-  uint32_t coff;  // byte offset of the lane's (swizzled) chunk inside its row
+  int row0;   // the lane's row in the wave's first instruction
+  int chunk;  // the lane's 16-byte chunk in LDS
   PASA_DEVICE void init(int wave, int lane) {
     row0 = wave * RPI + lane / CPR;
-    coff = (uint32_t)(((lane % CPR) ^ swz<D>(row0)) << 4);
+    chunk = lane % CPR;
   }
   // Per-lane byte offsets of the wave's NI loads of a tile, relative to the tile's first row.  Rows are
   // clamped to n_rows - 1: a no-op for a matrix of at least 64 rows (tiles are requested such that
   // they lie inside it), and for a shorter one the rows that do not exist re-read the last row.
   PASA_DEVICE void offsets(uint32_t row_bytes, int n_rows, uint32_t (&x)[NI]) const {
 #pragma unroll
-    for (int i = 0; i < NI; ++i) x[i] = (uint32_t)min(row0 + STEP * i, n_rows - 1) * row_bytes + coff;
+    for (int i = 0; i < NI; ++i)
+      x[i] = (uint32_t)min(row0 + STEP * i, n_rows - 1) * row_bytes + (uint32_t)((chunk ^ swz<D>(row0 + STEP * i)) << 4);
   }
   // Requests this wave's share of the tile whose first row is at `base` (wave-uniform).
   // lds_wave: LDS address of the slot plus wave*1024.
@@ -309,10 +307,10 @@ struct BitWalk {
 // blocks, so a chunk of 32 blocks intersects several groups and the per-block weights of a chunk have
 // to be kept until all of its group matrices have passed.  PART: kWhole: a workgroup walks all keys of its
 // query tile; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two teams of waves; kWide (dense): eight waves, 256 query rows; kQuad (sparse):
-// eight waves, four query blocks of 64 tokens (pasa_quad.hpp).
-enum : int { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3, kQuad = 4 };
+// eight waves, four query blocks of 64 tokens (pasa_quad.hpp); kDeep (sparse, two 64-token blocks): a ring of eight tiles.
+enum : int { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3, kQuad = 4, kDeep = 5 };
 constexpr int teams_of(int part) { return part == kTeams ? 2 : 1; }
-constexpr int waves_of(int part) { return part >= kWide ? 8 : 4; }  // of a team
+constexpr int waves_of(int part) { return part == kWide || part == kQuad ? 8 : 4; }  // of a team
 template <int D, int MODE, bool MULTI, int PART>
 __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_kernel(AttnParams p) {
   constexpr bool SPARSE = MODE != 0, SLICED = PART == kSliced;
@@ -325,7 +323,9 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   constexpr bool QUAD = PART == kQuad;
   static_assert(!QUAD || (D == kQuadDim && MODE == 2 && !MULTI), "");
   constexpr int GROUPS = QUAD ? kQuadGroups : 1;  // groups of waves with a query block of their own
-  struct PlainShared { __attribute__((aligned(1024))) char ring[TEAMS * kRing * TILE_BYTES]; };
+  constexpr bool DEEP = PART == kDeep;
+  constexpr int RING = DEEP ? 2 * kRing : kRing;
+  struct PlainShared { __attribute__((aligned(1024))) char ring[TEAMS * RING * TILE_BYTES]; };
   __shared__ std::conditional_t<QUAD, QuadShared, PlainShared> shared;
   char* const ring = shared.ring;
 
@@ -343,8 +343,8 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   uint32_t x_kv[NI];  // lane offsets of the loads of a whole K or V tile
   dma.offsets(row_bytes, p.n, x_kv);
   const uint32_t ring_wave = ring_base + (uint32_t)(wave * 1024);
-  auto slot = [&](int i) -> uint32_t { return ring_base + (uint32_t)((i & (kRing - 1)) * TILE_BYTES); };
-  auto slot_wave = [&](int i) -> uint32_t { return ring_wave + (uint32_t)((i & (kRing - 1)) * TILE_BYTES); };
+  auto slot = [&](int i) -> uint32_t { return ring_base + (uint32_t)((i & (RING - 1)) * TILE_BYTES); };
+  auto slot_wave = [&](int i) -> uint32_t { return ring_wave + (uint32_t)((i & (RING - 1)) * TILE_BYTES); };
   int xcd = blockIdx.x % kXcds;
   if constexpr (SLICED) {  // ask the hardware which XCD this workgroup really runs on
     unsigned id;
@@ -597,6 +597,29 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
       } else if (r_cur >= 0) {
         request(vb, r_cur, 1);
       }
+    } else if constexpr (DEEP) {
+      // The same a tile pair at a time, three pairs ahead: alone on its compute unit a workgroup waits for nothing but its loads
+      int r1 = plan(), r2 = plan();
+      auto ask = [&](int r, int pr) {  // (after the last pair: one that exists, unused)
+        if (r < 0) r = max(r_cur, 0);
+        request(kb, r, 2 * pr);
+        request(vb, r, 2 * pr + 1);
+      };
+      load_q();
+      if (r_cur >= 0) { ask(r_cur, 0); ask(r1, 1); ask(r2, 2); }
+      settle_q();
+#pragma unroll 1
+      while (whole(r_cur)) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * NI) : "memory");  // the pair has landed, two are on their way
+        const int r3 = plan(), r_req = r3 >= 0 ? r3 : r_cur;
+        const uint32_t k_tile = slot(2 * pair), v_tile = slot(2 * pair + 1);
+        pipes::fused_step(k_tile + lo.k, v_tile + lo.v[0], v_tile + lo.v[1], w.qf, w.o, w.m, w.l, p.c, tile_ptr(kb, r_req),
+                          tile_ptr(vb, r_req), x_kv, slot_wave(2 * pair + 6), slot_wave(2 * pair + 7));
+        r_cur = r1;
+        r1 = r2;
+        r2 = r3;
+        ++pair;
+      }
     } else {
       load_q();
       if (r_cur >= 0) { request(kb, r_cur, 0); request(vb, r_cur, 1); }
@@ -620,7 +643,7 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
 #pragma unroll 1
     while (r_cur >= 0) {
       ring_barrier<NI>(0);
-      const int r_nxt = plan();
+      const int r_nxt = DEEP ? -1 : plan();  // (DEEP: the ragged last block is the last one, and what comes after it has been planned)
       const int r_req = r_nxt >= 0 ? r_nxt : r_cur;
       const uint32_t k_tile = slot(2 * pair), v_tile = slot(2 * pair + 1);
       f32x16 s0, s1;
@@ -648,6 +671,38 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
     only_a.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b);
     only_b.init(mask_a, mask_b, c_lo, c_hi, first_a, first_b);
     int a_blk = only_a.next(lane), b_blk = only_b.next(lane);
+    if constexpr (DEEP) {
+      // Both pairs of waves have K and V of two blocks of their own: the next ones land during the whole step, with one barrier
+      auto whole = [&](int blk) -> bool { return blk != kNoBlock && blk * 64 + 64 <= n; };
+      if (whole(a_blk) && whole(b_blk)) {
+        typedef TileDma<D, 2> PairDma;
+        uint32_t x_own[PairDma::NI];
+        PairDma pd;
+        pd.init(wave & 1, lane);
+        pd.offsets(row_bytes, n, x_own);
+        const int s0 = second ? 4 : 0;
+        auto own_slot = [&](int i) -> uint32_t { return slot(s0 + i) + (uint32_t)((wave & 1) * 1024); };
+        ring_barrier<NI>(0);  // every wave is done with the ring
+        {
+          const int mine = second ? b_blk : a_blk;
+          PairDma::request(tile_ptr(kb, mine * 64), x_own, own_slot(0));
+          PairDma::request(tile_ptr(vb, mine * 64), x_own, own_slot(1));
+        }
+        int at = 0;
+#pragma unroll 1
+        while (whole(a_blk) && whole(b_blk)) {
+          ring_barrier<NI>(0);
+          const int a_nxt = only_a.next(lane), b_nxt = only_b.next(lane);
+          const int nxt = second ? b_nxt : a_nxt, r_req = (nxt != kNoBlock ? nxt : second ? b_blk : a_blk) * 64;  // (after the last: once more the same)
+          const uint32_t k_tile = slot(s0 + at), v_tile = slot(s0 + at + 1);
+          pipes::fused_step(k_tile + lo.k, v_tile + lo.v[0], v_tile + lo.v[1], w.qf, w.o, w.m, w.l, p.c, tile_ptr(kb, r_req),
+                            tile_ptr(vb, r_req), x_own, own_slot(at ^ 2), own_slot((at ^ 2) + 1));
+          a_blk = a_nxt;
+          b_blk = b_nxt;
+          at ^= 2;
+        }
+      }
+    }
     if (a_blk != kNoBlock || b_blk != kNoBlock) {
       ring_barrier<NI>(0);  // every wave is done with the ring
       request(kb, (a_blk != kNoBlock ? a_blk : b_blk) * 64, 0);
@@ -1053,6 +1108,8 @@ hipError_t launch_part(const AttnParams& p, int grid, hipStream_t stream) {
     if (p.wide) return launch<D, MODE, MULTI, kWide>(p, grid, stream);
   } else {
     if (p.n_slices > 1) return launch<D, MODE, MULTI, kSliced>(p, grid, stream);
+    if constexpr (MODE == 2)
+      if (p.deep) return launch<D, MODE, MULTI, kDeep>(p, grid, stream);
     if constexpr (D == kQuadDim && MODE == 2 && !MULTI)
       if (p.wide) return launch<D, MODE, MULTI, kQuad>(p, grid, stream);
   }

@@ -27,6 +27,7 @@ struct AttnParams {
   int32_t n_slices;      // 1 = off (the attention kernel writes the output itself)
   int32_t teams;         // dense path, 1: the keys of a query tile are halved between two teams of waves of a workgroup
   int32_t wide;          // 1: workgroups of 256 query rows (dense: one key walk for all of them; sparse: pasa_quad.hpp)
+  int32_t deep;          // sparse path, 1: a ring of eight tiles
   float* part_o;         // fp32 [BH][n_slices][n][d]: unnormalised partial numerators
   float* part_ml;        // fp32 [BH][n_slices][n][2]: running maximum (log2 units) and partial normaliser
   uint32_t* queue;       // [8] work-item counters, one per XCD (reset by the launcher)

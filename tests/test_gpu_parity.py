@@ -456,23 +456,36 @@ def _bitmap(chosen):
 
 
 @pytest.mark.parametrize("n,heads,group,kind", [
-    (22720, 2, 32, "routed"), (22721, 1, 64, "routed"), (22783, 1, 1000, "routed"), (22848, 2, 0, "routed"), (22912, 1, 32, "routed"),
-    (22720, 1, 32, "uneven"), (22849, 2, 0, "uneven"), (22975, 1, 32, "uneven"), (25600, 1, 32, "same"), (25601, 1, 32, "apart"),
-    (24000, 1, 64, "one"), (24001, 1, 32, "empty"), (262144, 1, 32, "few"), (262145, 1, 0, "few")])
+    (22720, 2, 32, "routed"), (22721, 2, 64, "routed"), (22783, 2, 1000, "routed"), (22848, 2, 0, "routed"), (22912, 2, 32, "routed"),
+    (22720, 2, 32, "uneven"), (22849, 2, 0, "uneven"), (22975, 2, 32, "uneven"), (25600, 2, 32, "same"), (25601, 2, 32, "apart"),
+    (24000, 2, 64, "one"), (24001, 2, 32, "empty"), (262144, 1, 32, "few"), (262145, 1, 0, "few")])
 def test_workgroups_of_four_query_blocks_against_two(P, n, heads, group, kind):
     """The number of selected blocks that the caller declares decides between workgroups of four and of two query blocks; the kernels read
     the bitmap, so the same bitmap is given to both.  Numbers of query blocks with 0 to 3 left over, ragged last blocks of 1 and 63 tokens; equal numbers
     of selected blocks (routed), very different ones in neighbouring rows, none and all of them (uneven), four rows alike, four rows without a common
     block, one block, no whole block at all in some rows (empty), as many key blocks as can be planned and a ragged one more"""
+    _compare_routes(P, n, heads, 128, group, kind, 353)
+
+
+@pytest.mark.parametrize("n,heads,d,group,kind", [
+    (4096, 4, 128, 64, "routed"), (4097, 3, 128, 32, "routed"), (4159, 2, 64, 16, "routed"), (8191, 2, 128, 0, "uneven"), (4161, 4, 64, 32, "uneven"),
+    (5000, 2, 64, 1000, "same"), (5120, 1, 128, 8, "apart"), (4224, 3, 128, 32, "one"), (4225, 2, 64, 32, "empty")])
+def test_ring_of_eight_tiles_against_four(P, n, heads, d, group, kind):
+    """The same for small grids, where the declared number decides between rings of eight and of four tiles: odd and even numbers of
+    shared and of private blocks, one query block running out of them before the other, ragged last blocks of 1, 8, 33 and 63 tokens"""
+    _compare_routes(P, n, heads, d, group, kind, 8)
+
+
+def _compare_routes(P, n, heads, d, group, kind, declared):
     g = torch.Generator(device="cuda")
     g.manual_seed(n + heads)
-    q, k, v = (torch.randn((1, heads, n, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    q, k, v = (torch.randn((1, heads, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
     shape = P.Shape.of(q, block=64, group=group)
     nb = P.num_blocks(shape)
     u = torch.rand((heads, nb, nb), generator=g, device="cuda")
     rows = torch.arange(nb, device="cuda")[:, None]
     if kind == "routed":
-        idx, mask = P.route(P.block_score(q, k, shape), 60, 7, 0.5)
+        idx, mask = P.route(P.block_score(q, k, shape), min(60, nb // 6), 7, 0.5)
     else:
         density = {"same": 0.2, "apart": 0.2, "few": 40 / nb}.get(kind, 0.1)
         if kind == "uneven":
@@ -493,12 +506,12 @@ def test_workgroups_of_four_query_blocks_against_two(P, n, heads, group, kind):
         mask = _bitmap(chosen)
     ws = torch.empty(P.attn_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
     P.kv_stats(k, v, shape, ws=ws)
-    out4, lse4 = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, want_lse=True, prepared=True, k_sel=353)
-    again = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, prepared=True, k_sel=353)
+    out4, lse4 = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, want_lse=True, prepared=True, k_sel=declared)
+    again = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, prepared=True, k_sel=declared)
     out2, lse2 = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, want_lse=True, prepared=True, k_sel=1)
     torch.cuda.synchronize()
     assert torch.equal(out4, again)
-    if kind not in ("one", "empty"):
+    if declared > 100 and kind not in ("one", "empty"):
         assert not torch.equal(out4, out2)  # (so both did run)
     # P is rounded to bf16 relative to the maximum so far, so differently in the two orders.  The values are white noise, whose weighted mean is as small
     # as the error that the rounding makes of it: 2^-9 / sqrt(3) of the result for each, 1.6e-3 for both, and 2^-9 / sqrt(12) twice for the
