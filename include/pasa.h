@@ -15,6 +15,7 @@
  *                         of the unselected ones under one normaliser (Eq.7, Eq.4, Eq.5, Eq.12, Eq.14)
  *   pasa_attn_dense_ref   dense attention with the same tile machinery (Eq.1)
  *   pasa_forward          statistics, scores, routing and piecewise attention in one call
+ *   pasa_forward_buffers  the same with the intermediates in the caller's buffers
  *
  * Conventions
  *   - Every pointer is a DEVICE pointer unless marked "host".  The caller owns every buffer; the
@@ -233,6 +234,16 @@ PASA_API int pasa_sparse_attn_fwd_prepared(const void* q, const void* k, const v
 PASA_API size_t pasa_forward_workspace_bytes(const pasa_shape_t* shape, double keep_ratio);
 PASA_API int pasa_forward(const void* q, const void* k, const void* v, const pasa_shape_t* shape, double keep_ratio,
                           uint64_t seed, float noise_amp, void* out, float* lse, void* ws, size_t ws_bytes, void* stream);
+
+/*
+ * The same with every intermediate in a buffer of the caller's, and the block-mean keys pooled as pasa_block_score pools them: leaves exactly what
+ * pasa_block_score, pasa_route (k_sel of N_B blocks) and pasa_sparse_attn_fwd one after the other leave, in two launches fewer.
+ *   scores, idx, mask   as in pasa_block_score and pasa_route (mask not NULL)
+ *   score_ws, attn_ws   scratch as for pasa_block_score and pasa_sparse_attn_fwd
+ */
+PASA_API int pasa_forward_buffers(const void* q, const void* k, const void* v, const pasa_shape_t* shape, int32_t k_sel, uint64_t seed,
+                                  float noise_amp, float* scores, int32_t* idx, uint32_t* mask, void* score_ws, size_t score_ws_bytes,
+                                  void* attn_ws, size_t attn_ws_bytes, void* out, float* lse, void* stream);
 
 /*
  * Validation of a selection before it is handed to pasa_sparse_attn_fwd (debugging aid for callers that build

@@ -202,6 +202,13 @@ bool sparse_quad(const pasa_shape_t* s, int32_t k_sel) {
          k_sel >= 100 && (int64_t)k_sel * s->n >= 8000000;
 }
 
+// Whether a whole forward runs statistics and scoring in two launches instead of four (pasa_fused.hip).  The pooling then runs with the two workgroups a
+// compute unit of the statistics: enough for tensors that are in cache or nearly so, not for the rate of the memory.  us, four / two, by MB of Q:
+//   d = 128: 1024 tokens, 16 heads (4) 21.9 / 16.6; 2048, 40 (21) 39.3 / 29.4; 4140, 12 (13) 30.0 / 23.9; 9900, 16 (41) 52.3 / 47.8; 32,760, 2 (17)
+//     37.5 / 28.7; 75,600, 1 (19) 40.6 / 30.4; 118,800, 3 (91) 119 / 126; 75,600, 5 (97) 112 / 128; 32,760, 12 (101) 101 / 119
+//   d = 64: 2048, 40 (10) 23.7 / 17.3; 9900, 12 (15) 26.5 / 19.2; 32,760, 4 (17) 27.5 / 20.8; 32,760, 12 (50) 48.1 / 47.7
+bool stats_and_score_together(const pasa_shape_t* s) { return (int64_t)s->B * s->H * s->n * s->d <= ((int64_t)20 << 20); }
+
 constexpr int kMaxDevices = 64;
 std::atomic<void*> g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each device, null until looked up
 std::mutex g_scratch_mutex;
@@ -271,14 +278,15 @@ size_t pasa_attn_workspace_bytes(const pasa_shape_t* shape) {
   return carve_attn(shape).total;  // never zero for a valid shape (it holds a bitmap), so that 0 always means "bad shape"
 }
 
-static int block_score_impl(const void* q, const void* k, const pasa_shape_t* shape, const float* key_bias, float* scores,
-                            void* ws, size_t ws_bytes, const void* kbar_split, void* stream) {
+static int score_params(const void* q, const void* k, const pasa_shape_t* shape, const float* key_bias, float* scores, void* ws, size_t ws_bytes,
+                        const void* kbar_split, ScoreParams* out) {
   const int rc = check_shape(shape);
   if (rc != PASA_OK) return rc;
   if (!q || (!k && !kbar_split) || !scores || !ws) return PASA_EINVAL;
   if (!aligned16(q) || (k && !aligned16(k)) || !aligned16(scores) || !aligned16(ws)) return PASA_EALIGN;
   if (ws_bytes < pasa_score_workspace_bytes(shape)) return PASA_EWORKSPACE;
-  ScoreParams p{};
+  ScoreParams& p = *out;
+  p = ScoreParams{};
   p.q = static_cast<const uint16_t*>(q);
   p.k = static_cast<const uint16_t*>(k);
   p.stride_b = shape->stride_b; p.stride_h = shape->stride_h; p.stride_n = shape->stride_n;
@@ -291,6 +299,14 @@ static int block_score_impl(const void* q, const void* k, const pasa_shape_t* sh
   p.kbar = kbar_split ? const_cast<float*>(static_cast<const float*>(kbar_split))
                       : reinterpret_cast<float*>(static_cast<char*>(ws) + pasa_score_workspace_bytes(shape) / 2);
   p.scores = scores;
+  return PASA_OK;
+}
+
+static int block_score_impl(const void* q, const void* k, const pasa_shape_t* shape, const float* key_bias, float* scores, void* ws, size_t ws_bytes,
+                            const void* kbar_split, void* stream) {
+  ScoreParams p;
+  const int rc = score_params(q, k, shape, key_bias, scores, ws, ws_bytes, kbar_split, &p);
+  if (rc != PASA_OK) return rc;
   return pasa_launch_block_score(p, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
@@ -370,9 +386,12 @@ int pasa_check_selection(const int32_t* idx, const uint32_t* mask, int32_t BH, i
                  hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
-// idx not null: the same launch builds the selection bitmap in the workspace from these index lists of k_sel blocks
-static int kv_stats_impl(const void* k, const void* v, const pasa_shape_t* shape, const int32_t* idx, int32_t k_sel, void* ws,
-                         size_t ws_bytes, void* stream) {
+// idx not null: the same launch builds the selection bitmap in the workspace from these index lists of k_sel blocks.
+// out->group stays 0 where the approximation is off and there is nothing to launch
+static int stats_params(const void* k, const void* v, const pasa_shape_t* shape, const int32_t* idx, int32_t k_sel, void* ws, size_t ws_bytes,
+                        StatsParams* out) {
+  StatsParams& t = *out;
+  t = StatsParams{};
   pasa_shape_t s;
   const int rc = check_attn_args(shape, true, ws, ws_bytes, &s);
   if (rc != PASA_OK) return rc;
@@ -382,7 +401,6 @@ static int kv_stats_impl(const void* k, const void* v, const pasa_shape_t* shape
   const int nb = num_blocks(&s);
   const AttnWorkspace w = carve_attn(&s);
   char* base = static_cast<char*>(ws);
-  StatsParams t{};
   t.k = static_cast<const uint16_t*>(k); t.v = static_cast<const uint16_t*>(v);
   t.stride_b = s.stride_b; t.stride_h = s.stride_h; t.stride_n = s.stride_n;
   t.bh = s.B * s.H; t.H = s.H; t.n = s.n; t.nb = nb; t.block = s.block; t.tail = s.n - (nb - 1) * s.block; t.d = s.d;
@@ -404,11 +422,36 @@ static int kv_stats_impl(const void* k, const void* v, const pasa_shape_t* shape
   t.kbar_split = reinterpret_cast<uint16_t*>(base + w.kbar);
   t.idx = idx; t.k_sel = k_sel; t.mask_words = (nb + 31) / 32;
   t.mask = reinterpret_cast<uint32_t*>(base + w.bitmap);
+  return PASA_OK;
+}
+
+static int kv_stats_impl(const void* k, const void* v, const pasa_shape_t* shape, const int32_t* idx, int32_t k_sel, void* ws, size_t ws_bytes,
+                         void* stream) {
+  StatsParams t;
+  const int rc = stats_params(k, v, shape, idx, k_sel, ws, ws_bytes, &t);
+  if (rc != PASA_OK || t.group == 0) return rc;
   return pasa_launch_kv_stats(t, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
 int pasa_kv_stats(const void* k, const void* v, const pasa_shape_t* shape, void* ws, size_t ws_bytes, void* stream) {
   return kv_stats_impl(k, v, shape, nullptr, 0, ws, ws_bytes, stream);
+}
+
+// scoring and statistics of a whole forward; pool_k: the scores' block-mean keys are pooled as pasa_block_score does, not taken from the statistics
+static int score_and_stats(const void* q, const void* k, const void* v, const pasa_shape_t* shape, float* scores, void* score_ws, size_t score_bytes,
+                           void* attn_ws, size_t attn_bytes, bool pool_k, void* stream) {
+  StatsParams t;
+  int rc = stats_params(k, v, shape, nullptr, 0, attn_ws, attn_bytes, &t);
+  if (rc != PASA_OK) return rc;
+  if (t.group == 0) return block_score_impl(q, k, shape, nullptr, scores, score_ws, score_bytes, nullptr, stream);
+  ScoreParams p;
+  rc = score_params(q, k, shape, nullptr, scores, score_ws, score_bytes, pool_k ? nullptr : t.kbar_split, &p);
+  if (rc != PASA_OK) return rc;
+  if (!stats_and_score_together(shape)) {
+    return pasa_launch_kv_stats(t, static_cast<hipStream_t>(stream)) == hipSuccess && pasa_launch_block_score(p, static_cast<hipStream_t>(stream)) == hipSuccess
+               ? PASA_OK : PASA_EHIP;
+  }
+  return pasa_launch_stats_and_score(t, p, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
 int pasa_key_prior(const void* k, const void* v, const pasa_shape_t* shape, float eps, float* beta, void* ws,
@@ -549,6 +592,17 @@ ForwardWorkspace carve_forward(const pasa_shape_t* s, double keep_ratio) {
 }
 }  // namespace
 
+// pool_k: the scores' block-mean keys are pooled as pasa_block_score does it, not taken from the statistics (the two differ in the last place)
+static int forward_stages(const void* q, const void* k, const void* v, const pasa_shape_t* shape, int32_t k_sel, uint64_t seed, float noise_amp,
+                          float* scores, int32_t* idx, uint32_t* mask, void* score_ws, size_t score_bytes, void* attn_ws, size_t attn_bytes, void* out,
+                          float* lse, bool pool_k, void* stream) {
+  int r = score_and_stats(q, k, v, shape, scores, score_ws, score_bytes, attn_ws, attn_bytes, pool_k, stream);
+  if (r != PASA_OK) return r;
+  r = pasa_route(scores, shape->B * shape->H, num_blocks(shape), k_sel, seed, noise_amp, idx, mask, stream);
+  if (r != PASA_OK) return r;
+  return pasa_sparse_attn_fwd_prepared(q, k, v, shape, idx, mask, k_sel, out, lse, attn_ws, attn_bytes, stream);
+}
+
 size_t pasa_forward_workspace_bytes(const pasa_shape_t* shape, double keep_ratio) { return carve_forward(shape, keep_ratio).total; }
 
 int pasa_forward(const void* q, const void* k, const void* v, const pasa_shape_t* shape, double keep_ratio, uint64_t seed,
@@ -570,19 +624,19 @@ int pasa_forward(const void* q, const void* k, const void* v, const pasa_shape_t
   float* scores = reinterpret_cast<float*>(base + f.scores);
   int32_t* idx = reinterpret_cast<int32_t*>(base + f.idx);
   uint32_t* mask = reinterpret_cast<uint32_t*>(base + f.mask);
-  const size_t attn_bytes = ws_bytes - f.attn_ws, score_bytes = pasa_score_workspace_bytes(shape);
-  int r;
-  if (shape->group > 0) {  // the statistics first: scoring takes the block-mean keys from them
-    r = pasa_kv_stats(k, v, shape, base + f.attn_ws, attn_bytes, stream);
-    if (r != PASA_OK) return r;
-    r = pasa_block_score_with_stats(q, shape, nullptr, scores, base + f.score_ws, score_bytes, base + f.attn_ws, attn_bytes, stream);
-  } else {
-    r = pasa_block_score(q, k, shape, nullptr, scores, base + f.score_ws, score_bytes, stream);
-  }
-  if (r != PASA_OK) return r;
-  r = pasa_route(scores, shape->B * shape->H, f.nb, f.k_sel, seed, noise_amp, idx, mask, stream);
-  if (r != PASA_OK) return r;
-  return pasa_sparse_attn_fwd_prepared(q, k, v, shape, idx, mask, f.k_sel, out, lse, base + f.attn_ws, attn_bytes, stream);
+  return forward_stages(q, k, v, shape, f.k_sel, seed, noise_amp, scores, idx, mask, base + f.score_ws, pasa_score_workspace_bytes(shape),
+                        base + f.attn_ws, ws_bytes - f.attn_ws, out, lse, /*pool_k=*/false, stream);
+}
+
+int pasa_forward_buffers(const void* q, const void* k, const void* v, const pasa_shape_t* shape, int32_t k_sel, uint64_t seed, float noise_amp,
+                         float* scores, int32_t* idx, uint32_t* mask, void* score_ws, size_t score_ws_bytes, void* attn_ws, size_t attn_ws_bytes,
+                         void* out, float* lse, void* stream) {
+  const int rc = check_shape(shape);
+  if (rc != PASA_OK) return rc;
+  if (num_blocks(shape) > kRouteMaxBlocks) return PASA_EUNSUPPORTED;
+  if (!mask) return PASA_EINVAL;
+  return forward_stages(q, k, v, shape, k_sel, seed, noise_amp, scores, idx, mask, score_ws, score_ws_bytes, attn_ws, attn_ws_bytes, out, lse,
+                        /*pool_k=*/true, stream);
 }
 
 int pasa_attn_dense_ref(const void* q, const void* k, const void* v, const pasa_shape_t* shape, void* out, float* lse,

@@ -81,6 +81,8 @@ struct ScoreParams {
   int32_t pool_k;         // 1: pool the keys here; 0: kbar already holds the split block-mean keys (left by the statistics kernel)
 };
 hipError_t pasa_launch_block_score(const ScoreParams& p, hipStream_t stream);
+// both of the above in two launches; p.kbar may be what the statistics leave
+hipError_t pasa_launch_stats_and_score(const StatsParams& t, const ScoreParams& p, hipStream_t stream);
 
 struct RouteParams {
   const float* scores;

@@ -17,7 +17,7 @@ _lib = None
 
 EXPORTS = ("pasa_strerror", "pasa_topk_count", "pasa_num_blocks", "pasa_mask_words", "pasa_score_workspace_bytes",
            "pasa_attn_workspace_bytes", "pasa_block_score", "pasa_block_score_with_stats", "pasa_route", "pasa_route_gumbel", "pasa_kv_stats", "pasa_key_prior", "pasa_sparse_attn_fwd",
-           "pasa_sparse_attn_fwd_prepared", "pasa_sparse_attn_fwd_static", "pasa_forward", "pasa_forward_workspace_bytes", "pasa_check_selection", "pasa_attn_dense_ref", "pasa_l1_workspace_bytes", "pasa_l1_distance",
+           "pasa_sparse_attn_fwd_prepared", "pasa_sparse_attn_fwd_static", "pasa_forward", "pasa_forward_buffers", "pasa_forward_workspace_bytes", "pasa_check_selection", "pasa_attn_dense_ref", "pasa_l1_workspace_bytes", "pasa_l1_distance",
            "pasa_budget_schedule", "pasa_mfma_probe")
 
 
@@ -109,6 +109,9 @@ def load_library() -> ctypes.CDLL:
         L.pasa_forward_workspace_bytes.argtypes = [sp, ctypes.c_double]
         L.pasa_forward.restype = ctypes.c_int
         L.pasa_forward.argtypes = [vp, vp, vp, sp, ctypes.c_double, ctypes.c_uint64, ctypes.c_float, vp, vp, vp, ctypes.c_size_t, vp]
+        L.pasa_forward_buffers.restype = ctypes.c_int
+        L.pasa_forward_buffers.argtypes = [vp, vp, vp, sp, ctypes.c_int32, ctypes.c_uint64, ctypes.c_float, vp, vp, vp, vp, ctypes.c_size_t,
+                                           vp, ctypes.c_size_t, vp, vp, vp]
         L.pasa_check_selection.restype = ctypes.c_int
         L.pasa_check_selection.argtypes = [vp, vp, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, vp, vp]
         L.pasa_kv_stats.restype = ctypes.c_int
@@ -374,16 +377,12 @@ def forward(q, k, v, keep_ratio: float, seed: int, noise_amp: float, block: int 
         b["ws_score"] = torch.empty(score_workspace_bytes(shape), dtype=torch.uint8, device=q.device)
         b["ws_attn"] = torch.empty(attn_workspace_bytes(shape), dtype=torch.uint8, device=q.device)
         b["out"] = torch.empty_like(q)
-    # block_score, route and sparse_attn_fwd with the marshalling of the three done once: at 1024 tokens the six launches take
-    # the device 27 us, and a call was bound by 40 us of host work (23 now)
     _check_extent(shape, q=q, k=k, v=v, out=b["out"])
     if not strides == k.stride() == v.stride() == b["out"].stride():
         _check_strides(shape, k=k, v=v, out=b["out"])
-    stream, qp, kp, scores, idx, mask = _stream(), _ptr(q), _ptr(k), _ptr(b["scores"]), _ptr(b["idx"]), _ptr(b["mask"])
-    _check(L.pasa_block_score(qp, kp, c, None, scores, _ptr(b["ws_score"]), b["ws_score"].numel(), stream), "pasa_block_score")
-    _check(L.pasa_route(scores, shape.B * shape.H, nb, k_sel, seed & (2**64 - 1), noise_amp, idx, mask, stream), "pasa_route")
-    _check(L.pasa_sparse_attn_fwd(qp, kp, _ptr(v), c, idx, mask, k_sel, _ptr(b["out"]), None, _ptr(b["ws_attn"]),
-                                  b["ws_attn"].numel(), stream), "pasa_sparse_attn_fwd")
+    _check(L.pasa_forward_buffers(q.data_ptr(), k.data_ptr(), v.data_ptr(), c, k_sel, seed & (2**64 - 1), noise_amp, b["scores"].data_ptr(),
+                                  b["idx"].data_ptr(), b["mask"].data_ptr(), b["ws_score"].data_ptr(), b["ws_score"].numel(),
+                                  b["ws_attn"].data_ptr(), b["ws_attn"].numel(), b["out"].data_ptr(), None, _stream()), "pasa_forward_buffers")
     return b["out"], b["idx"]
 
 

@@ -772,3 +772,27 @@ def test_random_configurations_against_oracle(P, case):
     assert_close(to_f64(out), res["o"], what=what)
     np.testing.assert_allclose(lse.cpu().numpy(), res["lse"], atol=2e-2, err_msg=what)
     assert_close(to_f64(dense), oracle.dense_attention(to_f64(q), to_f64(k), to_f64(v), scale=scale), what="dense, " + what)
+
+
+@pytest.mark.parametrize("n,heads,d,block,group,batch", [
+    (100, 1, 128, 64, 32, 1), (1023, 3, 64, 64, 32, 1), (4140, 4, 128, 64, 64, 1), (4097, 9, 64, 128, 16, 2), (3000, 2, 128, 64, 0, 1),
+    (2113, 1, 128, 64, 1000, 2), (40960, 4, 128, 64, 32, 1), (40961, 4, 128, 64, 32, 1)])
+def test_forward_leaves_what_its_stages_leave(P, n, heads, d, block, group, batch):
+    """Statistics and scoring share launches in a whole forward up to 20 Mi elements (the last two sizes are the line): the same bits as the stages one
+    by one, for both origins of the block-mean keys, with and without a second launch over the units of a group, heads dealt by XCD or not"""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn((batch, heads, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    shape = P.Shape.of(q, block=block, group=group)
+    k_sel = P.topk_count(P.num_blocks(shape), 0.2)
+    buffers = {}
+    out, idx = P.forward(q, k, v, 0.2, 11, 0.125, block=block, group=group, buffers=buffers)
+    scores = P.block_score(q, k, shape)
+    want_idx, want_mask = P.route(scores, k_sel, 11, 0.125)
+    assert torch.equal(buffers["scores"], scores) and torch.equal(idx, want_idx) and torch.equal(buffers["mask"], want_mask)
+    assert torch.equal(out, P.sparse_attn_fwd(q, k, v, shape, want_idx, want_mask))
+    single, lse = P.forward_single_call(q, k, v, shape, 0.2, 11, 0.125, want_lse=True)
+    ws = P.kv_stats(k, v, shape)
+    want_idx, want_mask = P.route(P.block_score(q, k, shape, stats_ws=ws if group else None), k_sel, 11, 0.125)
+    want, want_lse = P.sparse_attn_fwd(q, k, v, shape, want_idx, want_mask, ws=ws, want_lse=True, prepared=True)
+    assert torch.equal(single, want) and torch.equal(lse, want_lse)
