@@ -57,25 +57,24 @@ PASA_DEVICE void pool_mean(const ScoreParams& p, int j, int bh, int which, char*
 // 32 elements: a quarter of a row (hi and lo) is exactly one 128-byte line, the workgroup fetches the quarters of
 // its 64 + 64 rows with fully coalesced 16-byte loads (eight lanes per line), parks them in LDS (rows padded to 144
 // bytes: conflict-free 16-byte reads down a column of rows), and every lane reads its operands from there.  Two LDS
-// buffers: the loads of the next quarter are in flight during the MFMAs of the current one.  In a quarter, lane
-// (x, h) holds elements [8h + 16m, 8h + 16m + 8) of its row for the MFMAs m = 0, 1.
+// buffers, one barrier a quarter.  What bounds a small grid is the time of a trip to memory: the quarters of a tile are requested all together (a quarter
+// at a time, one ahead of the MFMAs, was a trip each), those of the next tile of the run during the last quarter's MFMAs, and the queries' stay in
+// registers for the whole run.  With the runs of strips below, pooling and scores, us: 4140 tokens, 4 heads 8.9 -> 8.0; 32,760, 12 39.5 -> 38.4;
+// 118,800, 3 56.3 -> 50.5; 75,600, 40 440 -> 415.  In a quarter, lane (x, h) holds elements [8h + 16m, 8h + 16m + 8) of its row for the MFMAs m = 0, 1.
 constexpr int kScorePitch = 32 * 4 + 16, kScoreLds = 2 * 128 * kScorePitch;
 template <int D>
 PASA_DEVICE void score_gemm(const ScoreParams& p, int runs, int wg, char* lds_bytes) {
   constexpr int QF = 32;               // elements per quarter-row (stored as 32 bf16 hi + 32 bf16 lo = 32 floats' worth of bytes)
   constexpr int NQ = D / QF;           // quarters
   constexpr int PITCH = kScorePitch;   // bytes per LDS row
-  char(*const lds)[128 * PITCH] = reinterpret_cast<char(*)[128 * PITCH]>(lds_bytes);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, x = lane & 31, h = lane >> 5;
-  // Workgroup ids are decoded so that all workgroups of a head run on one XCD (the hardware deals consecutive ids
-  // round-robin to the 8 XCDs): the head's pooled means are then fetched into one L2 instead of eight.
+  // The hardware deals consecutive workgroup ids round-robin to the 8 XCDs: each XCD takes a run of consecutive strips, so that the pooled means of a
+  // head are fetched into one L2 or two instead of eight.
   const int n_tiles = (p.nb + 63) / 64;
-  const int per_head = runs * n_tiles;
-  // (with fewer than 16 heads that would leave XCDs idle: then ids simply run head by head)
-  const bool by_xcd = p.bh >= 16;
-  const int slot = by_xcd ? wg >> 3 : wg;
-  const int bh = by_xcd ? (slot / per_head) * 8 + (wg & 7) : slot / per_head;
-  if (bh >= p.bh) return;  // padding workgroup: leaves before any barrier
+  const int per_head = runs * n_tiles, total = p.bh * per_head, per_xcd = (total + 7) / 8;
+  const int slot = (wg & 7) * per_xcd + (wg >> 3);
+  if (slot >= total) return;  // padding workgroup: leaves before any barrier
+  const int bh = slot / per_head;
   const int within = slot % per_head;
   const int run_id = within % runs, i0 = (within / runs) * 64;
   // A workgroup owns a strip of 64 score rows and walks a run of 64-column tiles along it: the 256-byte row
@@ -89,43 +88,40 @@ PASA_DEVICE void score_gemm(const ScoreParams& p, int runs, int wg, char* lds_by
   const float* const kbar = p.kbar + (int64_t)bh * p.nb * D;
   // loader role: thread t fetches 16-byte chunk (t & 7) of tile rows (t >> 3) + 32 i, i = 0..3 (rows 0..63 are
   // pooled queries, 64..127 pooled keys); rows past the end are clamped: their products are never stored
-  // (the staging registers are four named variables and the two roles are macros: with an array captured by a
-  // lambda the compiler kept a copy of the staged values in scratch memory, four times the bytes of the scores)
   const int ld_row = tid >> 3, ld_col = (tid & 7) * 4;
-  const float* const src0 = qbar + (int64_t)min(i0 + ld_row, p.nb - 1) * D + ld_col;
-  const float* const src1 = qbar + (int64_t)min(i0 + ld_row + 32, p.nb - 1) * D + ld_col;
-  const float* src2 = nullptr;
-  const float* src3 = nullptr;
-  float4 st0, st1, st2, st3;
-#define PASA_SCORE_FETCH(qtr)                                        \
-  do {                                                               \
-    st0 = *reinterpret_cast<const float4*>(src0 + (qtr) * QF);       \
-    st1 = *reinterpret_cast<const float4*>(src1 + (qtr) * QF);       \
-    st2 = *reinterpret_cast<const float4*>(src2 + (qtr) * QF);       \
-    st3 = *reinterpret_cast<const float4*>(src3 + (qtr) * QF);       \
-  } while (0)
-#define PASA_SCORE_PARK(buf)                                                                       \
-  do {                                                                                             \
-    *reinterpret_cast<float4*>(&lds[buf][(ld_row) * PITCH + (tid & 7) * 16]) = st0;                \
-    *reinterpret_cast<float4*>(&lds[buf][(ld_row + 32) * PITCH + (tid & 7) * 16]) = st1;           \
-    *reinterpret_cast<float4*>(&lds[buf][(ld_row + 64) * PITCH + (tid & 7) * 16]) = st2;           \
-    *reinterpret_cast<float4*>(&lds[buf][(ld_row + 96) * PITCH + (tid & 7) * 16]) = st3;           \
-  } while (0)
+  typedef float f32x4 __attribute__((ext_vector_type(4)));  // (arrays of HIP's float4 were kept in scratch memory, four times the bytes of the scores)
+  f32x4 sq[NQ][2], sk[NQ][2];
+#pragma unroll
+  for (int qtr = 0; qtr < NQ; ++qtr)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      sq[qtr][i] = *reinterpret_cast<const f32x4*>(qbar + (int64_t)min(i0 + ld_row + 32 * i, p.nb - 1) * D + ld_col + qtr * QF);
+      sk[qtr][i] = *reinterpret_cast<const f32x4*>(kbar + (int64_t)min(jt0 * 64 + ld_row + 32 * i, p.nb - 1) * D + ld_col + qtr * QF);
+    }
+  char* const park = lds_bytes + ld_row * PITCH + (tid & 7) * 16;
   // consumer role: wave (wi, wj) multiplies query rows 32 wi + x with key rows 32 wj + x
   const int a_off = (32 * (wave >> 1) + x) * PITCH + h * 16, b_off = (64 + 32 * (wave & 1) + x) * PITCH + h * 16;
 #pragma unroll 1
   for (int jt = jt0; jt < jt1; ++jt) {
     const int j0 = jt * 64;
-    src2 = kbar + (int64_t)min(j0 + ld_row, p.nb - 1) * D + ld_col;
-    src3 = kbar + (int64_t)min(j0 + ld_row + 32, p.nb - 1) * D + ld_col;
     f32x16 acc = {0};
-    PASA_SCORE_FETCH(0);
-    PASA_SCORE_PARK(0);  // buffer 0 was last read two barriers ago
-    __syncthreads();
 #pragma unroll
     for (int qtr = 0; qtr < NQ; ++qtr) {
-      if (qtr + 1 < NQ) PASA_SCORE_FETCH(qtr + 1);
-      const char* buf = lds[qtr & 1];
+      // the buffer's readers finished before the previous barrier (NQ is even: a tile begins with the buffer that its predecessor did not end with)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        *reinterpret_cast<f32x4*>(park + (qtr & 1) * 128 * PITCH + 32 * i * PITCH) = sq[qtr][i];
+        *reinterpret_cast<f32x4*>(park + (qtr & 1) * 128 * PITCH + (64 + 32 * i) * PITCH) = sk[qtr][i];
+      }
+      __syncthreads();
+      if (qtr + 1 == NQ && jt + 1 < jt1) {
+#pragma unroll
+        for (int n = 0; n < NQ; ++n)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+            sk[n][i] = *reinterpret_cast<const f32x4*>(kbar + (int64_t)min(j0 + 64 + ld_row + 32 * i, p.nb - 1) * D + ld_col + n * QF);
+      }
+      const char* buf = lds_bytes + (qtr & 1) * 128 * PITCH;
       // operand fragments of 8 bf16: [m] hi, [2 + m] lo of elements 8h + 16m .. + 8
       bf16x8 a[4], b[4];
 #pragma unroll
@@ -139,10 +135,6 @@ PASA_DEVICE void score_gemm(const ScoreParams& p, int runs, int wg, char* lds_by
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m], b[2 + m], acc, 0, 0, 0);  // qh kl
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m], b[m], acc, 0, 0, 0);      // qh kh
       }
-      if (qtr + 1 < NQ) {
-        PASA_SCORE_PARK((qtr + 1) & 1);  // the other buffer: its readers finished before the previous barrier
-        __syncthreads();
-      }
     }
     // result register 4g + r of lane (x, h) is row 8g + 4h + r, column x of the wave's quarter
     const int j = j0 + 32 * (wave & 1) + x;
@@ -155,8 +147,6 @@ PASA_DEVICE void score_gemm(const ScoreParams& p, int runs, int wg, char* lds_by
       }
     }
   }
-#undef PASA_SCORE_FETCH
-#undef PASA_SCORE_PARK
 }
 
 // Workgroups of score_gemm: strips of 64 rows; a strip is cut into runs of column tiles only as far as it takes to fill the device
@@ -166,7 +156,7 @@ inline unsigned score_workgroups(const ScoreParams& p, int* runs_out) {
   int runs = (int)((2048 + strips - 1) / strips);
   runs = runs < 1 ? 1 : runs > tiles ? tiles : runs;
   *runs_out = runs;
-  return (unsigned)((p.bh >= 16 ? 8 * ((p.bh + 7) / 8) : p.bh) * runs * tiles);
+  return (unsigned)(8 * ((p.bh * runs * tiles + 7) / 8));
 }
 
 }  // namespace
