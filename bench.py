@@ -28,7 +28,7 @@ HBM_PEAK_BYTES_PER_S = 8.0e12   # MI355X HBM3E
 # measurement, "bench.traffic: workload=<name> group=<g> bytes_per_launch=<float> kernel_sha=<digest> measured=<date>",
 # where the digest names the attention kernel's sources at the time of the run: a figure measured on other sources is
 # not reported (roofline.traffic = null and roofline.traffic_source says why).
-KERNEL_SOURCES = ("pasa_attn.hip", "pasa_mfma_pipes.hpp", "pasa_device.hpp", "pasa_kernels.hpp")
+KERNEL_SOURCES = ("pasa_attn.hip", "pasa_quad.hpp", "pasa_mfma_pipes.hpp", "pasa_device.hpp", "pasa_kernels.hpp")
 
 
 def kernel_source_digest():

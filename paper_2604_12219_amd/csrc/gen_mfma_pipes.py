@@ -1181,7 +1181,7 @@ def gen():
         clob = ", ".join([f'"v{r}"' for r in range(168, 200)] + [f'"v{r}"' for r in range(216, 256)] +
                          ['"memory"', '"scc"', '"vcc"', '"m0"'])
         out.append(f"  asm volatile(\n{text}\n      : {', '.join(outs)}\n      : {', '.join(ins)}\n      : {clob});\n}}\n\n")
-    for D, waves in ((128, 4), (128, 8), (64, 4), (64, 8)):
+    for D, waves in ((128, 4), (64, 4)):
         ns, nt = D // 16, D // 32
         ni = tile_loads(D, waves)
         dma_ins = ['[sb] "s"(sb)', '[ls] "s"(ls)'] + [f'[x{j}] "v"(x[{j}])' for j in range(ni)]
