@@ -195,11 +195,15 @@ bool sparse_deep(const pasa_shape_t* s, int32_t k_sel) {
 //   32,760 tokens (x 512 blocks): 12 heads, 77 blocks 1331 / 1383, 179 blocks 2615 / 2620; 47,040: 8 heads, 110: 1898 / 1865, 257: 3844 / 3586;
 //   20 heads, 110: 4628 / 4755; 60,480: 8 heads, 47: 1467 / 1565, 142: 3169 / 3124; 75,600: 5 heads, 59: 1448 / 1453, 177: 3228 / 2982; 20 heads,
 //   59: 5732 / 6006, 177: 12,666 / 12,099; 118,800: 3 heads, 93: 2137 / 2183, 279: 5210 / 4702; 147,600: 6 heads, 115: 6853 / 6688, 346: 16,168 / 13,852
+// With the covariance prior the query blocks select much the same key blocks, which the caches then hold, and there is less to save; the host cannot see
+// that, so the keys and values of all heads must exceed the memory-side cache (256 MB).  Whole calls, two / four, without the prior and with it:
+//   5 heads of 75,600 (194 MB), 177 blocks 3383 / 3143, 3062 / 3144; 3 of 118,800 (182 MB), 279 blocks 5147 / 4766, 4264 / 4521; 40 of 75,600 (1.5 GB),
+//   177 blocks 26,053 / 24,614, 25,278 / 24,898; 5 of 147,600 (378 MB), 277 blocks, with it 10,185 / 10,148; 12 of 75,600 (464 MB), 355 blocks 14,085 / 12,317
 // Blocks of 128 tokens: 147,600 tokens, 6 heads, 58 blocks 4780 / 4889, 173: 11,014 / 11,338 (not taken).
 bool sparse_quad(const pasa_shape_t* s, int32_t k_sel) {
   const int nb = num_blocks(s);
   return s->d == 128 && s->block == 64 && s->kv_slices <= 1 && s->n >= 64 && s->n / 64 <= kQuadMaxTiles && (s->group == 0 || s->group >= 32) && nb >= k_sel &&
-         k_sel >= 100 && (int64_t)k_sel * s->n >= 8000000;
+         k_sel >= 100 && (int64_t)k_sel * s->n >= 8000000 && (int64_t)s->B * s->H * s->n * (4 * s->d) > (int64_t)(256 << 20);
 }
 
 // Whether a whole forward runs statistics and scoring in two launches instead of four (pasa_fused.hip).  The pooling then runs with the two workgroups a

@@ -464,7 +464,7 @@ def test_workgroups_of_four_query_blocks_against_two(P, n, heads, group, kind):
     the bitmap, so the same bitmap is given to both.  Numbers of query blocks with 0 to 3 left over, ragged last blocks of 1 and 63 tokens; equal numbers
     of selected blocks (routed), very different ones in neighbouring rows, none and all of them (uneven), four rows alike, four rows without a common
     block, one block, no whole block at all in some rows (empty), as many key blocks as can be planned and a ragged one more"""
-    _compare_routes(P, n, heads, 128, group, kind, 353)
+    _compare_routes(P, n, max(heads, (512 << 10) // n + 1), 128, group, kind, 353)
 
 
 @pytest.mark.parametrize("n,heads,d,group,kind", [
