@@ -1,7 +1,7 @@
 // Statistics and scoring in the same launches, for the calls that run both (the whole forward): neither needs the other's first kernel.
 // A launch with the gap before it takes 2.5 us or more whatever is in it, and the statistics' few workgroups leave most of the device idle for as long as
-// they walk their units: the pooling fills it.  us, four launches / two (with the keys pooled): 1024 tokens, 2 heads, d = 64 12.6 / 7.9;
-// 4140 tokens, 4 heads, d = 128, groups of 64 23.5 / 17.0.  Which calls take it: stats_and_score_together in pasa_api.hip.
+// they walk their units: the pooling fills it.  us, four launches / two (with the keys pooled): 1024 tokens, 2 heads, d = 64 12.1 / 7.6;
+// 4140 tokens, 4 heads, d = 128, groups of 64 22.6 / 16.0.  Which calls take it: stats_and_score_together in pasa_api.hip.
 #include "pasa_score.hpp"
 #include "pasa_stats.hpp"
 
