@@ -319,19 +319,28 @@ int pasa_block_score(const void* q, const void* k, const pasa_shape_t* shape, co
   return block_score_impl(q, k, shape, key_bias, scores, ws, ws_bytes, nullptr, stream);
 }
 
-static int route_impl(const float* scores, int32_t BH, int32_t n_blocks, int32_t k_sel, uint64_t seed, float noise_amp,
-                      int gumbel, int32_t* idx, uint32_t* mask, void* stream) {
+static int route_params(const float* scores, int32_t BH, int32_t n_blocks, int32_t k_sel, uint64_t seed, float noise_amp, int gumbel, int32_t* idx,
+                        uint32_t* mask, RouteParams* out) {
   if (!scores || !idx || BH < 1 || n_blocks < 1) return PASA_EINVAL;
   if (k_sel < 1 || k_sel > n_blocks) return PASA_EINVAL;
   if (!(noise_amp >= 0.f) || isinf(noise_amp)) return PASA_EINVAL;
   if (n_blocks > kRouteMaxBlocks) return PASA_EUNSUPPORTED;
-  RouteParams p{};
+  RouteParams& p = *out;
+  p = RouteParams{};
   p.scores = scores;
   p.bh = BH; p.nb = n_blocks; p.k_sel = k_sel; p.mask_words = (n_blocks + 31) / 32;
   p.seed_lo = (uint32_t)(seed & 0xffffffffu); p.seed_hi = (uint32_t)(seed >> 32);
   p.amp = noise_amp;
   p.gumbel = gumbel;
   p.idx = idx; p.mask = mask;
+  return PASA_OK;
+}
+
+static int route_impl(const float* scores, int32_t BH, int32_t n_blocks, int32_t k_sel, uint64_t seed, float noise_amp,
+                      int gumbel, int32_t* idx, uint32_t* mask, void* stream) {
+  RouteParams p;
+  const int rc = route_params(scores, BH, n_blocks, k_sel, seed, noise_amp, gumbel, idx, mask, &p);
+  if (rc != PASA_OK) return rc;
   return pasa_launch_route(p, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
@@ -441,23 +450,6 @@ int pasa_kv_stats(const void* k, const void* v, const pasa_shape_t* shape, void*
   return kv_stats_impl(k, v, shape, nullptr, 0, ws, ws_bytes, stream);
 }
 
-// scoring and statistics of a whole forward; pool_k: the scores' block-mean keys are pooled as pasa_block_score does, not taken from the statistics
-static int score_and_stats(const void* q, const void* k, const void* v, const pasa_shape_t* shape, float* scores, void* score_ws, size_t score_bytes,
-                           void* attn_ws, size_t attn_bytes, bool pool_k, void* stream) {
-  StatsParams t;
-  int rc = stats_params(k, v, shape, nullptr, 0, attn_ws, attn_bytes, &t);
-  if (rc != PASA_OK) return rc;
-  if (t.group == 0) return block_score_impl(q, k, shape, nullptr, scores, score_ws, score_bytes, nullptr, stream);
-  ScoreParams p;
-  rc = score_params(q, k, shape, nullptr, scores, score_ws, score_bytes, pool_k ? nullptr : t.kbar_split, &p);
-  if (rc != PASA_OK) return rc;
-  if (!stats_and_score_together(shape)) {
-    return pasa_launch_kv_stats(t, static_cast<hipStream_t>(stream)) == hipSuccess && pasa_launch_block_score(p, static_cast<hipStream_t>(stream)) == hipSuccess
-               ? PASA_OK : PASA_EHIP;
-  }
-  return pasa_launch_stats_and_score(t, p, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
-}
-
 int pasa_key_prior(const void* k, const void* v, const pasa_shape_t* shape, float eps, float* beta, void* ws,
                    size_t ws_bytes, void* stream) {
   pasa_shape_t s;
@@ -482,9 +474,10 @@ int pasa_key_prior(const void* k, const void* v, const pasa_shape_t* shape, floa
   return pasa_launch_key_prior(t, eps, beta, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
-static int attn_common(const void* q, const void* k, const void* v, const pasa_shape_t* shape, const int32_t* idx,
-                       const uint32_t* mask, int32_t k_sel, void* out, float* lse, void* ws, size_t ws_bytes,
-                       void* stream, bool sparse, bool with_stats) {
+// Everything but the launches: checks the arguments and fills what the attention kernel is launched with.
+// *build: the bitmap that has to be built from the index lists first (the caller gave none), null if there is nothing to build
+static int attn_params(const void* q, const void* k, const void* v, const pasa_shape_t* shape, const int32_t* idx, const uint32_t* mask, int32_t k_sel,
+                       void* out, float* lse, void* ws, size_t ws_bytes, bool sparse, AttnParams* params, uint32_t** build) {
   pasa_shape_t s;
   const int rc = check_attn_args(shape, sparse, ws, ws_bytes, &s);
   if (rc != PASA_OK) return rc;
@@ -496,14 +489,11 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
     if ((!idx && !mask) || k_sel < 1 || k_sel > nb) return PASA_EINVAL;
     if ((idx && !aligned4(idx)) || (mask && !aligned4(mask))) return PASA_EALIGN;
   }
-  const bool mask_with_stats = sparse && with_stats && !mask && s.group > 0;  // (without the approximation there is no statistics launch)
-  if (sparse && with_stats) {
-    const int rs = kv_stats_impl(k, v, &s, mask_with_stats ? idx : nullptr, k_sel, ws, ws_bytes, stream);
-    if (rs != PASA_OK) return rs;
-  }
   const AttnWorkspace w = carve_attn(&s);
   char* base = static_cast<char*>(ws);
-  AttnParams a{};
+  AttnParams& a = *params;
+  a = AttnParams{};
+  *build = nullptr;
   a.q = static_cast<const uint16_t*>(q); a.k = static_cast<const uint16_t*>(k); a.v = static_cast<const uint16_t*>(v);
   a.o = static_cast<uint16_t*>(out); a.lse = lse;
   a.stride_b = s.stride_b; a.stride_h = s.stride_h; a.stride_n = s.stride_n;
@@ -512,11 +502,8 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
   a.n_slices = 1;
   if (sparse) {
     if (!mask) {  // the caller has index lists only: the bitmap the kernel walks is built from them
-      uint32_t* built = reinterpret_cast<uint32_t*>(base + w.bitmap);
-      if (!mask_with_stats &&
-          pasa_launch_mask_from_idx(idx, (int64_t)s.B * s.H * nb, nb, k_sel, built, static_cast<hipStream_t>(stream)) != hipSuccess)
-        return PASA_EHIP;
-      mask = built;
+      *build = reinterpret_cast<uint32_t*>(base + w.bitmap);
+      mask = *build;
     }
     a.idx = idx; a.mask = mask; a.k_sel = k_sel; a.mask_words = (nb + 31) / 32;
     a.group = s.group >= nb ? nb : s.group;
@@ -532,7 +519,25 @@ static int attn_common(const void* q, const void* k, const void* v, const pasa_s
   a.teams = !sparse && dense_teams(&s);
   a.deep = sparse && sparse_deep(&s, k_sel);
   a.wide = sparse ? !a.deep && sparse_quad(&s, k_sel) : !a.teams && dense_wide(&s);
-  return pasa_launch_attn(a, sparse, s.d, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
+  return PASA_OK;
+}
+
+static int attn_common(const void* q, const void* k, const void* v, const pasa_shape_t* shape, const int32_t* idx,
+                       const uint32_t* mask, int32_t k_sel, void* out, float* lse, void* ws, size_t ws_bytes,
+                       void* stream, bool sparse, bool with_stats) {
+  AttnParams a;
+  uint32_t* build;
+  const int rc = attn_params(q, k, v, shape, idx, mask, k_sel, out, lse, ws, ws_bytes, sparse, &a, &build);
+  if (rc != PASA_OK) return rc;
+  const bool mask_with_stats = with_stats && build && a.group > 0;  // (without the approximation there is no statistics launch)
+  if (with_stats) {
+    const int rs = kv_stats_impl(k, v, shape, mask_with_stats ? idx : nullptr, k_sel, ws, ws_bytes, stream);
+    if (rs != PASA_OK) return rs;
+  }
+  if (build && !mask_with_stats &&
+      pasa_launch_mask_from_idx(idx, (int64_t)a.bh * a.nb, a.nb, k_sel, build, static_cast<hipStream_t>(stream)) != hipSuccess)
+    return PASA_EHIP;
+  return pasa_launch_attn(a, sparse, shape->d, static_cast<hipStream_t>(stream)) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
 int pasa_sparse_attn_fwd(const void* q, const void* k, const void* v, const pasa_shape_t* shape, const int32_t* idx,
@@ -596,15 +601,35 @@ ForwardWorkspace carve_forward(const pasa_shape_t* s, double keep_ratio) {
 }
 }  // namespace
 
+// The stages of a whole forward.  Every argument of every stage is checked before the first launch.
 // pool_k: the scores' block-mean keys are pooled as pasa_block_score does it, not taken from the statistics (the two differ in the last place)
 static int forward_stages(const void* q, const void* k, const void* v, const pasa_shape_t* shape, int32_t k_sel, uint64_t seed, float noise_amp,
                           float* scores, int32_t* idx, uint32_t* mask, void* score_ws, size_t score_bytes, void* attn_ws, size_t attn_bytes, void* out,
                           float* lse, bool pool_k, void* stream) {
-  int r = score_and_stats(q, k, v, shape, scores, score_ws, score_bytes, attn_ws, attn_bytes, pool_k, stream);
-  if (r != PASA_OK) return r;
-  r = pasa_route(scores, shape->B * shape->H, num_blocks(shape), k_sel, seed, noise_amp, idx, mask, stream);
-  if (r != PASA_OK) return r;
-  return pasa_sparse_attn_fwd_prepared(q, k, v, shape, idx, mask, k_sel, out, lse, attn_ws, attn_bytes, stream);
+  StatsParams t;
+  ScoreParams p;
+  RouteParams r;
+  AttnParams a;
+  uint32_t* build;
+  int rc = stats_params(k, v, shape, nullptr, 0, attn_ws, attn_bytes, &t);
+  if (rc != PASA_OK) return rc;
+  const bool approx = t.group > 0;  // otherwise there are no statistics, and no key means in them
+  rc = score_params(q, k, shape, nullptr, scores, score_ws, score_bytes, pool_k || !approx ? nullptr : t.kbar_split, &p);
+  if (rc != PASA_OK) return rc;
+  rc = route_params(scores, shape->B * shape->H, num_blocks(shape), k_sel, seed, noise_amp, 0, idx, mask, &r);
+  if (rc != PASA_OK) return rc;
+  rc = attn_params(q, k, v, shape, idx, mask, k_sel, out, lse, attn_ws, attn_bytes, true, &a, &build);
+  if (rc != PASA_OK) return rc;
+
+  const hipStream_t on = static_cast<hipStream_t>(stream);
+  if (approx && stats_and_score_together(shape)) {
+    if (pasa_launch_stats_and_score(t, p, on) != hipSuccess) return PASA_EHIP;
+  } else {
+    if (approx && pasa_launch_kv_stats(t, on) != hipSuccess) return PASA_EHIP;
+    if (pasa_launch_block_score(p, on) != hipSuccess) return PASA_EHIP;
+  }
+  if (pasa_launch_route(r, on) != hipSuccess) return PASA_EHIP;
+  return pasa_launch_attn(a, true, shape->d, on) == hipSuccess ? PASA_OK : PASA_EHIP;
 }
 
 size_t pasa_forward_workspace_bytes(const pasa_shape_t* shape, double keep_ratio) { return carve_forward(shape, keep_ratio).total; }

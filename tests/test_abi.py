@@ -178,6 +178,49 @@ def test_argument_validation_returns_before_any_launch(P):
         assert isinstance(L.pasa_strerror(code), bytes) and len(L.pasa_strerror(code)) > 0
 
 
+def test_whole_forward_checks_every_stage_before_the_first_launch(P):
+    """an argument that only a later stage looks at is reported before anything is enqueued: without a device a launch would give PASA_EHIP.
+    (CPU only: the pointers are no buffers)"""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("a launch that came too early would write through these pointers")
+    L = P.load_library()
+    EINVAL, EUNSUPPORTED, EWORKSPACE, EALIGN, EHIP = -1, -2, -3, -4, -5
+    ok, big = dict(q=0x1000, k=0x1000, v=0x1000, out=0x2000), 1 << 40
+
+    def buffers(shape, amp=0.1, k_sel=4, scores=0x3000, idx=0x4000, mask=0x5000, sws=0x6000, aws=0x7000, score_bytes=big, attn_bytes=big, **ptr):
+        a = dict(ok, **ptr)
+        return L.pasa_forward_buffers(a["q"], a["k"], a["v"], ctypes.byref(shape.c()), k_sel, 7, amp, scores, idx, mask, sws, score_bytes, aws, attn_bytes,
+                                      a["out"], None, None)
+
+    def single(shape, amp=0.1, **ptr):
+        a = dict(ok, **ptr)
+        return L.pasa_forward(a["q"], a["k"], a["v"], ctypes.byref(shape.c()), 0.15, 7, amp, a["out"], None, 0x6000, big, None)
+
+    for shape in (_shape(P), _shape(P, group=0), _shape(P, H=40, n=75_600), _shape(P, d=64, n=1000), _shape(P, block=128, group=16)):
+        nb = P.num_blocks(shape)
+        for call in (buffers, single):
+            assert call(shape) == EHIP  # (nothing to object to: the first launch)
+            for name in ("q", "k", "v", "out"):
+                assert call(shape, **{name: None}) == EINVAL, name
+                assert call(shape, **{name: 0x1008}) == EALIGN, name
+            assert call(shape, out=0x1000) == EINVAL  # output aliases an input
+            for amp in (-1.0, float("inf"), float("nan")):
+                assert call(shape, amp=amp) == EINVAL
+        assert buffers(shape, k_sel=0) == EINVAL and buffers(shape, k_sel=-1) == EINVAL and buffers(shape, k_sel=nb + 1) == EINVAL
+        assert buffers(shape, k_sel=nb) == EHIP
+        for name in ("scores", "idx", "mask", "sws", "aws"):
+            assert buffers(shape, **{name: None}) == EINVAL, name
+        assert buffers(shape, scores=0x3004) == EALIGN and buffers(shape, sws=0x6004) == EALIGN and buffers(shape, aws=0x7004) == EALIGN
+        assert buffers(shape, idx=0x4002) == EALIGN and buffers(shape, mask=0x5002) == EALIGN
+        assert buffers(shape, score_bytes=P.score_workspace_bytes(shape) - 1) == EWORKSPACE
+        assert buffers(shape, attn_bytes=attn_layout(shape)[0] - 1) == EWORKSPACE
+        assert buffers(shape, score_bytes=P.score_workspace_bytes(shape), attn_bytes=attn_layout(shape)[0]) == EHIP
+    for call in (buffers, single):
+        assert call(_shape(P, group=48)) == EUNSUPPORTED and call(_shape(P, d=96)) == EUNSUPPORTED and call(_shape(P, n=5000 * 64)) == EUNSUPPORTED
+        assert call(_shape(P, kv_slices=12)) == EUNSUPPORTED and call(_shape(P, scale=-1.0)) == EINVAL and call(_shape(P, n=0)) == EINVAL
+
+
 def _forward_bytes(P, s, keep):
     bh, nb = s.B * s.H, P.num_blocks(s)
     return (align256(bh * nb * nb * 4) + align256(bh * nb * P.topk_count(nb, keep) * 4) + align256(bh * nb * -(-nb // 32) * 4) +
