@@ -497,23 +497,25 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
     quad_plan(shared, rows, n_whole, wave, lane);
     settle_q();
     QuadPasses(shared, kb, vb, row_bytes, group, wave, lane, p.c).all(w.qf, w.o, w.m, w.l);
-    // the ragged last key block: fetched shifted back, for all groups; weights zero where it is not selected
+    // the ragged last key block: fetched shifted back, for all groups.  Waves whose query block did not select it leave it alone: weights of
+    // zero would not do where its values are not finite
     if (n_whole < p.nb) {
       uint32_t any = 0u;
 #pragma unroll
       for (int g = 0; g < GROUPS; ++g) any |= rows[g][n_whole >> 5];
       if ((uniform((int)any) >> (n_whole & 31)) & 1) {
-        const bool mine = (mask_row[n_whole >> 5] >> (n_whole & 31)) & 1u;
         const int r0 = n_whole * 64;
         ring_barrier<NI>(0);  // every wave is done with the ring
         request(kb, r0, 0);
         request(vb, r0, 1);
         ring_barrier<NI>(0);
-        f32x16 s0, s1;
-        bf16x8 pf[4];
-        pipes::rows_x_q(slot(0) + lo.k, w.qf, s0, s1);
-        exact_tile_softmax<D>(s0, s1, w, p.c, mine ? r0 - tile_row(r0) : 64, n - tile_row(r0), lane, pf);
-        pipes::cols_x_p64(slot(1) + lo.v[0], slot(1) + lo.v[1], pf, w.o);
+        if ((uniform((int)mask_row[n_whole >> 5]) >> (n_whole & 31)) & 1) {
+          f32x16 s0, s1;
+          bf16x8 pf[4];
+          pipes::rows_x_q(slot(0) + lo.k, w.qf, s0, s1);
+          exact_tile_softmax<D>(s0, s1, w, p.c, r0 - tile_row(r0), n - tile_row(r0), lane, pf);
+          pipes::cols_x_p64(slot(1) + lo.v[0], slot(1) + lo.v[1], pf, w.o);
+        }
       }
     }
   }

@@ -524,6 +524,29 @@ def _compare_routes(P, n, heads, d, group, kind, declared):
     np.testing.assert_allclose(lse4.cpu().numpy(), lse2.cpu().numpy(), atol=1e-3)
 
 
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_values_of_a_ragged_block_that_a_neighbour_selected_stay_out(P, bad):
+    """workgroups of four query blocks fetch the ragged last key block for whichever of them selected it; without the approximation a query
+    block that did not select it must not see its values, also where they are not finite"""
+    n, heads, declared = 66000, 12, 353
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    q, k, v = (torch.randn((1, heads, n, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    shape = P.Shape.of(q, block=64, group=0)
+    nb = P.num_blocks(shape)
+    chosen = torch.rand((1, nb, nb), generator=g, device="cuda") < 0.02
+    chosen[:, :, 0] = True
+    chosen[:, :, nb - 1] = torch.arange(nb, device="cuda") % 4 == 1
+    mask = _bitmap(chosen).expand(heads, -1, -1).contiguous()
+    clean = P.sparse_attn_fwd(q, k, v, shape, None, mask, k_sel=declared)
+    v[:, :, 64 * (nb - 1):] = bad
+    out = P.sparse_attn_fwd(q, k, v, shape, None, mask, k_sel=declared)
+    torch.cuda.synchronize()
+    selected = (torch.arange(n, device="cuda") // 64) % 4 == 1
+    assert torch.equal(out[:, :, ~selected], clean[:, :, ~selected])
+    assert not torch.isfinite(out[:, :, selected].float()).any()
+
+
 @pytest.mark.parametrize("n,heads,d,block", [(65536, 9, 128, 64), (65537, 7, 128, 64), (65537, 8, 128, 64), (131072, 1, 64, 64),
                                               (128 * 2049 + 77, 1, 64, 128)])
 def test_blocks_visited_first_at_the_ends_of_the_rule(P, n, heads, d, block):
