@@ -111,6 +111,19 @@ PASA_API size_t pasa_score_workspace_bytes(const pasa_shape_t* shape);
  * floating-point summation order only. */
 PASA_API size_t pasa_attn_workspace_bytes(const pasa_shape_t* shape);
 
+/* host-only.  Which form of the attention kernel a call with this shape takes: k_sel > 0 for the sparse entry points with that k_sel, 0 for
+ * pasa_attn_dense_ref; a negative status for a bad shape or k_sel.  (pasa_sparse_attn_fwd_static: as with kv_slices = 1.)  The forms differ in speed and in the order of summation, not in what they compute
+ * (for tests and measurements; the choice may change with the library). */
+enum {
+  PASA_ATTN_WHOLE = 0,  /* a workgroup of four waves walks all keys of its 128 query rows     */
+  PASA_ATTN_SLICED = 1, /* key-range slicing (kv_slices > 1)                                  */
+  PASA_ATTN_TEAMS = 2,  /* dense: two teams of four waves, half of the keys each              */
+  PASA_ATTN_WIDE = 3,   /* dense: eight waves, 256 query rows                                 */
+  PASA_ATTN_QUAD = 4,   /* sparse: eight waves, four query blocks of 64 tokens                */
+  PASA_ATTN_DEEP = 5    /* sparse: two query blocks of 64 tokens, twice the tiles in flight   */
+};
+PASA_API int32_t pasa_attn_variant(const pasa_shape_t* shape, int32_t k_sel);
+
 /*
  * Stage 1 -- block-pooled scoring (Sec. "Taylor Expansion Approximation", Eq.8).
  *   scores[bh, i, j] = mean(Q block i) . mean(K block j) * scale + key_bias[bh, j]

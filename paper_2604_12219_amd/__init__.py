@@ -9,6 +9,7 @@ from .pasa import (  # noqa: F401
     PasaError,
     Shape,
     attn_dense_ref,
+    attn_variant,
     attn_workspace_bytes,
     block_score,
     check_selection,

@@ -206,6 +206,13 @@ bool sparse_quad(const pasa_shape_t* s, int32_t k_sel) {
          k_sel >= 100 && (int64_t)k_sel * s->n >= 8000000 && (int64_t)s->B * s->H * s->n * (4 * s->d) > (int64_t)(256 << 20);
 }
 
+// The form of the attention kernel a call takes (k_sel: declared number of selected key blocks; dense: not looked at)
+AttnVariant attn_variant(const pasa_shape_t* s, bool sparse, int32_t k_sel) {
+  if (!sparse) return dense_teams(s) ? kTeams : dense_wide(s) ? kWide : kWhole;
+  if (choose_slices(s) > 1) return kSliced;
+  return sparse_deep(s, k_sel) ? kDeep : sparse_quad(s, k_sel) ? kQuad : kWhole;
+}
+
 // Whether a whole forward runs statistics and scoring in two launches instead of four (pasa_fused.hip).  The pooling then runs with the two workgroups a
 // compute unit of the statistics: enough for tensors that are in cache or nearly so, not for the rate of the memory.  us, four / two, by MB of Q:
 //   d = 128: 1024 tokens, 16 heads (4) 21.9 / 16.6; 2048, 40 (21) 39.3 / 29.4; 4140, 12 (13) 30.0 / 23.9; 9900, 16 (41) 52.3 / 47.8; 32,760, 2 (17)
@@ -280,6 +287,19 @@ size_t pasa_attn_workspace_bytes(const pasa_shape_t* shape) {
   if (check_group(shape->group, num_blocks(shape)) != PASA_OK) return 0;
   if (check_slices(shape) != PASA_OK) return 0;
   return carve_attn(shape).total;  // never zero for a valid shape (it holds a bitmap), so that 0 always means "bad shape"
+}
+
+int32_t pasa_attn_variant(const pasa_shape_t* shape, int32_t k_sel) {
+  const int rc = check_shape(shape);
+  if (rc != PASA_OK) return rc;
+  if (k_sel < 0 || k_sel > num_blocks(shape)) return PASA_EINVAL;
+  if (k_sel > 0) {
+    const int rg = check_group(shape->group, num_blocks(shape));
+    if (rg != PASA_OK) return rg;
+    const int rs = check_slices(shape);
+    if (rs != PASA_OK) return rs;
+  }
+  return attn_variant(shape, k_sel > 0, k_sel);
 }
 
 static int score_params(const void* q, const void* k, const pasa_shape_t* shape, const float* key_bias, float* scores, void* ws, size_t ws_bytes,
@@ -516,9 +536,7 @@ static int attn_params(const void* q, const void* k, const void* v, const pasa_s
     a.part_ml = reinterpret_cast<float*>(base + w.part_ml);
     a.queue = reinterpret_cast<uint32_t*>(base + w.queue);
   }
-  a.teams = !sparse && dense_teams(&s);
-  a.deep = sparse && sparse_deep(&s, k_sel);
-  a.wide = sparse ? !a.deep && sparse_quad(&s, k_sel) : !a.teams && dense_wide(&s);
+  a.variant = attn_variant(&s, sparse, k_sel);
   return PASA_OK;
 }
 

@@ -305,10 +305,7 @@ struct BitWalk {
 // Kernel variants.  MODE 0: dense (every tile); 1: sparse, one 128-token query block per workgroup;
 // 2: sparse, two adjacent 64-token query blocks per workgroup.  MULTI: the group has fewer than 32
 // blocks, so a chunk of 32 blocks intersects several groups and the per-block weights of a chunk have
-// to be kept until all of its group matrices have passed.  PART: kWhole: a workgroup walks all keys of its
-// query tile; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two teams of waves; kWide (dense): eight waves, 256 query rows; kQuad (sparse):
-// eight waves, four query blocks of 64 tokens (pasa_quad.hpp); kDeep (sparse, two 64-token blocks): a ring of eight tiles.
-enum : int { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3, kQuad = 4, kDeep = 5 };
+// to be kept until all of its group matrices have passed.  PART: see AttnVariant.
 constexpr int teams_of(int part) { return part == kTeams ? 2 : 1; }
 constexpr int waves_of(int part) { return part == kWide || part == kQuad ? 8 : 4; }  // of a team
 template <int D, int MODE, bool MULTI, int PART>
@@ -1106,15 +1103,16 @@ hipError_t launch(const AttnParams& p, int grid, hipStream_t stream) {
 template <int D, int MODE, bool MULTI>
 hipError_t launch_part(const AttnParams& p, int grid, hipStream_t stream) {
   if constexpr (MODE == 0) {
-    if (p.teams) return launch<D, MODE, MULTI, kTeams>(p, grid, stream);
-    if (p.wide) return launch<D, MODE, MULTI, kWide>(p, grid, stream);
+    if (p.variant == kTeams) return launch<D, MODE, MULTI, kTeams>(p, grid, stream);
+    if (p.variant == kWide) return launch<D, MODE, MULTI, kWide>(p, grid, stream);
   } else {
-    if (p.n_slices > 1) return launch<D, MODE, MULTI, kSliced>(p, grid, stream);
+    if (p.variant == kSliced) return launch<D, MODE, MULTI, kSliced>(p, grid, stream);
     if constexpr (MODE == 2)
-      if (p.deep) return launch<D, MODE, MULTI, kDeep>(p, grid, stream);
+      if (p.variant == kDeep) return launch<D, MODE, MULTI, kDeep>(p, grid, stream);
     if constexpr (D == kQuadDim && MODE == 2 && !MULTI)
-      if (p.wide) return launch<D, MODE, MULTI, kQuad>(p, grid, stream);
+      if (p.variant == kQuad) return launch<D, MODE, MULTI, kQuad>(p, grid, stream);
   }
+  if (p.variant != kWhole) return hipErrorInvalidValue;  // (the grid is made for the variant)
   return launch<D, MODE, MULTI, kWhole>(p, grid, stream);
 }
 
@@ -1130,7 +1128,7 @@ hipError_t launch_d(const AttnParams& p, bool sparse, int grid, hipStream_t stre
 
 hipError_t pasa_launch_attn(AttnParams p, bool sparse, int d, hipStream_t stream) {
   p.c = p.scale * kLog2e;
-  const int tile = p.wide ? 256 : 128;  // query rows per workgroup
+  const int tile = 32 * waves_of(p.variant);  // query rows per workgroup
   p.q_tiles = (p.n + tile - 1) / tile;
   p.q_tiles_per_xcd = (p.q_tiles + kXcds - 1) / kXcds;
   int grid = p.bh * kXcds * p.q_tiles_per_xcd;

@@ -5,6 +5,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+// Forms of the attention kernel (attn_kernel in pasa_attn.hip); which call takes which: attn_variant in pasa_api.hip.
+// kWhole: a workgroup walks all keys of its 128 query rows; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two
+// teams of waves with half of the keys each; kWide (dense): eight waves, 256 query rows; kQuad (sparse): eight waves, four query blocks of 64 tokens
+// (pasa_quad.hpp); kDeep (sparse, two 64-token blocks): a ring of eight tiles.  The numbers are those of PASA_ATTN_* in pasa.h.
+enum AttnVariant : int32_t { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3, kQuad = 4, kDeep = 5 };
+
 struct AttnParams {
   const uint16_t* q;
   const uint16_t* k;
@@ -25,9 +31,7 @@ struct AttnParams {
   int32_t group, n_groups, n_chunks;
   // key-range slicing (sparse path): slice s covers chunks [s*n_chunks/n_slices, (s+1)*n_chunks/n_slices)
   int32_t n_slices;      // 1 = off (the attention kernel writes the output itself)
-  int32_t teams;         // dense path, 1: the keys of a query tile are halved between two teams of waves of a workgroup
-  int32_t wide;          // 1: workgroups of 256 query rows (dense: one key walk for all of them; sparse: pasa_quad.hpp)
-  int32_t deep;          // sparse path, 1: a ring of eight tiles
+  AttnVariant variant;
   float* part_o;         // fp32 [BH][n_slices][n][d]: unnormalised partial numerators
   float* part_ml;        // fp32 [BH][n_slices][n][2]: running maximum (log2 units) and partial normaliser
   uint32_t* queue;       // [8] work-item counters, one per XCD (reset by the launcher)

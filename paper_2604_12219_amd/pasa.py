@@ -16,7 +16,7 @@ _LIB_PATH = os.path.join(_HERE, "libpasa_hip.so")
 _lib = None
 
 EXPORTS = ("pasa_strerror", "pasa_topk_count", "pasa_num_blocks", "pasa_mask_words", "pasa_score_workspace_bytes",
-           "pasa_attn_workspace_bytes", "pasa_block_score", "pasa_block_score_with_stats", "pasa_route", "pasa_route_gumbel", "pasa_kv_stats", "pasa_key_prior", "pasa_sparse_attn_fwd",
+           "pasa_attn_workspace_bytes", "pasa_attn_variant", "pasa_block_score", "pasa_block_score_with_stats", "pasa_route", "pasa_route_gumbel", "pasa_kv_stats", "pasa_key_prior", "pasa_sparse_attn_fwd",
            "pasa_sparse_attn_fwd_prepared", "pasa_sparse_attn_fwd_static", "pasa_forward", "pasa_forward_buffers", "pasa_forward_workspace_bytes", "pasa_check_selection", "pasa_attn_dense_ref", "pasa_l1_workspace_bytes", "pasa_l1_distance",
            "pasa_budget_schedule", "pasa_mfma_probe")
 
@@ -87,6 +87,8 @@ def load_library() -> ctypes.CDLL:
         L.pasa_score_workspace_bytes.argtypes = [sp]
         L.pasa_attn_workspace_bytes.restype = ctypes.c_size_t
         L.pasa_attn_workspace_bytes.argtypes = [sp]
+        L.pasa_attn_variant.restype = ctypes.c_int32
+        L.pasa_attn_variant.argtypes = [sp, ctypes.c_int32]
         L.pasa_block_score.restype = ctypes.c_int
         L.pasa_block_score.argtypes = [vp, vp, sp, vp, vp, vp, ctypes.c_size_t, vp]
         L.pasa_block_score_with_stats.restype = ctypes.c_int
@@ -205,6 +207,17 @@ def score_workspace_bytes(shape: Shape) -> int:
 
 def attn_workspace_bytes(shape: Shape) -> int:
     return load_library().pasa_attn_workspace_bytes(ctypes.byref(shape.c()))
+
+
+ATTN_VARIANTS = ("whole", "sliced", "teams", "wide", "quad", "deep")  # PASA_ATTN_* of pasa.h
+
+
+def attn_variant(shape: Shape, k_sel: int = 0) -> str:
+    """the form of the attention kernel that a sparse call with k_sel selected blocks takes, or (k_sel = 0) the dense one"""
+    v = load_library().pasa_attn_variant(ctypes.byref(shape.c()), k_sel)
+    if v < 0:
+        raise PasaError(v, "pasa_attn_variant")
+    return ATTN_VARIANTS[v]
 
 
 def _workspace(nbytes, device, ws):

@@ -221,6 +221,23 @@ def test_whole_forward_checks_every_stage_before_the_first_launch(P):
         assert call(_shape(P, kv_slices=12)) == EUNSUPPORTED and call(_shape(P, scale=-1.0)) == EINVAL and call(_shape(P, n=0)) == EINVAL
 
 
+def test_forms_of_the_attention_kernel(P):
+    """pasa_attn_variant: what it refuses, the names of the binding in the order of the header, one shape of every form"""
+    text = open(HEADER).read()
+    names = dict((n.lower(), int(v)) for n, v in re.findall(r"PASA_ATTN_([A-Z_]+) = (\d+)", text))
+    from paper_2604_12219_amd.pasa import ATTN_VARIANTS
+    assert {n: i for i, n in enumerate(ATTN_VARIANTS)} == names
+    for shape, k_sel, status in ((_shape(P), -1, -1), (_shape(P), 129, -1), (_shape(P, d=96), 0, -2), (_shape(P, group=48), 4, -2), (_shape(P, kv_slices=12), 4, -2)):
+        assert P.load_library().pasa_attn_variant(ctypes.byref(shape.c()), k_sel) == status
+        with pytest.raises(P.PasaError):
+            P.attn_variant(shape, k_sel)
+    assert P.attn_variant(_shape(P, group=48)) == "teams"  # (the dense path has no groups)
+    assert P.attn_variant(_shape(P, n=1400)) == "teams" and P.attn_variant(_shape(P, H=12, n=32_760)) == "wide"
+    assert P.attn_variant(_shape(P, n=32_768, kv_slices=8), 40) == "sliced" and P.attn_variant(_shape(P, H=4, n=4140), 10) == "deep"
+    assert P.attn_variant(_shape(P, H=40, n=75_600), 177) == "quad" and P.attn_variant(_shape(P, H=12, n=32_760), 102) == "whole"
+    assert P.attn_variant(_shape(P, H=40, n=75_600, group=16), 177) == "whole" and P.attn_variant(_shape(P, H=40, n=147_600, block=128), 58) == "whole"
+
+
 def _forward_bytes(P, s, keep):
     bh, nb = s.B * s.H, P.num_blocks(s)
     return (align256(bh * nb * nb * 4) + align256(bh * nb * P.topk_count(nb, keep) * 4) + align256(bh * nb * -(-nb // 32) * 4) +

@@ -55,6 +55,7 @@ def test_dense_in_two_teams_against_one_walk_per_query_tile(P, n, d):
     """the same heads in a grid of 32 workgroups per XCD (two teams of waves) and of 33 (one): equal up to the rounding of P and of
     the output to bf16, tolerances as for key-range slicing below"""
     q, k, v = (torch.cat([t] * 17, dim=1)[:, :33].contiguous() for t in _inputs((1, 1, n), 2, d, seed=n))
+    assert P.attn_variant(P.Shape.of(q[:, :32])) == "teams" and P.attn_variant(P.Shape.of(q)) != "teams"
     two, two_lse = P.attn_dense_ref(q[:, :32], k[:, :32], v[:, :32], P.Shape.of(q[:, :32]), want_lse=True)
     one, one_lse = P.attn_dense_ref(q, k, v, P.Shape.of(q), want_lse=True)
     torch.cuda.synchronize()
@@ -71,6 +72,7 @@ def test_dense_in_wide_workgroups(P, n, d):
     keys in the same order in both.  Last wide tiles of 1, 65, 128, 255 and 256 rows, last key tiles of 1, 63 and 64 keys, odd and even numbers of them"""
     q2, k2, v2 = _inputs((1, 1, n), 2, d, seed=n)
     q, k, v = (torch.cat([t] * 17, dim=1)[:, :33].contiguous() for t in (q2, k2, v2))
+    assert P.attn_variant(P.Shape.of(q[:, :32])) == "wide" and P.attn_variant(P.Shape.of(q)) == "whole"
     wide, wide_lse = P.attn_dense_ref(q[:, :32], k[:, :32], v[:, :32], P.Shape.of(q[:, :32]), want_lse=True)
     narrow, narrow_lse = P.attn_dense_ref(q, k, v, P.Shape.of(q), want_lse=True)
     torch.cuda.synchronize()
@@ -464,7 +466,7 @@ def test_workgroups_of_four_query_blocks_against_two(P, n, heads, group, kind):
     the bitmap, so the same bitmap is given to both.  Numbers of query blocks with 0 to 3 left over, ragged last blocks of 1 and 63 tokens; equal numbers
     of selected blocks (routed), very different ones in neighbouring rows, none and all of them (uneven), four rows alike, four rows without a common
     block, one block, no whole block at all in some rows (empty), as many key blocks as can be planned and a ragged one more"""
-    _compare_routes(P, n, max(heads, (512 << 10) // n + 1), 128, group, kind, 353)
+    _compare_routes(P, n, max(heads, (512 << 10) // n + 1), 128, group, kind, 353, "quad")
 
 
 @pytest.mark.parametrize("n,heads,d,group,kind", [
@@ -473,14 +475,15 @@ def test_workgroups_of_four_query_blocks_against_two(P, n, heads, group, kind):
 def test_ring_of_eight_tiles_against_four(P, n, heads, d, group, kind):
     """The same for small grids, where the declared number decides between rings of eight and of four tiles: odd and even numbers of
     shared and of private blocks, one query block running out of them before the other, ragged last blocks of 1, 8, 33 and 63 tokens"""
-    _compare_routes(P, n, heads, d, group, kind, 8)
+    _compare_routes(P, n, heads, d, group, kind, 8, "deep")
 
 
-def _compare_routes(P, n, heads, d, group, kind, declared):
+def _compare_routes(P, n, heads, d, group, kind, declared, variant):
     g = torch.Generator(device="cuda")
     g.manual_seed(n + heads)
     q, k, v = (torch.randn((1, heads, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
     shape = P.Shape.of(q, block=64, group=group)
+    assert P.attn_variant(shape, declared) == variant and P.attn_variant(shape, 1) == "whole"
     nb = P.num_blocks(shape)
     u = torch.rand((heads, nb, nb), generator=g, device="cuda")
     rows = torch.arange(nb, device="cuda")[:, None]
@@ -533,6 +536,7 @@ def test_values_of_a_ragged_block_that_a_neighbour_selected_stay_out(P, bad):
     g.manual_seed(3)
     q, k, v = (torch.randn((1, heads, n, 128), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
     shape = P.Shape.of(q, block=64, group=0)
+    assert P.attn_variant(shape, declared) == "quad"
     nb = P.num_blocks(shape)
     chosen = torch.rand((1, nb, nb), generator=g, device="cuda") < 0.02
     chosen[:, :, 0] = True
