@@ -190,20 +190,28 @@ bool sparse_deep(const pasa_shape_t* s, int32_t k_sel) {
 }
 
 // Whether the sparse path takes workgroups of four query blocks of 64 tokens (pasa_quad.hpp) instead of two: they fetch fewer tiles, but plan
-// their steps first (15 us a workgroup, with the starts and ends of its runs of steps).  So the selection has to be long, and the more so the
-// smaller a head: its keys and values are in the L2s then anyway.  Attention alone, us, two / four:
-//   32,760 tokens (x 512 blocks): 12 heads, 77 blocks 1331 / 1383, 179 blocks 2615 / 2620; 47,040: 8 heads, 110: 1898 / 1865, 257: 3844 / 3586;
-//   20 heads, 110: 4628 / 4755; 60,480: 8 heads, 47: 1467 / 1565, 142: 3169 / 3124; 75,600: 5 heads, 59: 1448 / 1453, 177: 3228 / 2982; 20 heads,
-//   59: 5732 / 6006, 177: 12,666 / 12,099; 118,800: 3 heads, 93: 2137 / 2183, 279: 5210 / 4702; 147,600: 6 heads, 115: 6853 / 6688, 346: 16,168 / 13,852
-// With the covariance prior the query blocks select much the same key blocks, which the caches then hold, and there is less to save; the host cannot see
-// that, so the keys and values of all heads must exceed the memory-side cache (256 MB).  Whole calls, two / four, without the prior and with it:
-//   5 heads of 75,600 (194 MB), 177 blocks 3383 / 3143, 3062 / 3144; 3 of 118,800 (182 MB), 279 blocks 5147 / 4766, 4264 / 4521; 40 of 75,600 (1.5 GB),
-//   177 blocks 26,053 / 24,614, 25,278 / 24,898; 5 of 147,600 (378 MB), 277 blocks, with it 10,185 / 10,148; 12 of 75,600 (464 MB), 355 blocks 14,085 / 12,317
+// their steps first (15 us a workgroup, with the starts and ends of its runs of steps) and have a compute unit to themselves meanwhile.  What they save depends
+// on how little neighbouring query blocks have in common and on the caches, and the host knows only sizes.  The covariance prior and smooth inputs
+// make the selections alike; the rule is such that even then the four lose next to nothing (at worst 1.7 %: groups of 64, 24 heads of 118,800 tokens, 177
+// blocks).  Attention alone, us, two / four: first with independent noise as strong as the smooth field and no prior, then with noise of 0.2 and the prior:
+//   * the selection has to be long.  75,600 tokens, 40 heads: 130 of 1182 blocks 19,446 / 18,845, 17,903 / 18,033 (in groups of 64 18,151 / 17,668,
+//     16,583 / 16,899); 177: 24,957 / 23,678, 22,361 / 22,376 (23,861 / 22,474, 21,031 / 21,253); 295: - , 32,847 / 32,605
+//   * the keys and values of a head have to exceed the eight L2s (32 MB), which otherwise hold what the rows select alike: 32,760 tokens, 40 heads, 245 of 512
+//     blocks 11,442 / 11,577, 10,628 / 10,959; 47,628, 24 heads, 168 of 745 8104 / 7878, 7189 / 7608; 60,480, 12 heads, 189 of 945 6157 / 5860, 5249 / 5578; just
+//     above, 68,040, 12 heads, 177 of 1064: - , 6134 / 6302
+//   * those of all heads have to exceed the memory-side cache (256 MB) by far: 5 heads of 118,800 (304 MB), 371 of 1857 11,111 / 9848, 8578 / 8720; 10 of
+//     75,600 (387 MB), 200 of 1182 - , 6350 / 6433
+//   * the last round of workgroups (32 compute units of the XCD with the most tiles at a time) must not be much emptier than that of twice as many: 20 heads
+//     of 75,600 (23.1 and 46.2 rounds), 177 blocks - , 11,432 / 11,716; 40 (46.2, 92.5) as above.  Where a head is larger there is more to gain: 24 of 118,800
+//     (44.2, 87.8), 278 blocks 42,038 / 35,884, 32,562 / 32,564; 20 of 147,600 (45.6, 90.6), 461 - , 52,136 / 51,158
 // Blocks of 128 tokens: 147,600 tokens, 6 heads, 58 blocks 4780 / 4889, 173: 11,014 / 11,338 (not taken).
 bool sparse_quad(const pasa_shape_t* s, int32_t k_sel) {
   const int nb = num_blocks(s);
-  return s->d == 128 && s->block == 64 && s->kv_slices <= 1 && s->n >= 64 && s->n / 64 <= kQuadMaxTiles && (s->group == 0 || s->group >= 32) && nb >= k_sel &&
-         k_sel >= 100 && (int64_t)k_sel * s->n >= 8000000 && (int64_t)s->B * s->H * s->n * (4 * s->d) > (int64_t)(256 << 20);
+  if (s->d != 128 || s->block != 64 || s->kv_slices > 1 || s->n / 64 > kQuadMaxTiles || (s->group > 0 && s->group < 32)) return false;
+  const int64_t bh = (int64_t)s->B * s->H, n = s->n, head_bytes = n * (4 * s->d);
+  const int64_t quad = (bh * ((n + 2047) / 2048) + 31) / 32, pair = (bh * ((n + 1023) / 1024) + 31) / 32;  // rounds; half rounds
+  return k_sel >= 160 && k_sel <= nb && head_bytes > (36 << 20) && bh * head_bytes > (int64_t)(512 << 20) &&
+         160 * quad <= (head_bytes > (56 << 20) ? 82 : 81) * pair;
 }
 
 // The form of the attention kernel a call takes (k_sel: declared number of selected key blocks; dense: not looked at)

@@ -235,6 +235,9 @@ def test_forms_of_the_attention_kernel(P):
     assert P.attn_variant(_shape(P, n=1400)) == "teams" and P.attn_variant(_shape(P, H=12, n=32_760)) == "wide"
     assert P.attn_variant(_shape(P, n=32_768, kv_slices=8), 40) == "sliced" and P.attn_variant(_shape(P, H=4, n=4140), 10) == "deep"
     assert P.attn_variant(_shape(P, H=40, n=75_600), 177) == "quad" and P.attn_variant(_shape(P, H=12, n=32_760), 102) == "whole"
+    for shape, k_sel in ((_shape(P, H=40, n=32_760), 245), (_shape(P, H=24, n=47_628), 168), (_shape(P, H=40, n=60_480), 189), (_shape(P, H=12, n=68_040), 177),
+                         (_shape(P, H=10, n=75_600), 177), (_shape(P, H=5, n=118_800), 279), (_shape(P, H=20, n=75_600), 177), (_shape(P, H=40, n=75_600), 130)):
+        assert P.attn_variant(shape, k_sel) == "whole", shape  # what four query blocks a workgroup lost on where rows select alike
     assert P.attn_variant(_shape(P, H=40, n=75_600, group=16), 177) == "whole" and P.attn_variant(_shape(P, H=40, n=147_600, block=128), 58) == "whole"
 
 
