@@ -181,12 +181,15 @@ bool dense_wide(const pasa_shape_t* s) {
 
 // Whether the sparse path with blocks of 64 tokens takes a ring of eight tiles instead of four.  The workgroup then has a compute unit to itself, so
 // only where no compute unit would get two (see dense_teams), and it pays where the walk is long enough: the blocks of one of the two query blocks then
-// take one barrier a step, and shared tiles arrive three steps ahead.  us, four / eight:
+// take one barrier a step, and shared tiles arrive three steps ahead.  Where nearly every block is selected there are hardly any blocks of one query block
+// alone, and it gains nothing: 7/8 of them is the line.  us, four / eight:
 //   d = 128: 4140 tokens, 4 heads, 3 of 65 blocks 18.6 / 19.4, 10: 30.3 / 29.4, 26: 52.4 / 49.8; 9900, 3 heads, 8 of 155: 32.5 / 31.8, 62: 102 / 97.5;
-//     32,760, 1 head, 26 of 512: 76.4 / 72.3; 2048, 16 heads, 13 of 32: 32.5 / 34.6
-//   d = 64: 4140, 4 heads, 3: 12.3 / 12.2, 10: 20.8 / 19.4, 26: 37.0 / 33.9; 9900, 3 heads, 62: 75.4 / 67.0; 32,760, 1 head, 77: 104 / 90.9
+//     32,760, 1 head, 26 of 512: 76.4 / 72.3; 2048, 16 heads, 13 of 32: 32.5 / 34.6; 4140, 6 heads, 52: 79.4 / 77.1, 58: 83.9 / 84.3, 65: 88.3 / 89.3
+//   d = 64: 4140, 4 heads, 3: 12.3 / 12.2, 10: 20.8 / 19.4, 26: 37.0 / 33.9; 9900, 3 heads, 62: 75.4 / 67.0; 32,760, 1 head, 77: 104 / 90.9;
+//     4140, 6 heads, 52: 57.6 / 55.4, 61: 62.5 / 62.4, 65: 64.0 / 65.0
 bool sparse_deep(const pasa_shape_t* s, int32_t k_sel) {
-  return s->block == 64 && s->kv_slices <= 1 && num_blocks(s) >= 64 && k_sel >= 8 && (int64_t)s->B * s->H * (((int64_t)s->n + 1023) / 1024) <= 32;
+  const int nb = num_blocks(s);
+  return s->block == 64 && s->kv_slices <= 1 && nb >= 64 && k_sel >= 8 && 8 * (int64_t)k_sel <= 7 * (int64_t)nb && (int64_t)s->B * s->H * (((int64_t)s->n + 1023) / 1024) <= 32;
 }
 
 // Whether the sparse path takes workgroups of four query blocks of 64 tokens (pasa_quad.hpp) instead of two: they fetch fewer tiles, but plan

@@ -234,6 +234,8 @@ def test_forms_of_the_attention_kernel(P):
     assert P.attn_variant(_shape(P, group=48)) == "teams"  # (the dense path has no groups)
     assert P.attn_variant(_shape(P, n=1400)) == "teams" and P.attn_variant(_shape(P, H=12, n=32_760)) == "wide"
     assert P.attn_variant(_shape(P, n=32_768, kv_slices=8), 40) == "sliced" and P.attn_variant(_shape(P, H=4, n=4140), 10) == "deep"
+    for d in (64, 128):  # nearly every block selected: the ring of eight tiles has nothing to gain
+        assert [P.attn_variant(_shape(P, H=6, n=4140, d=d), k) for k in (7, 8, 56, 57, 65)] == ["whole", "deep", "deep", "whole", "whole"]
     assert P.attn_variant(_shape(P, H=40, n=75_600), 177) == "quad" and P.attn_variant(_shape(P, H=12, n=32_760), 102) == "whole"
     for shape, k_sel in ((_shape(P, H=40, n=32_760), 245), (_shape(P, H=24, n=47_628), 168), (_shape(P, H=40, n=60_480), 189), (_shape(P, H=12, n=68_040), 177),
                          (_shape(P, H=10, n=75_600), 177), (_shape(P, H=5, n=118_800), 279), (_shape(P, H=20, n=75_600), 177), (_shape(P, H=40, n=75_600), 130)):
