@@ -120,7 +120,9 @@ enum {
   PASA_ATTN_TEAMS = 2,  /* dense: two teams of four waves, half of the keys each              */
   PASA_ATTN_WIDE = 3,   /* dense: eight waves, 256 query rows                                 */
   PASA_ATTN_QUAD = 4,   /* sparse: eight waves, four query blocks of 64 tokens                */
-  PASA_ATTN_DEEP = 5    /* sparse: two query blocks of 64 tokens, twice the tiles in flight   */
+  PASA_ATTN_DEEP = 5,   /* sparse: two query blocks of 64 tokens, twice the tiles in flight   */
+  PASA_ATTN_SHORT = 6,  /* dense, blocks of 128 tokens: PASA_ATTN_WHOLE, steps for few tiles  */
+  PASA_ATTN_SHORT_TEAMS = 7 /* dense: PASA_ATTN_TEAMS, steps for few tiles                    */
 };
 PASA_API int32_t pasa_attn_variant(const pasa_shape_t* shape, int32_t k_sel);
 

@@ -217,10 +217,24 @@ bool sparse_quad(const pasa_shape_t* s, int32_t k_sel) {
          160 * quad <= (head_bytes > (56 << 20) ? 82 : 81) * pair;
 }
 
+// Whether a walk (dense: every tile; sparse, blocks of 128 tokens: the selected ones) is too short for pipelined steps (pipe_step): a run of them
+// starts and ends with a half-empty one, and requests a tile that nobody needs.  `tiles` of 64 keys.  us, steps of one tile / pipelined:
+//   dense, d = 128: 1 tile, 1 head 6.5 / 6.9; 5, 1 head 10.6 / 10.8; 8 14.1 / 14.0; 12 17.9 / 17.0 (64 heads, 8 28.6 / 29.0, 16 48.8 / 46.8; 300, 1 30.0 / 30.7)
+//   dense, d = 64: 300 heads, 1 tile 17.0 / 18.8, 4 37.7 / 38.4; 1 head, 5 tiles 7.4 / 7.9; 8 9.5 / 9.7; 12 12.1 / 12.2; 16 14.8 / 14.8; 20 17.1 / 17.0
+//   blocks of 128, d = 128: 200 heads of 1024 tokens, 2 of 8 blocks 74.5 / 77.3, 4 104 / 106, 6 135 / 135, 8 168 / 166; 4140, 2 heads, 2 of 33 16.3 / 16.5, 6 25.5 /
+//     25.3, 16 50.4 / 48.6
+//   blocks of 128, d = 64: 4140, 2 heads, 2 of 33 11.0 / 11.3, 8 21.6 / 22.2, 24 47.8 / 48.4, 33 61.2 / 61.4; 40 heads, 8 93.6 / 94.6, 12 130 / 130, 32 303 / 299;
+//     32,760, 12 heads, 4 of 256 146 / 150, 16 342 / 340
+bool short_walk(const pasa_shape_t* s, bool sparse, int64_t tiles) { return tiles < (sparse ? (s->d == 128 ? 12 : 64) : (s->d == 128 ? 9 : 16)); }
+
 // The form of the attention kernel a call takes (k_sel: declared number of selected key blocks; dense: not looked at)
 AttnVariant attn_variant(const pasa_shape_t* s, bool sparse, int32_t k_sel) {
-  if (!sparse) return dense_teams(s) ? kTeams : dense_wide(s) ? kWide : kWhole;
+  if (!sparse) {
+    if (short_walk(s, false, ((int64_t)s->n + 63) / 64)) return dense_teams(s) ? kShortTeams : kShort;
+    return dense_teams(s) ? kTeams : dense_wide(s) ? kWide : kWhole;
+  }
   if (choose_slices(s) > 1) return kSliced;
+  if (s->block == 128) return short_walk(s, true, 2 * (int64_t)k_sel) ? kShort : kWhole;
   return sparse_deep(s, k_sel) ? kDeep : sparse_quad(s, k_sel) ? kQuad : kWhole;
 }
 

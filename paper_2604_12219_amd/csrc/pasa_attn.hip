@@ -306,7 +306,7 @@ struct BitWalk {
 // 2: sparse, two adjacent 64-token query blocks per workgroup.  MULTI: the group has fewer than 32
 // blocks, so a chunk of 32 blocks intersects several groups and the per-block weights of a chunk have
 // to be kept until all of its group matrices have passed.  PART: see AttnVariant.
-constexpr int teams_of(int part) { return part == kTeams ? 2 : 1; }
+constexpr int teams_of(int part) { return part == kTeams || part == kShortTeams ? 2 : 1; }
 constexpr int waves_of(int part) { return part == kWide || part == kQuad ? 8 : 4; }  // of a team
 template <int D, int MODE, bool MULTI, int PART>
 __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_kernel(AttnParams p) {
@@ -550,7 +550,7 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
     };
     auto whole = [&](int r) -> bool { return r >= 0 && r + 64 <= n; };
     int r_cur = plan(), pair = 0;
-    if constexpr (MODE == 0 || (MODE == 1 && PART == kWhole)) {
+    if constexpr ((MODE == 0 && PART != kShort && PART != kShortTeams) || (MODE == 1 && PART == kWhole)) {
       // Tiles whose 64 rows are all keys of the tile: pipelined steps, each with P V of one tile and the logits of the next.
       // K of tile t is in slot 2 (t & 1), V in the slot after it.  Against steps of one tile (fused_step), 12 heads of 32,760
       // tokens: 3.90 -> 3.47 ms with all-zero inputs (clock at its maximum: 3130 -> 2780 cycles a step of two workgroups, 2048 of
@@ -1105,6 +1105,8 @@ hipError_t launch_part(const AttnParams& p, int grid, hipStream_t stream) {
   if constexpr (MODE == 0) {
     if (p.variant == kTeams) return launch<D, MODE, MULTI, kTeams>(p, grid, stream);
     if (p.variant == kWide) return launch<D, MODE, MULTI, kWide>(p, grid, stream);
+    if constexpr (D == 64)  // (at d = 128 walks that two teams share are long enough)
+      if (p.variant == kShortTeams) return launch<D, MODE, MULTI, kShortTeams>(p, grid, stream);
   } else {
     if (p.variant == kSliced) return launch<D, MODE, MULTI, kSliced>(p, grid, stream);
     if constexpr (MODE == 2)
@@ -1112,6 +1114,8 @@ hipError_t launch_part(const AttnParams& p, int grid, hipStream_t stream) {
     if constexpr (D == kQuadDim && MODE == 2 && !MULTI)
       if (p.variant == kQuad) return launch<D, MODE, MULTI, kQuad>(p, grid, stream);
   }
+  if constexpr (MODE != 2)
+    if (p.variant == kShort) return launch<D, MODE, MULTI, kShort>(p, grid, stream);
   if (p.variant != kWhole) return hipErrorInvalidValue;  // (the grid is made for the variant)
   return launch<D, MODE, MULTI, kWhole>(p, grid, stream);
 }

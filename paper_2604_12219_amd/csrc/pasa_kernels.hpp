@@ -8,8 +8,9 @@
 // Forms of the attention kernel (attn_kernel in pasa_attn.hip); which call takes which: attn_variant in pasa_api.hip.
 // kWhole: a workgroup walks all keys of its 128 query rows; kSliced: key-range slicing (persistent workgroups, partial results); kTeams (dense): two
 // teams of waves with half of the keys each; kWide (dense): eight waves, 256 query rows; kQuad (sparse): eight waves, four query blocks of 64 tokens
-// (pasa_quad.hpp); kDeep (sparse, two 64-token blocks): a ring of eight tiles.  The numbers are those of PASA_ATTN_* in pasa.h.
-enum AttnVariant : int32_t { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3, kQuad = 4, kDeep = 5 };
+// (pasa_quad.hpp); kDeep (sparse, two 64-token blocks): a ring of eight tiles; kShort, kShortTeams: kWhole and kTeams with steps of one tile (dense, blocks of
+// 128 tokens), for walks too short for pipelined steps.  The numbers are those of PASA_ATTN_* in pasa.h.
+enum AttnVariant : int32_t { kWhole = 0, kSliced = 1, kTeams = 2, kWide = 3, kQuad = 4, kDeep = 5, kShort = 6, kShortTeams = 7 };
 
 struct AttnParams {
   const uint16_t* q;

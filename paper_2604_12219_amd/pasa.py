@@ -209,7 +209,7 @@ def attn_workspace_bytes(shape: Shape) -> int:
     return load_library().pasa_attn_workspace_bytes(ctypes.byref(shape.c()))
 
 
-ATTN_VARIANTS = ("whole", "sliced", "teams", "wide", "quad", "deep")  # PASA_ATTN_* of pasa.h
+ATTN_VARIANTS = ("whole", "sliced", "teams", "wide", "quad", "deep", "short", "short_teams")  # PASA_ATTN_* of pasa.h
 
 
 def attn_variant(shape: Shape, k_sel: int = 0) -> str:

@@ -234,6 +234,13 @@ def test_forms_of_the_attention_kernel(P):
     assert P.attn_variant(_shape(P, group=48)) == "teams"  # (the dense path has no groups)
     assert P.attn_variant(_shape(P, n=1400)) == "teams" and P.attn_variant(_shape(P, H=12, n=32_760)) == "wide"
     assert P.attn_variant(_shape(P, n=32_768, kv_slices=8), 40) == "sliced" and P.attn_variant(_shape(P, H=4, n=4140), 10) == "deep"
+    # walks of few tiles: dense (the last two sizes in front of the line and behind it), alone and in a grid that teams are too many for; blocks of 128
+    assert [P.attn_variant(_shape(P, H=1, n=n)) for n in (64, 512, 513, 704, 705)] == ["short", "short", "whole", "whole", "teams"]
+    assert [P.attn_variant(_shape(P, H=300, n=n)) for n in (64, 512)] == ["short", "short"]
+    assert [P.attn_variant(_shape(P, H=1, n=n, d=64)) for n in (64, 448, 449, 960, 961)] == ["short", "short", "short_teams", "short_teams", "teams"]
+    assert [P.attn_variant(_shape(P, H=300, n=n, d=64)) for n in (64, 960)] == ["short", "short"]
+    assert [P.attn_variant(_shape(P, block=128), k) for k in (1, 5, 6, 64)] == ["short", "short", "whole", "whole"]
+    assert [P.attn_variant(_shape(P, block=128, d=64), k) for k in (1, 31, 32, 64)] == ["short", "short", "whole", "whole"]
     for d in (64, 128):  # nearly every block selected: the ring of eight tiles has nothing to gain
         assert [P.attn_variant(_shape(P, H=6, n=4140, d=d), k) for k in (7, 8, 56, 57, 65)] == ["whole", "deep", "deep", "whole", "whole"]
     assert P.attn_variant(_shape(P, H=40, n=75_600), 177) == "quad" and P.attn_variant(_shape(P, H=12, n=32_760), 102) == "whole"

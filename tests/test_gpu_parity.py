@@ -55,7 +55,8 @@ def test_dense_in_two_teams_against_one_walk_per_query_tile(P, n, d):
     """the same heads in a grid of 32 workgroups per XCD (two teams of waves) and of 33 (one): equal up to the rounding of P and of
     the output to bf16, tolerances as for key-range slicing below"""
     q, k, v = (torch.cat([t] * 17, dim=1)[:, :33].contiguous() for t in _inputs((1, 1, n), 2, d, seed=n))
-    assert P.attn_variant(P.Shape.of(q[:, :32])) == "teams" and P.attn_variant(P.Shape.of(q)) != "teams"
+    assert P.attn_variant(P.Shape.of(q[:, :32])) == ("short_teams" if n < 961 and d == 64 else "teams")
+    assert P.attn_variant(P.Shape.of(q)) in ("short", "whole", "wide")
     two, two_lse = P.attn_dense_ref(q[:, :32], k[:, :32], v[:, :32], P.Shape.of(q[:, :32]), want_lse=True)
     one, one_lse = P.attn_dense_ref(q, k, v, P.Shape.of(q), want_lse=True)
     torch.cuda.synchronize()
@@ -482,6 +483,34 @@ def test_ring_of_eight_tiles_against_four(P, n, heads, d, group, kind):
     """The same for small grids, where the declared number decides between rings of eight and of four tiles: odd and even numbers of
     shared and of private blocks, one query block running out of them before the other, ragged last blocks of 1, 8, 33 and 63 tokens"""
     _compare_routes(P, n, heads, d, group, kind, 8, "deep")
+
+
+@pytest.mark.parametrize("n,heads,d,group,kind", [
+    (1500, 3, 128, 32, "routed"), (1409, 2, 128, 8, "uneven"), (1536, 2, 128, 0, "one"), (4140, 2, 64, 32, "routed"), (4097, 2, 64, 16, "uneven"),
+    (4160, 1, 64, 0, "one")])
+def test_blocks_of_128_in_short_walks_against_pipelined_steps(P, n, heads, d, group, kind):
+    """The declared number of blocks decides between steps of one tile and pipelined ones; a tile's keys are met in the same order and the same halves in
+    both, so the results have the same bits.  Ragged last blocks of 1, 44, 64, 92 tokens and none; rows of one block, of none but the ragged one, of all"""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn((1, heads, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    shape = P.Shape.of(q, block=128, group=group)
+    nb, few = P.num_blocks(shape), 5 if d == 128 else 31
+    assert P.attn_variant(shape, few) == "short" and P.attn_variant(shape, few + 1) == "whole"
+    if kind == "routed":
+        _, mask = P.route(P.block_score(q, k, shape), nb // 3, 5, 0.5)
+    else:
+        chosen = torch.rand((heads, nb, nb), generator=g, device="cuda") < torch.linspace(-0.3, 1.3, nb, device="cuda")[:, None]
+        if kind == "one":
+            chosen = (torch.arange(nb, device="cuda")[:, None] == torch.arange(nb, device="cuda").flip(0)).expand(heads, -1, -1).clone()
+        chosen[:, :, nb - 1] |= ~chosen.any(-1)
+        mask = _bitmap(chosen)
+    ws = P.kv_stats(k, v, shape, ws=torch.empty(P.attn_workspace_bytes(shape), dtype=torch.uint8, device="cuda"))
+    short, short_lse = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, want_lse=True, prepared=True, k_sel=few)
+    whole, whole_lse = P.sparse_attn_fwd(q, k, v, shape, None, mask, ws=ws, want_lse=True, prepared=True, k_sel=few + 1)
+    torch.cuda.synchronize()
+    assert torch.isfinite(whole.float()).all()
+    assert torch.equal(short, whole) and torch.equal(short_lse, whole_lse)
 
 
 def _compare_routes(P, n, heads, d, group, kind, declared, variant):
