@@ -173,10 +173,14 @@ bool dense_teams(const pasa_shape_t* s) {
 //   d = 128: 7 heads of 4140 (35 narrow / 21 wide tiles on an XCD) 113 / 111; 12 (60 / 36) 132 / 229; 24 (120 / 72) 257 / 357;
 //     6 of 9900 (60 / 30) 291 / 281; 26 (260 / 130) 1273 / 1362; 2 of 32,760 (64 / 32) 976 / 936; 3 (96 / 48) 1475 / 1562
 //   d = 64: 7 of 4140 82.5 / 80.0; 12 86.6 / 159; 6 of 9900 195 / 193; 2 of 32,760 616 / 594
+// At d = 64 a tile's loads are half as much and what a round of wide workgroups takes to start and to end counts for more, while over several rounds the two
+// narrow ones of a compute unit cover each other's: there it is left at one round, two where the walk is long.  us, the code before this path and its pipelined
+// steps / narrow / wide: 16 heads of 4096 (1 round) 89.5 / - / 86.0; 64 of 2048 (2) 92.6 / - / 94.6; 8 of 16,384 (2) 619 / - / 602; 96 of 2048 (3) 139 / 137 /
+// 142; 128 (4) 182 / 178 / 188; 64 of 8192 (8) 1250 / 1206 / 1287; 12 of 32,760 (6) 3532 / 3431 / 3461
 bool dense_wide(const pasa_shape_t* s) {
   const int64_t bh = (int64_t)s->B * s->H, n = s->n;
   const int64_t wide = (bh * ((n + 2047) / 2048) + 31) / 32, narrow = (bh * ((n + 1023) / 1024) + 31) / 32;  // rounds; half rounds
-  return 62 * wide <= 32 * narrow;
+  return 62 * wide <= 32 * narrow && (s->d == 128 || wide <= (n > 8192 ? 2 : 1));
 }
 
 // Whether the sparse path with blocks of 64 tokens takes a ring of eight tiles instead of four.  The workgroup then has a compute unit to itself, so

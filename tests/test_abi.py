@@ -241,6 +241,9 @@ def test_forms_of_the_attention_kernel(P):
     assert [P.attn_variant(_shape(P, H=300, n=n, d=64)) for n in (64, 960)] == ["short", "short"]
     assert [P.attn_variant(_shape(P, block=128), k) for k in (1, 5, 6, 64)] == ["short", "short", "whole", "whole"]
     assert [P.attn_variant(_shape(P, block=128, d=64), k) for k in (1, 31, 32, 64)] == ["short", "short", "whole", "whole"]
+    assert [P.attn_variant(_shape(P, H=h, n=2048, d=64)) for h in (32, 64, 96, 128)] == ["wide", "whole", "whole", "whole"]
+    assert [P.attn_variant(_shape(P, H=h, n=9900, d=64)) for h in (6, 12, 18, 40)] == ["wide", "wide", "whole", "whole"]
+    assert [P.attn_variant(_shape(P, H=h, n=2048)) for h in (32, 64, 96, 128)] == ["wide"] * 4
     for d in (64, 128):  # nearly every block selected: the ring of eight tiles has nothing to gain
         assert [P.attn_variant(_shape(P, H=6, n=4140, d=d), k) for k in (7, 8, 56, 57, 65)] == ["whole", "deep", "deep", "whole", "whole"]
     assert P.attn_variant(_shape(P, H=40, n=75_600), 177) == "quad" and P.attn_variant(_shape(P, H=12, n=32_760), 102) == "whole"
