@@ -247,7 +247,12 @@ AttnVariant attn_variant(const pasa_shape_t* s, bool sparse, int32_t k_sel) {
 //   d = 128: 1024 tokens, 16 heads (4) 21.9 / 16.6; 2048, 40 (21) 39.3 / 29.4; 4140, 12 (13) 30.0 / 23.9; 9900, 16 (41) 52.3 / 47.8; 32,760, 2 (17)
 //     37.5 / 28.7; 75,600, 1 (19) 40.6 / 30.4; 118,800, 3 (91) 119 / 126; 75,600, 5 (97) 112 / 128; 32,760, 12 (101) 101 / 119
 //   d = 64: 2048, 40 (10) 23.7 / 17.3; 9900, 12 (15) 26.5 / 19.2; 32,760, 4 (17) 27.5 / 20.8; 32,760, 12 (50) 48.1 / 47.7
-bool stats_and_score_together(const pasa_shape_t* s) { return (int64_t)s->B * s->H * s->n * s->d <= ((int64_t)20 << 20); }
+// At d = 128 512 units of the statistics run at a time: where there are as many, nothing is idle that the pooling could fill, and it is only held back.  Whole
+// forwards, us: 256 tokens, 256 heads (256 units) 92.0 / 88.6, 512 heads 155 / 159; 128 tokens, 1024 heads 266 / 272; 64 tokens, 2048 410 / 416; d = 64, 64
+// tokens, 2048 heads 235 / 233.
+bool stats_and_score_together(const StatsParams& t) {
+  return (int64_t)t.bh * t.n * t.d <= ((int64_t)20 << 20) && (t.d == 64 || (int64_t)t.bh * t.n_units < 512);
+}
 
 constexpr int kMaxDevices = 64;
 std::atomic<void*> g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each device, null until looked up
@@ -669,7 +674,7 @@ static int forward_stages(const void* q, const void* k, const void* v, const pas
   if (rc != PASA_OK) return rc;
 
   const hipStream_t on = static_cast<hipStream_t>(stream);
-  if (approx && stats_and_score_together(shape)) {
+  if (approx && stats_and_score_together(t)) {
     if (pasa_launch_stats_and_score(t, p, on) != hipSuccess) return PASA_EHIP;
   } else {
     if (approx && pasa_launch_kv_stats(t, on) != hipSuccess) return PASA_EHIP;

@@ -839,10 +839,10 @@ def test_random_configurations_against_oracle(P, case):
 
 @pytest.mark.parametrize("n,heads,d,block,group,batch", [
     (100, 1, 128, 64, 32, 1), (1023, 3, 64, 64, 32, 1), (4140, 4, 128, 64, 64, 1), (4097, 9, 64, 128, 16, 2), (3000, 2, 128, 64, 0, 1),
-    (2113, 1, 128, 64, 1000, 2), (40960, 4, 128, 64, 32, 1), (40961, 4, 128, 64, 32, 1)])
+    (2113, 1, 128, 64, 1000, 2), (40960, 4, 128, 64, 32, 1), (40961, 4, 128, 64, 32, 1), (130, 511, 128, 64, 32, 1), (130, 256, 128, 64, 32, 2)])
 def test_forward_leaves_what_its_stages_leave(P, n, heads, d, block, group, batch):
-    """Statistics and scoring share launches in a whole forward up to 20 Mi elements (the last two sizes are the line): the same bits as the stages one
-    by one, for both origins of the block-mean keys, with and without a second launch over the units of a group, heads dealt by XCD or not"""
+    """Statistics and scoring share launches in a whole forward up to 20 Mi elements (40,960 and 40,961 tokens are the line) and below 512 units of the
+    statistics (511 and 512 heads): the same bits as the stages one by one, for both origins of the block-mean keys, with and without a second launch over the units of a group, heads dealt by XCD or not"""
     g = torch.Generator(device="cuda")
     g.manual_seed(n)
     q, k, v = (torch.randn((batch, heads, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
