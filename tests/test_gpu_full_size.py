@@ -87,8 +87,8 @@ def test_full_size_dense_reference_sampled_against_oracle(P):
 @pytest.mark.parametrize("name,head", [("wan14b-720p", 20), ("long-video", 33), ("wan1.3b-480p", 7)])
 def test_whole_head_of_a_full_size_workload_against_oracle(P, name, head):
     """Every query block of one head in the middle of the launch, all heads launched as bench.py launches them: covers
-    every slot of the kernel's workgroup-id decode for that head and the ragged last query tile (two 64-token query
-    blocks per workgroup at the 14B and 480p shapes, one 128-token block at the long-video shape).  Routing bit for
+    every slot of the kernel's workgroup-id decode for that head and the ragged last query tile (four 64-token query
+    blocks per workgroup at the 14B shape, two at the 480p shape, one 128-token block at the long-video shape).  Routing bit for
     bit, output and lse row by row."""
     w = workloads.WORKLOADS[name]
     q, k, v = workloads.make_workload_qkv(w, device="cuda")

@@ -562,6 +562,52 @@ def _compare_routes(P, n, heads, d, group, kind, declared, variant):
     np.testing.assert_allclose(lse4.cpu().numpy(), lse2.cpu().numpy(), atol=1e-3)
 
 
+@pytest.mark.parametrize("variant,n,d,block,declared", [
+    ("quad", 75841, 128, 64, 353), ("quad", 75810, 128, 64, 353), ("deep", 4161, 128, 64, 8), ("deep", 4131, 64, 64, 8), ("whole", 1345, 128, 64, 4),
+    ("whole", 1500, 128, 128, 6), ("short", 1409, 64, 128, 3), ("wide", 1089, 128, 64, 0), ("wide", 1281, 64, 64, 0), ("teams", 1345, 128, 64, 0),
+    ("short_teams", 575, 64, 64, 0), ("short", 300, 128, 64, 0)])
+def test_forms_of_the_kernel_respect_strides_batch_and_scale(P, variant, n, d, block, declared):
+    """Every form of the attention kernel (declared = 0: dense) on views of token-major storage [B, n, H, d + pad], batch 2, a scale of the caller's and a
+    ragged last block: the bits of the contiguous run, nothing written beside the output (the inputs' padding holds NaN), and the oracle's values"""
+    B, scale, group = 2, 0.07, 32
+    of = lambda h: P.Shape(B, h, n, d, block, group, h * n * d, n * d, d, scale)
+    heads = next(h for h in range(1, 41) if P.attn_variant(of(h), declared) == variant)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    q, k, v = (torch.randn((B, heads, n, d), generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    big = torch.full((4, B, n, heads, d + 8), float("nan"), dtype=torch.bfloat16, device="cuda")
+    big[3] = 7.0
+    for i, t in enumerate((q, k, v)):
+        big[i, :, :, :, :d] = t.permute(0, 2, 1, 3)
+    qs, ks, vs, out_s = (big[i, :, :, :, :d].permute(0, 2, 1, 3) for i in range(4))
+    shape, strided = of(heads), P.Shape.of(qs, block=block, group=group, scale=scale)
+    assert P.attn_variant(strided, declared) == variant
+    if declared:
+        nb = P.num_blocks(shape)
+        idx, mask = P.route(P.block_score(q, k, shape), min(declared, 60), 9, 0.5)
+        out, lse = P.sparse_attn_fwd(q, k, v, shape, None, mask, want_lse=True, k_sel=declared)
+        _, lse_s = P.sparse_attn_fwd(qs, ks, vs, strided, None, mask, out=out_s, want_lse=True, k_sel=declared)
+    else:
+        out, lse = P.attn_dense_ref(q, k, v, shape, want_lse=True)
+        _, lse_s = P.attn_dense_ref(qs, ks, vs, strided, out=out_s, want_lse=True)
+    torch.cuda.synchronize()
+    assert torch.equal(out_s, out) and torch.equal(lse_s, lse)
+    assert (big[3, :, :, :, d:] == 7.0).all()
+    last = tuple(to_f64(t[-1:, -1:]) for t in (q, k, v))
+    got, got_lse = to_f64(out[-1:, -1:]), lse[-1].cpu().numpy()
+    if declared:
+        blocks = sorted({0, nb // 2, nb - 3, nb - 2, nb - 1})
+        res = oracle.pasa_attention(*last, idx[-1:].cpu().numpy(), block, group=group, scale=scale, q_blocks=blocks, return_all=True)
+        rows = np.concatenate([np.arange(j * block, min((j + 1) * block, n)) for j in blocks])
+        ref, ref_lse = res["o"][:, rows], res["lse"][0, rows]
+    else:
+        rows = np.unique(np.concatenate([np.arange(0, n, 7), np.arange(n - 70, n)]))
+        ref, ref_lse = oracle.dense_attention(*last, scale=scale, q_rows=rows, return_lse=True)
+        ref_lse = ref_lse[0]
+    assert_close(got[:, rows], ref, what=f"{variant} n={n} d={d}")
+    np.testing.assert_allclose(got_lse[rows], ref_lse, atol=2e-2)
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_values_of_a_ragged_block_that_a_neighbour_selected_stay_out(P, bad):
     """workgroups of four query blocks fetch the ragged last key block for whichever of them selected it; without the approximation a query
