@@ -608,6 +608,43 @@ def test_forms_of_the_kernel_respect_strides_batch_and_scale(P, variant, n, d, b
     np.testing.assert_allclose(got_lse[rows], ref_lse, atol=2e-2)
 
 
+@pytest.mark.parametrize("variant,n,d,block,group,step,declared", [
+    ("whole", 133 * 64 - 9, 128, 64, 96, 2.0, 1), ("whole", 133 * 64 - 9, 64, 64, 96, 2.0, 1), ("whole", 133 * 128 - 70, 128, 128, 128, 1.5, 8),
+    ("short", 133 * 128 - 70, 128, 128, 128, 1.5, 1), ("deep", 133 * 64 - 9, 128, 64, 1000, 1.5, 8), ("deep", 133 * 64 - 9, 64, 64, 96, 2.0, 8),
+    ("quad", 75610, 128, 64, 320, 0.5, 353)])
+def test_weights_of_a_group_follow_a_maximum_that_grows_within_it(P, variant, n, d, block, group, step, declared):
+    """A group's first-order term takes the summed weights of its chunks of 32 blocks, each relative to the maximum at its time.  Here every row selects the
+    last block, whose logits are low, and the mean-key logits rise by `step` from chunk to chunk: sums that stayed relative to an older maximum would
+    count e^step times too much a chunk.  The first component of the keys carries the logit and a deviation of +-1/2 that the values follow, so the
+    first-order term is half as large as the zeroth one; both are exact in bf16"""
+    of = lambda h: P.Shape(1, h, n, d, block, group, h * n * d, n * d, d)
+    heads = next(h for h in range(1, 41) if P.attn_variant(of(h), declared) == variant)
+    shape = of(heads)
+    nb = P.num_blocks(shape)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + d)
+    rnd = lambda *size: torch.randn(size, generator=g, device="cuda")
+    token = torch.arange(n, device="cuda")
+    chunk = token // (32 * block)
+    side = (token % 2).float() * 2 - 1
+    q, k, v = rnd(n, d), 0.1 * rnd(n, d), 1.0 + 0.3 * rnd(n, d) + side[:, None]
+    q[:, 0] = d ** 0.5
+    k[:, 0] = torch.where(chunk == chunk[-1], torch.full_like(side, -4.0), step * chunk) + side / 2
+    q, k, v = (t.to(torch.bfloat16).expand(1, heads, n, d).contiguous() for t in (q, k, v))
+    idx = torch.full((heads, nb, 1), nb - 1, dtype=torch.int32, device="cuda")
+    out, lse = P.sparse_attn_fwd(q, k, v, shape, None, _bitmap(torch.arange(nb, device="cuda").expand(heads, nb, nb) == nb - 1), want_lse=True, k_sel=declared)
+    torch.cuda.synchronize()
+    blocks = sorted({0, 1, 2, 3, nb // 2, nb - 2, nb - 1})
+    first = tuple(to_f64(t[:, :1]) for t in (q, k, v))
+    res = oracle.pasa_attention(*first, idx[:1].cpu().numpy(), block, group=group, q_blocks=blocks, return_all=True)
+    rows = np.concatenate([np.arange(j * block, min((j + 1) * block, n)) for j in blocks])
+    part = np.abs(res["parts"][0, rows])
+    assert part[:, 2].mean() > 0.3 * part[:, 1].mean()  # the term is there
+    for h in {0, heads - 1}:
+        assert_close(to_f64(out[:, h:h + 1])[:, rows], res["o"][:, rows], what=f"{variant} head {h}")
+        np.testing.assert_allclose(lse[h].cpu().numpy()[rows], res["lse"][0, rows], atol=2e-2)
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])
 def test_values_of_a_ragged_block_that_a_neighbour_selected_stay_out(P, bad):
     """workgroups of four query blocks fetch the ragged last key block for whichever of them selected it; without the approximation a query
