@@ -33,7 +33,8 @@
 // (Nothing goes through the workspace: callers may share one among calls that overlap.)  The rule is in pasa_api.hip
 // (dense_teams).
 //
-// Dense path, grids that keep the device busy with workgroups of 256 query rows: eight waves share every tile (dense_wide).
+// Dense path, grids that keep the device busy with workgroups of 256 query rows: eight waves share every tile (dense_wide).  Sparse path: four query blocks of 64
+// tokens a workgroup (sparse_quad, pasa_quad.hpp), or a ring of eight tiles (sparse_deep).
 //
 // Data movement.  All tiles (K, V, block statistics, group matrices) are 64-row tiles that stream
 // through a ring of four 16 KB LDS buffers by direct global->LDS loads: the exact passes consume a
@@ -453,7 +454,8 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
   // the workgroups of an XCD no longer set out together: with two 64-token blocks per workgroup and more keys than the
   // L2s hold, 4 % more tile reads miss (40 heads of 75,600 tokens, 15 % of the blocks: 174 -> 181 GB), which costs more than it
   // gives where memory is what bounds the launch.  So two-block workgroups do it while K and V of a head fit the eight L2s
-  // (32 MB) or those of all heads the memory-side cache (256 MB).  Ascending throughout / own blocks first, us, on cards with a
+  // (32 MB) or those of all heads the memory-side cache (256 MB).  (Workgroups of four query blocks, which 40 heads of 75,600 at 15 % take, have an order
+  // of their own; what follows are two-block workgroups throughout.)  Ascending throughout / own blocks first, us, on cards with a
   // high and a low clock: d = 128, blocks of 64: 12 heads of 32,760 tokens 1686 / 1664, 1784 / 1766; 40 of 32,760 5666 / 5575, 5955 / 5800;
   // 5 of 75,600 (the whole call, routing with the prior) 3175 / 3121; 3 of 118,800 4979 / 5002, 5017 / 4991; 10 of 75,600 6464 / 6452,
   // 6837 / 6822; 20 of 75,600 12,521 / 12,665, 13,490 / 13,319; 40 of 75,600 24,911 / 25,390, 26,882 / 26,360.  Blocks of 128: 40 of 147,600
@@ -556,7 +558,8 @@ __global__ void __launch_bounds__(teams_of(PART) * waves_of(PART) * 64, 2) attn_
       // tokens: 3.90 -> 3.47 ms with all-zero inputs (clock at its maximum: 3130 -> 2780 cycles a step of two workgroups, 2048 of
       // them MFMAs), 5.89 -> 5.65 ms with random ones (where the power limit sets the clock, so that what a step moves and
       // switches counts more than its cycles); 4140 tokens, 4 heads: 74.7 -> 67.6 us.  Blocks of 128 tokens,
-      // 147,600 tokens: 6 heads, 58 blocks 4850 -> 4698, 173 blocks 11,310 -> 10,821.
+      // 147,600 tokens: 6 heads, 58 blocks 4943 -> 4823, 173 blocks 11,306 -> 11,005; the whole call of 40 heads, 58 blocks 34,407 -> 33,575.  Walks of few
+      // tiles have no use for them (short_walk in pasa_api.hip; kShort, kShortTeams).
       // (Two 64-token blocks a workgroup gain nothing: their shared pass is short, and a run of pipelined steps starts and ends with half
       // empty ones: 4 heads of 4140 tokens 29.6 -> 30.1 us, 12 of 32,760 1660 -> 1647.)
       if (r_cur >= 0) request(kb, r_cur, 0);

@@ -5,6 +5,7 @@
 // flight).  Two query blocks that stream the union of their selections fetch 257 key blocks for 354 selected ones (75,600 tokens, 15 %),
 // four fetch 373 for 708.  Attention alone, us, workgroups of two query blocks / of four: 75,600 tokens, 40 heads, 177 of 1182 blocks
 // 24,912 / 24,034; 5 heads 3228 / 2982, 414 blocks 6631 / 5732; 118,800 tokens, 3 heads, 279 of 1857 blocks 5210 / 4702, 650 blocks 10,541 / 8776.
+// (What the rule, sparse_quad in pasa_api.hip, leaves to two query blocks of these: few heads, whose selections may be alike.)
 // What is left of the time is power: with all-zero inputs 10 heads of the first take 6.3 / 5.0 ms, with random ones 6.5 / 6.0.
 //
 // Classes and runs.  A key block belongs to the class of the groups that selected it (15 classes of four groups).  One block each of some
